@@ -277,9 +277,6 @@ __global__ void k_gate(int64_t n, int E, double calib, double thr, const soap_rv
   fallback[i] = (bad || !(err < thr)) ? 1 : 0;
 }
 
-// coef[n][k] = sum_p (D[n][p] - mean[p]) V[p][k] (mean row mean_idx[n] when
-// given): 64 x 64 tile per block of
-// 256 threads (4 x 4 outputs each), K in steps of 32 through LDS, FP32
 // Network inputs of one sample from its raw description r = (lat, lon,
 // radius, contrast, phase, T_eff, inclination, v sin i) in degrees, R*, K
 // and km/s: the spot latitude scaled to +-60 deg, the sine and cosine of
@@ -310,51 +307,154 @@ __global__ void __launch_bounds__(256) k_features(int64_t n, const double* __res
   o[11] = 1.0f;
 }
 
-__global__ void __launch_bounds__(256) k_pca_project(int n, int P, int k, const float* __restrict__ D,
-                                                     int64_t ldd, const float* __restrict__ mean,
-                                                     const int* __restrict__ mean_idx, int n_mean,
-                                                     const float* __restrict__ V, float* __restrict__ coef) {
-  __shared__ float sA[32][64 + 1];
-  __shared__ float sB[32][64 + 1];
-  const int r0 = blockIdx.x * 64, c0 = blockIdx.y * 64;  // rows on x: up to 2^25 / 64 blocks
-  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-  float acc[4][4] = {};
-  for (int p0 = 0; p0 < P; p0 += 32) {
-    for (int t = threadIdx.x; t < 32 * 64; t += 256) {
-      const int pp = t & 31, rr = t >> 5;  // A: row rr, pixel pp (coalesced over pixels)
-      const int row = r0 + rr, pix = p0 + pp;
-      int mi = (mean_idx && row < n) ? mean_idx[row] : 0;
-      const bool bad = mi < 0 || mi >= n_mean;  // no such centre: the row's coefficients are NaN
-      mi = bad ? 0 : mi;
-      const float* mrow = mean + (int64_t)mi * P;
-      sA[pp][rr] = (row < n && pix < P) ? (bad ? __builtin_nanf("") : D[(int64_t)row * ldd + pix] - mrow[pix]) : 0.f;
-      const int cc = t & 63, pq = t >> 6;  // B: pixel pq < 32, component cc
-      const int pb = p0 + pq, col = c0 + cc;
-      sB[pq][cc] = (pb < P && col < k) ? V[(int64_t)pb * k + col] : 0.f;
-    }
-    __syncthreads();
-#pragma unroll 8
-    for (int pp = 0; pp < 32; ++pp) {
-      float a[4], b[4];
+// coef[n][k] = sum_p (D[n][p] - mean[p]) V[p][k] (mean row mean_idx[n] when
+// given), FP32 on the matrix cores (v_mfma_f32_16x16x4_f32).  A block of PCA_W
+// waves makes a tile of 16 MT rows x 64 components; the waves split the pixels
+// (16 at a time, in turn, so a block reads its rows in contiguous stretches)
+// and their partial tiles are added in wave order through LDS, so results
+// repeat bit for bit.  Lane l holds, for row l % 16, the four pixels
+// 4 (l / 16) + s of a step's 16 (one 16-byte load; MFMA s takes pixel s of
+// every lane) and, for each of those pixels, the components 4 (l % 16) + c
+// (one 16-byte load of a row of V; component tile c).
+// Bound by the FP32 matrix rate (16 MFMAs of 32 cycles per step and wave) and
+// the loads of V from L2 (every row tile reads its 64 columns of V).  2048
+// rows x 20000 pixels x 128 components: 126 us (83 TFLOP/s; a large FP32
+// matrix product reaches 149), against 4.85 ms as 64 x 64 tiles on 64 blocks
+// with vector FMAs; 8192 rows: 482 us.  Sixteen waves per block take 139 us,
+// two steps in flight 125 us, and a step that subtracts the mean as it loads
+// (so that every load is waited for at once) 209 us.
+constexpr int PCA_W = 8;   // waves per block
+constexpr int PCA_N = 64;   // components per block
+constexpr int PCA_D = 3;   // steps of 16 pixels in flight per wave
+
+typedef float pca_f4 __attribute__((ext_vector_type(4), aligned(4)));  // any element alignment
+
+// C4: 16-byte loads from the rows of V (k a multiple of 4; lanes past k repeat
+// the last four components, which are not stored)
+template <int MT, bool C4>
+__global__ void __launch_bounds__(64 * PCA_W) k_pca_project(int n, int P, int k, const float* __restrict__ D,
+                                                            int64_t ldd, const float* __restrict__ mean,
+                                                            const int* __restrict__ mean_idx, int n_mean,
+                                                            const float* __restrict__ V, float* __restrict__ coef) {
+  __shared__ float s_part[PCA_W / 2][16 * MT][PCA_N + 4];
+  const int l = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int64_t r0 = (int64_t)blockIdx.x * 16 * MT;  // rows on x: up to 2^25 / 16 blocks
+  const int c0 = blockIdx.y * PCA_N;
+  const int lk = 4 * (l >> 4), lc = c0 + 4 * (l & 15);
+  const float* drow[MT];
+  const float* mrow[MT];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        a[u] = sA[pp][ty * 4 + u];
-        b[u] = sB[pp][tx * 4 + u];
+  for (int a = 0; a < MT; ++a) {
+    const int64_t row = min(r0 + 16 * a + (l & 15), (int64_t)n - 1);  // rows past n are not stored
+    const int mi = mean_idx ? mean_idx[row] : 0;
+    drow[a] = D + row * ldd + lk;
+    mrow[a] = lk + mean + (int64_t)(mi >= 0 && mi < n_mean ? mi : 0) * P;  // no such centre: NaN at the store
+  }
+  unsigned vo[4];  // the lane's part of its offsets in V
+#pragma unroll
+  for (int c = 0; c < 4; ++c) vo[c] = (unsigned)lk * k + (C4 ? min(lc, k - 4) + c : min(lc + c, k - 1));
+  f32x4 acc[MT][4];
+#pragma unroll
+  for (int a = 0; a < MT; ++a)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) acc[a][c] = f32x4{0.f, 0.f, 0.f, 0.f};
+  // Loads keep their raw values until they are used, PCA_D - 1 steps later, and
+  // are unconditional (past the wave's last whole step they repeat it), so
+  // that nothing waits for them early.
+  struct Step {
+    pca_f4 d[MT], m[MT], v[4];  // v[s][c]: pixel s, component c
+  };
+  auto load = [&](Step& o, int p) {
+#pragma unroll
+    for (int a = 0; a < MT; ++a) {
+      o.d[a] = *reinterpret_cast<const pca_f4*>(drow[a] + p);
+      o.m[a] = *reinterpret_cast<const pca_f4*>(mrow[a] + p);
+    }
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const float* vr = V + (int64_t)(p + s) * k;
+      if constexpr (C4) {
+        o.v[s] = *reinterpret_cast<const pca_f4*>(vr + vo[0]);
+      } else {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) o.v[s][c] = vr[vo[c]];
+      }
+    }
+  };
+  auto multiply = [&](const Step& o) {
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+#pragma unroll
+      for (int a = 0; a < MT; ++a)
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+          acc[a][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(o.d[a][s] - o.m[a][s], o.v[s][c], acc[a][c], 0, 0, 0);
+  };
+  // whole steps of 16 pixels: step i of the wave starts at pixel 16 (w + PCA_W i)
+  const int steps = P / 16;
+  const int mine = (steps - w + PCA_W - 1) / PCA_W;
+  if (mine > 0) {
+    Step o[PCA_D];
+    auto at = [&](int i) { return 16 * (w + PCA_W * min(i, mine - 1)); };
+#pragma unroll
+    for (int d = 0; d + 1 < PCA_D; ++d) load(o[d], at(d));
+    for (int i0 = 0; i0 < mine; i0 += PCA_D) {
+#pragma unroll
+      for (int d = 0; d < PCA_D; ++d) {
+        load(o[(d + PCA_D - 1) % PCA_D], at(i0 + d + PCA_D - 1));
+        if (i0 + d < mine) multiply(o[d]);
+      }
+    }
+  }
+  if (P % 16 && w == steps % PCA_W) {  // the rest, by the wave whose turn it is: pixels past P are zeros
+    Step o;
+    const int p = 16 * steps;
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const bool in = p + lk + s < P;
+#pragma unroll
+      for (int a = 0; a < MT; ++a) {
+        o.d[a][s] = in ? drow[a][p + s] : 0.f;
+        o.m[a][s] = in ? mrow[a][p + s] : 0.f;
       }
 #pragma unroll
-      for (int u = 0; u < 4; ++u)
-#pragma unroll
-        for (int w = 0; w < 4; ++w) acc[u][w] = fmaf(a[u], b[w], acc[u][w]);
+      for (int c = 0; c < 4; ++c) o.v[s][c] = in ? V[(int64_t)(p + s) * k + vo[c]] : 0.f;
     }
-    __syncthreads();
+    multiply(o);
   }
+  // partial tiles: lane l ends with row 4 (l / 16) + r, component 4 (l % 16) + c.
+  // The upper half of the waves hands its tiles to the lower half, which adds
+  // them to its own; then every output adds the PCA_W / 2 sums in order.
+  auto put = [&](int slot) {
 #pragma unroll
-  for (int u = 0; u < 4; ++u)
+    for (int a = 0; a < MT; ++a)
 #pragma unroll
-    for (int w = 0; w < 4; ++w) {
-      const int row = r0 + ty * 4 + u, col = c0 + tx * 4 + w;
-      if (row < n && col < k) coef[(int64_t)row * k + col] = acc[u][w];
-    }
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) s_part[slot][16 * a + 4 * (l >> 4) + r][4 * (l & 15) + c] = acc[a][c][r];
+  };
+  if (w >= PCA_W / 2) put(w - PCA_W / 2);
+  __syncthreads();
+  if (w < PCA_W / 2) {
+#pragma unroll
+    for (int a = 0; a < MT; ++a)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) acc[a][c][r] += s_part[w][16 * a + 4 * (l >> 4) + r][4 * (l & 15) + c];
+    put(w);  // each lane rewrites the slots it has just read
+  }
+  __syncthreads();
+  for (int t = threadIdx.x; t < 16 * MT * PCA_N; t += 64 * PCA_W) {
+    const int i = t / PCA_N, j = t - i * PCA_N;
+    float v = 0.f;
+#pragma unroll
+    for (int q = 0; q < PCA_W / 2; ++q) v += s_part[q][i][j];
+    const int64_t row = r0 + i;
+    if (row >= n || c0 + j >= k) continue;
+    const int mi = mean_idx ? mean_idx[row] : 0;
+    coef[row * k + c0 + j] = (mi < 0 || mi >= n_mean) ? __builtin_nanf("") : v;
+  }
 }
 
 // ---- launchers -------------------------------------------------------------
@@ -478,9 +578,18 @@ hipError_t sg_features(hipStream_t st, int64_t n, const double* raw, float* x) {
 
 hipError_t sg_pca_project(hipStream_t st, int n, int P, int k, const float* D, int64_t ldd, const float* mean,
                           const int* mean_idx, int n_mean, const float* V, float* coef) {
-  dim3 grid((n + 63) / 64, (k + 63) / 64);
-  hipLaunchKernelGGL(k_pca_project, grid, dim3(256), 0, st, n, P, k, D, ldd, mean, mean_idx,
-                     mean_idx ? n_mean : 1, V, coef);
+  const int nb = (k + PCA_N - 1) / PCA_N;
+  // 32-row tiles read V half as often, once they still give every CU two blocks
+  // (8192 x 128: 482 us against 676; 2048 x 128, 128 blocks of them: 297 against 209)
+  const bool wide = (int64_t)((n + 31) / 32) * nb >= 512;
+  const dim3 grid((unsigned)(wide ? (n + 31) / 32 : (n + 15) / 16), nb), block(64 * PCA_W);
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, grid, block, 0, st, n, P, k, D, ldd, mean, mean_idx, mean_idx ? n_mean : 1, V, coef);
+  };
+  if (k % 4 == 0)
+    wide ? go(k_pca_project<2, true>) : go(k_pca_project<1, true>);
+  else
+    wide ? go(k_pca_project<2, false>) : go(k_pca_project<1, false>);
   return hipGetLastError();
 }
 

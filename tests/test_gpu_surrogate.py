@@ -234,6 +234,23 @@ def test_pca_projection_with_per_row_centres():
     np.testing.assert_array_equal(np.delete(c2, 5, axis=0), np.delete(coef.cpu().numpy(), 5, axis=0))
 
 
+# edges of the projection's tiles: 16 and 32 rows, 16 pixels and 16 waves of
+# them, 4 and 64 components
+@pytest.mark.parametrize("n,P,k", [(1, 1, 1), (16, 16, 4), (17, 257, 63), (15, 255, 65), (33, 4097, 68), (16385, 47, 66)])
+def test_pca_projection_at_tile_edges(n, P, k):
+    rng = np.random.default_rng(n + P + k)
+    D = rng.normal(1.0, 0.1, (n, P + 3)).astype(np.float32)
+    mean = rng.normal(1.0, 0.1, P).astype(np.float32)
+    V = rng.normal(0.0, 1.0, (P, k)).astype(np.float32)
+    coef = torch.full((n + 1, k), 7.0, dtype=torch.float32, device="cuda")
+    L.soap_pca_project(_dev(D), _dev(mean), _dev(V), coef[:n], n_pix=P)
+    got = coef.cpu().numpy()
+    want = OSG.pca_project(D[:, :P].astype(np.float64), mean.astype(np.float64), V.astype(np.float64))
+    tol = 4.0 * P * 2.0**-24 * np.abs(D[:, :P] - mean).max() * np.abs(V).max()
+    assert np.abs(got[:n] - want).max() <= tol
+    assert np.all(got[n] == 7.0)  # nothing past the last row
+
+
 @pytest.mark.parametrize("n,P,k", [(100, 1000, 37), (64, 64, 64), (1, 33, 1), (130, 20000, 64)])
 def test_pca_projection_matches_oracle(n, P, k):
     _say("pca", n, P, k)
