@@ -366,16 +366,17 @@ soap_status soap_surrogate_rv(soap_ctx* ctx, const float* coef, const float* mem
                               double* rv_kms, double* err_kms, int32_t* fallback);
 
 /* Shape of the shift-and-sum kernel and its tuner.  A block of four waves
- * covers a tile of pixels for one chunk of `phases_per_chunk` phases: 8
- * (tiles of 2048 pixels) or 16 (1024 pixels) in FP32, 4 (1024 pixels) or 8
- * (512 pixels) in FP64; the first of each pair is the default.  More phases
- * per chunk read each source window once for more phases (fewer loads per
- * tap), fewer keep more pixels per lane (fewer empty phase slots where
- * regions are visible for only part of a chunk).  Phases per chunk is the
- * layout of the tap tables that the next soap_active_spectra call builds.
+ * covers a tile of pixels (1024 in FP32, 512 in FP64) for one chunk of
+ * `phases_per_chunk` phases: 8 or 16 in FP32, 4 or 8 in FP64; by default the
+ * larger of the two for calls that still fill the chip with it, and the
+ * smaller for other calls, per-phase region lists and batches.  More phases
+ * per chunk read each source window once for more phases (fewer reads per
+ * tap), fewer make more blocks (and fewer empty phase slots where regions
+ * are visible for only part of a chunk).  Phases per chunk is the layout of
+ * the tap tables that the next soap_active_spectra call builds.
  * Every wave keeps `depth` (2 or 3) windows of source samples in flight
- * (the loads of the next depth - 1 windows are issued before the current one
- * is consumed).  `order` picks how each XCD walks its (tile, chunk) items:
+ * (the copies of the next depth - 1 windows are started before the current
+ * one is consumed).  `order` picks how each XCD walks its (tile, chunk) items:
  * 0 = chunks with the most windows first, 1 = tile by tile (all chunks of a
  * tile together).  Every shape gives the same result bit for bit (each
  * pixel adds the non-zero taps of its phase in the same window order, and a
@@ -482,9 +483,9 @@ typedef struct {
   int64_t last_phases;       /* last apply: number of phases                */
   /* last apply's arithmetic per output pixel, summed over its phases and
    * windows: non-zero taps (one FMA each per pixel), window offsets with any
-   * non-zero tap (one FMA each to form the difference), and the FMAs the
-   * kernel issues (4 per (offset, four-phase group) with a non-zero tap,
-   * plus 8 difference FMAs per window)                                     */
+   * non-zero tap (one FMA each to form the difference), and the FMAs of the
+   * phase groups (four phases in FP32, two in FP64) that have a non-zero tap
+   * at an offset, plus one difference per such offset                      */
   int64_t taps_nonzero;
   int64_t taps_offsets;
   int64_t fma_issued;

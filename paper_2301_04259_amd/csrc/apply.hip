@@ -17,24 +17,42 @@
 //
 // Work split: one block of APPLY_WAVES waves per (tile of APPLY_WAVES x 64
 // x R pixels, chunk of PC phases); each wave owns 64 x R consecutive pixels
-// of the tile (R per lane) and walks every window of the chunk's list over
-// them, with R x PC accumulators per lane in registers.  The block copies
-// the chunk's window records (header and dense taps of APPLY_JW offsets,
-// built by the compaction kernel) into LDS, APPLY_LDS_WIN records per pass
-// with a barrier between passes, so the taps reach every lane as broadcast
-// LDS reads.  For each window a lane loads the R + APPLY_JW - 1 source
-// samples its pixels need (and as many quiet samples for paired tables) and
-// its R contrast values (rows are padded with their end samples, so no load
-// needs a bounds check and the end-value hold of the interpolation is built
-// in); then, offset by offset, each pair of phases with a tap there adds
-// k * D with fused multiply-adds, and a wave-uniform mask test skips the
-// other pairs.  The loads of the next DEP - 1 windows are in flight while a
-// window is consumed.  The block-to-work mapping keeps the chunks of one
-// tile on one XCD so their shared input windows hit the same L2, and either
-// starts the chunks with the most windows first or walks the tiles in
-// order.  The final store adds Q in double.  Every pixel's sum runs over the
-// windows in list order, so results repeat bit for bit whatever the
-// pipeline depth or item order.
+// of the tile (R per lane: 16 bytes of a row) and walks every window of the
+// chunk's list over them by itself, with R x PC accumulators per lane in
+// registers.  A window's operands (the active row over the wave's pixels and
+// APPLY_JW - 1 samples before them, the quiet row likewise for paired tables,
+// the contrast at the pixels, and the window's taps) are copied straight from
+// memory into one of the wave's DEP LDS slots, the copies of the next DEP - 1
+// windows in flight while a window is consumed; the rows are padded with
+// their end samples, so no copy needs a bounds check and the end-value hold
+// of the interpolation is built in.  Each lane then reads its R + APPLY_JW - 1
+// samples per row as 16-byte LDS reads and, offset by offset, forms the
+// differences D of its R pixels once and adds k * D for every group of phases
+// that has a tap there (a wave-uniform mask test skips the others): in FP32
+// four phases per v_mfma_f32_4x4x1_16b, whose lane l takes its own pixel's D
+// and the taps of phases 4 g + i from the lanes l % 4 = i of its block of
+// four, and which rounds each k * D + acc as one FMA does; in FP64 pairs of
+// phases with FMAs.
+// The block-to-work mapping keeps the chunks of one tile on one XCD so their
+// shared input windows hit the same L2, and either starts the chunks with the
+// most windows first or walks the tiles in order.  The final store adds Q in
+// double.  Every pixel's sum runs over the offsets in list order, so results
+// repeat bit for bit whatever the pipeline depth, item order or chunk size.
+//
+// What bounds it: for large calls memory and issue together (206k px x 100
+// phases, paired with contrast: 82 MB written and 122 MB read in 38.7 us, 5.3
+// TB/s; vector and matrix units busy 45% of the time), for small ones the
+// chain of a wave's windows (about 0.45 us each).  Before, with operands
+// loaded into registers window by window (4 offsets, 8 loads), taps read from
+// LDS as broadcasts and one FMA per phase and pixel: 49 us; 500 spots x 8
+// phases of 20000 px 162 us, now 107; FP64 100003 px x 60 phases 57.7, now
+// 40.2; 60000 px x 100 phases 30 us, now 20.6.  On the way: matrix
+// instructions alone 43.9 (16 phases per chunk); operands through LDS in
+// windows of 8 offsets 46.2, with the rows' addresses in the record headers,
+// reads kept whole and the loop ended by the mask 44.6, with streaming stores
+// 39.8.  Headers kept in registers and read back by v_readlane: 42.2 (and
+// small calls as now).  Groups of tiles per XCD, heaviest chunk first within
+// each: no gain at any group size.
 #include <algorithm>
 #include <vector>
 
@@ -44,87 +62,10 @@ namespace soap {
 
 namespace {
 
-// The R + APPLY_JW - 1 consecutive elements of a window from an
-// element-aligned address: 16-byte loads and one shorter load for the rest,
-// whose types promise only element alignment.  Every loaded element is used:
-// a loaded register that the program never reads may be reused by the
-// compiler while its load is still in flight, which makes the wave wait for
-// that load.
-typedef float f4e __attribute__((ext_vector_type(4), aligned(4)));
-typedef float f3e __attribute__((ext_vector_type(3), aligned(4)));
-typedef double d2e __attribute__((ext_vector_type(2), aligned(8)));
-
-template <typename T, int PC>
-constexpr int win_n() {
-  return ApplyShape<T, PC>::R + APPLY_JW - 1;
-}
-
-template <typename T, int PC>
-__device__ __forceinline__ void load_win(T (&w)[(win_n<T, PC>())], const T* p) {
-  constexpr int N = win_n<T, PC>();
-  if constexpr (sizeof(T) == 4) {
-    static_assert(N % 4 == 3, "16-byte loads and one 12-byte load");
-#pragma unroll
-    for (int k = 0; k + 4 <= N; k += 4) {
-      const f4e f = *reinterpret_cast<const f4e*>(p + k);
-      w[k] = f.x;
-      w[k + 1] = f.y;
-      w[k + 2] = f.z;
-      w[k + 3] = f.w;
-    }
-    const f3e g = *reinterpret_cast<const f3e*>(p + N - 3);
-    w[N - 3] = g.x;
-    w[N - 2] = g.y;
-    w[N - 1] = g.z;
-  } else {
-    static_assert(N % 2 == 1, "16-byte loads and one 8-byte load");
-#pragma unroll
-    for (int k = 0; k + 2 <= N; k += 2) {
-      const d2e f = *reinterpret_cast<const d2e*>(p + k);
-      w[k] = f.x;
-      w[k + 1] = f.y;
-    }
-    w[N - 1] = p[N - 1];
-  }
-}
-
-// R consecutive elements from 16-byte-aligned memory
-template <typename T, int PC>
-__device__ __forceinline__ void load_px(T (&c)[(ApplyShape<T, PC>::R)], const T* p) {
-  constexpr int R = ApplyShape<T, PC>::R;
-  if constexpr (sizeof(T) == 4) {
-#pragma unroll
-    for (int k = 0; k < R; k += 4) {
-      const float4 f = *reinterpret_cast<const float4*>(p + k);
-      c[k] = f.x;
-      c[k + 1] = f.y;
-      c[k + 2] = f.z;
-      c[k + 3] = f.w;
-    }
-  } else {
-#pragma unroll
-    for (int k = 0; k < R; k += 2) {
-      const double2 f = *reinterpret_cast<const double2*>(p + k);
-      c[k] = f.x;
-      c[k + 1] = f.y;
-    }
-  }
-}
-
-// operands of one window: D[q][r] = Ca[r] * A[m_r - j] - B[m_r - j],
-// j = jlo + q, with window sample s = r - q + APPLY_JW - 1
-template <typename T, int PC>
-struct Operands {
-  T a[(win_n<T, PC>())], b[(win_n<T, PC>())];  // b is used by paired tables only (D = C A - B)
-  T c[(ApplyShape<T, PC>::R)];
-};
-
 template <typename T>
 struct ApplyArgs {
-  int64_t P, Pstride;
-  int64_t cs_stride;  // stride of the spot contrast rows per bin (0: one row)
-  int B, n_ph, n_chunks, n_tiles, effect, paired, vg_cap, vec_ok, order;
-  const T *Sq, *Ss, *Sf, *Cs, *Cf, *ones;
+  int64_t P;
+  int n_ph, n_chunks, n_tiles, vg_cap, vec_ok, order;
   const double* Q;
   const unsigned char* wins;
   const int* nvg;
@@ -133,75 +74,209 @@ struct ApplyArgs {
 
 __device__ __forceinline__ int uni(int x) { return __builtin_amdgcn_readfirstlane(x); }
 
-// Rows a window reads: active (or quiet) source, quiet source, contrast.
-// Every fetch issues the same loads (a, b for paired tables, c), so that the
-// compiler can count outstanding loads exactly and the next windows' loads
-// stay in flight while the current window is consumed.  Without a contrast
-// the c operand comes from a resident row of ones; for the flux effect the
-// active operand is the quiet row itself, loaded a second time.  EFF is the
-// effect when known at compile time (-1: read from the arguments).  Row
-// offsets fit 32 bits (mu bins x padded row length), so the selection is a
-// few scalar multiplies and selects.
-template <typename T, int EFF>
-__device__ __forceinline__ void window_rows(const ApplyArgs<T>& A, int4 hr, const T*& src, const T*& sq,
-                                            const T*& con, int& jlo) {
-  const int t = uni(hr.x), b = uni(hr.y);
-  jlo = uni(hr.z);
-  const int eff = EFF >= 0 ? EFF : A.effect;
-  const int off = b * (int)A.Pstride;  // row b of a [B][Pstride] table
-  sq = A.Sq + off;
-  const T* st = (t == SOAP_SPOT ? A.Ss : A.Sf) + off;
-  const T* ct = A.ones;
-  if (A.Cs) ct = t == SOAP_SPOT ? A.Cs + (A.cs_stride ? off : 0) : A.Cf + off;
-  const bool quiet = t == 0;
-  src = (quiet || eff == SOAP_EFFECT_FLUX) ? sq : st;
-  con = (quiet || eff == SOAP_EFFECT_BCONV) ? A.ones : ct;
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+// One LDS slot of a wave: 1 KiB of the wave's pixels per row (the lanes' 16
+// bytes in lane order), then the ends of the sample rows (the APPLY_JW
+// samples past the 1 KiB: rows start APPLY_JW - 1 samples before the first
+// pixel) and the taps.
+template <typename T, int PC, int MODE>
+struct Slot {
+  static constexpr int R = ApplyShape<T, PC>::R;
+  static constexpr int ROWS = MODE == MODE_SPLIT ? 1 : 2;              // sample rows
+  static constexpr int CON = ROWS * 1024;                               // contrast at the pixels
+  static constexpr int TAIL = CON + (MODE == MODE_CONTRAST ? 1024 : 0);
+  static constexpr int TB = APPLY_JW * (int)sizeof(T);                  // bytes of a row's end
+  static constexpr int TAPS = TAIL + ROWS * TB;
+  static constexpr int TAP_BYTES = APPLY_JW * PC * (int)sizeof(T);
+  static constexpr int BYTES = TAPS + TAP_BYTES;
+  static constexpr int LANES_T = ROWS * TB / 16;                        // lanes that copy the ends
+  static constexpr int LANES = LANES_T + TAP_BYTES / 16;                // and the taps
+  static constexpr int N16 = (R + APPLY_JW - 1 + R - 1) / R;            // 16-byte reads per row
+  static constexpr int COPIES = ROWS + (MODE == MODE_CONTRAST ? 1 : 0) + 1;
+  static_assert(LANES <= 64 && BYTES % 16 == 0, "one copy for the ends and the taps");
+};
+
+// the compiler keeps nothing in m0 (a reserved register) across statements
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
+// Copies 16 bytes per lane from memory (any 4-byte alignment) to LDS at lds +
+// AT + 16 x lane, without going through registers; counted by vmcnt like a
+// load, which the compiler does not see here: every wait is in the loop below.
+template <int AT>
+__device__ __forceinline__ void copy16(unsigned lds, unsigned long long base, unsigned lane_off) {
+  asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+               :
+               : "s"(lds), "v"(lane_off), "s"(base), "n"(AT)
+               : "memory", "m0", "scc");
+}
+template <int AT>
+__device__ __forceinline__ void copy16_lanes(unsigned lds, unsigned long long p) {
+  asm volatile("s_add_u32 m0, %0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
+               :
+               : "s"(lds), "v"(p), "n"(AT)
+               : "memory", "m0", "scc");
+}
+#pragma clang diagnostic pop
+template <int N>
+__device__ __forceinline__ void wait_copies() {
+  asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory");
 }
 
-// mt: first pixel of the tile (uniform); lo: the lane's first pixel within
-// it.  The uniform part of every address is formed in SGPRs, so each load
-// takes a scalar base and a 32-bit per-lane offset.
-template <typename T, int PC, int EFF, bool PAIRED>
-__device__ __forceinline__ void fetch(Operands<T, PC>& o, const ApplyArgs<T>& A, int4 hr, int64_t mt, unsigned lo) {
-  const T *src, *sq, *con;
-  int jlo;
-  window_rows<T, EFF>(A, hr, src, sq, con, jlo);
-  // window start m - jlo - (JW - 1)
-  const int64_t at = mt - jlo - (APPLY_JW - 1);
-  load_win<T, PC>(o.a, (src + at) + lo);
-  if (PAIRED) load_win<T, PC>(o.b, (sq + at) + lo);
-  load_px<T, PC>(o.c, (con + mt) + lo);
+// A window record's header, through a scalar load.  Scalar loads share their
+// counter with LDS reads, and a wait for one waits for all: the header of the
+// next copies is loaded right after a window's LDS reads have arrived and is
+// used after its arithmetic, so neither is waited for in vain.
+struct Head {
+  unsigned long long act, quiet, con;
+  unsigned gmask;
+};
+__device__ __forceinline__ Head load_head(unsigned long long rec) {
+  typedef unsigned u32x8 __attribute__((ext_vector_type(8)));
+  asm volatile("" : "+s"(rec));  // not before this point
+  const u32x8 x = *(const __attribute__((address_space(4))) u32x8*)rec;
+  auto at = [&](int i) { return (unsigned long long)x[i] | ((unsigned long long)x[i + 1] << 32); };
+  return Head{at(0), at(2), at(4), x[6]};
 }
 
-// One window: for every offset q with a tap in the chunk, read the taps of
-// all phases at that offset from LDS (every lane reads the same address),
-// form the difference row, and let each pair of phases with a tap there add
-// k * D with fused multiply-adds.
-template <typename T, int PC, bool PAIRED>
-__device__ __forceinline__ void consume(T (&acc)[PC][(ApplyShape<T, PC>::R)], const Operands<T, PC>& o, unsigned gm,
-                                        const T* tw) {
-  constexpr int R = ApplyShape<T, PC>::R, JW = APPLY_JW, NP = PC / 2;
-  constexpr unsigned PMASK = (1u << NP) - 1u;
+// Starts the copies of one window into the slot at LDS address lds.  px_bytes:
+// the wave's first pixel in bytes.  Uniform bases in SGPRs, 32-bit lane
+// offsets; end_off: the lane's offset in the last copy, from the active row,
+// the quiet row or the record (as its lane number says).
+template <typename T, int PC, int MODE>
+__device__ __forceinline__ void fetch(const Head& h, unsigned long long rec, unsigned long long px_bytes,
+                                      unsigned lds, int lane, long long end_off) {
+  using S = Slot<T, PC, MODE>;
+  const unsigned lo = 16u * lane;
+  const unsigned long long act = h.act + px_bytes, quiet = h.quiet + px_bytes;
+  copy16<0>(lds, act, lo);
+  if constexpr (MODE != MODE_SPLIT) copy16<1024>(lds, quiet, lo);
+  if constexpr (MODE == MODE_CONTRAST) copy16<S::CON>(lds, h.con + px_bytes, lo);
+  // the ends of the rows and the taps, one copy
+  constexpr int LA = S::TB / 16;
+  unsigned long long p = rec;
+  if constexpr (S::ROWS == 2) p = lane < 2 * LA ? quiet : p;
+  p = lane < LA ? act : p;
+  if (lane < S::LANES) copy16_lanes<S::TAIL>(lds, p + end_off);
+}
+
+// Accumulators of one lane: PC phases x R pixels.  FP32 keeps four phases of a
+// pixel together, as the matrix instruction adds them.
+template <typename T, int PC>
+struct Acc {
+  static constexpr int R = ApplyShape<T, PC>::R;
+  T v[PC][R];
+  __device__ __forceinline__ void clear() {
 #pragma unroll
-  for (int q = 0; q < JW; ++q) {
-    const unsigned bits = (gm >> (q * NP)) & PMASK;
-    if (bits == 0u) continue;
-    T k[PC];
+    for (int p = 0; p < PC; ++p)
 #pragma unroll
-    for (int p = 0; p < PC; ++p) k[p] = tw[q * PC + p];
+      for (int r = 0; r < R; ++r) v[p][r] = T(0);
+  }
+  __device__ __forceinline__ T get(int p, int r) const { return v[p][r]; }
+};
+template <int PC>
+struct Acc<float, PC> {
+  static constexpr int R = ApplyShape<float, PC>::R;
+  f32x4 v[PC / 4][R];
+  __device__ __forceinline__ void clear() {
+#pragma unroll
+    for (int g = 0; g < PC / 4; ++g)
+#pragma unroll
+      for (int r = 0; r < R; ++r) v[g][r] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  __device__ __forceinline__ float get(int p, int r) const { return v[p / 4][r][p % 4]; }
+};
+
+// 16 bytes of LDS
+template <typename T>
+__device__ __forceinline__ void read16(T* x, const unsigned char* p) {
+  if constexpr (sizeof(T) == 4) {
+    const float4 f = *reinterpret_cast<const float4*>(p);
+    x[0] = f.x;
+    x[1] = f.y;
+    x[2] = f.z;
+    x[3] = f.w;
+  } else {
+    const double2 f = *reinterpret_cast<const double2*>(p);
+    x[0] = f.x;
+    x[1] = f.y;
+  }
+}
+// the values are wanted here as they are: the reads before it stay whole and
+// together instead of following their uses into the offsets' branches
+template <typename T, int N>
+__device__ __forceinline__ void settle(T (&x)[N]) {
+#pragma unroll
+  for (int i = 0; i < N; ++i) asm volatile("" : "+v"(x[i]));
+}
+
+// Offsets Q0 .. Q0 + NQ - 1 of one window from its slot.  row_at[i]: place of
+// the lane's i-th 16 bytes of the active row (past the last lane they are in
+// the row's end), row_at[N16 + i] of the quiet row; sample s of the lane is
+// m_0 - jlo - (JW - 1) + s, so pixel r at offset jlo + q uses s = r - q + JW -
+// 1.  The offsets of a window are mostly its first few, so the loop ends where
+// the mask does; within it every group of a pair of groups that has a tap is
+// added (a zero tap adds exactly zero).
+// then(): called once the reads have arrived.
+template <typename T, int PC, int MODE, int Q0, int NQ, typename F>
+__device__ __forceinline__ void consume(Acc<T, PC>& acc, unsigned gm, const unsigned char* slot,
+                                        const unsigned (&row_at)[2 * Slot<T, PC, MODE>::N16], int lane, F then) {
+  using S = Slot<T, PC, MODE>;
+  constexpr int R = S::R, JW = APPLY_JW, NG = ApplyShape<T, PC>::NG, N16 = S::N16;
+  constexpr int S0 = (JW - Q0 - NQ) / R * R, S1 = R - 1 - Q0 + JW;  // samples S0 .. S1 - 1 are used
+  constexpr int I0 = S0 / R, I1 = (S1 + R - 1) / R;
+  static_assert(I1 <= N16, "samples of a row");
+  T a[(I1 - I0) * R], b[(I1 - I0) * R], c[R];
+#pragma unroll
+  for (int i = I0; i < I1; ++i) {
+    read16(&a[(i - I0) * R], slot + row_at[i]);
+    if constexpr (MODE != MODE_SPLIT) read16(&b[(i - I0) * R], slot + row_at[N16 + i]);
+  }
+  if constexpr (MODE == MODE_CONTRAST) read16(c, slot + S::CON + 16 * lane);
+  // FP32: the lane's taps of the offsets; FP64: every phase's taps
+  constexpr int NK = sizeof(T) == 4 ? NQ * NG : NQ * PC;
+  T k[NK];
+  const unsigned char* kp = slot + S::TAPS + (sizeof(T) == 4 ? 4 * NG * (JW * (lane & 3) + Q0) : 8 * PC * Q0);
+  if constexpr (sizeof(T) == 4) {
+#pragma unroll
+    for (int i = 0; i < NK; i += 4) read16(&k[i], kp + 4 * i);
+    settle(k);
+  }
+  settle(a);
+  if constexpr (MODE != MODE_SPLIT) settle(b);
+  if constexpr (MODE == MODE_CONTRAST) settle(c);
+  then();
+#pragma unroll
+  for (int q = Q0; q < Q0 + NQ; ++q) {
+    if (q > Q0 && gm < (1u << (q * NG))) break;  // uniform
     T D[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-      const int s = r - q + JW - 1;
-      D[r] = PAIRED ? fma(o.c[r], o.a[s], -o.b[s]) : o.c[r] * o.a[s];
+      const int s = r - q + JW - 1 - S0;
+      D[r] = MODE == MODE_CONTRAST ? fma(c[r], a[s], -b[s]) : (MODE == MODE_PAIRED ? a[s] - b[s] : a[s]);
     }
+    const unsigned bits = gm >> (q * NG);
+    if constexpr (sizeof(T) == 4) {
 #pragma unroll
-    for (int pi = 0; pi < NP; ++pi) {
-      if (__builtin_expect((bits >> pi) & 1u, 1)) {
+      for (int g = 0; g < NG; g += 2) {
+        if (NG > 2 && !((bits >> g) & 3u)) continue;
 #pragma unroll
-        for (int p = 2 * pi; p < 2 * pi + 2; ++p)
+        for (int u = g; u < g + 2; ++u)
 #pragma unroll
-          for (int r = 0; r < R; ++r) acc[p][r] = fma(k[p], D[r], acc[p][r]);
+          for (int r = 0; r < R; ++r)
+            acc.v[u][r] = __builtin_amdgcn_mfma_f32_4x4x1f32(k[(q - Q0) * NG + u], D[r], acc.v[u][r], 0, 0, 0);
+      }
+    } else {
+#pragma unroll
+      for (int p = 0; p < PC; p += 2) read16(&k[(q - Q0) * PC + p], kp + 8 * ((q - Q0) * PC + p));
+#pragma unroll
+      for (int g = 0; g < NG; ++g) {
+        if (__builtin_expect((bits >> g) & 1u, 1)) {
+#pragma unroll
+          for (int p = 2 * g; p < 2 * g + 2; ++p)
+#pragma unroll
+            for (int r = 0; r < R; ++r) acc.v[p][r] = fma(k[(q - Q0) * PC + p], D[r], acc.v[p][r]);
+        }
       }
     }
   }
@@ -212,8 +287,7 @@ __device__ __forceinline__ void consume(T (&acc)[PC][(ApplyShape<T, PC>::R)], co
 // final combine of one item: Q (double) plus the accumulated differences,
 // written with 16-byte stores where the row allows
 template <typename T, int PC>
-__device__ __forceinline__ void store_item(const ApplyArgs<T>& A, const T (&acc)[PC][(ApplyShape<T, PC>::R)], int chunk,
-                                           int64_t m0) {
+__device__ __forceinline__ void store_item(const ApplyArgs<T>& A, const Acc<T, PC>& acc, int chunk, int64_t m0) {
   constexpr int R = ApplyShape<T, PC>::R;
   double Qr[R];
 #pragma unroll
@@ -226,16 +300,15 @@ __device__ __forceinline__ void store_item(const ApplyArgs<T>& A, const T (&acc)
     T* row = A.out + (int64_t)(p0 + p) * A.P;
     T vals[R];
 #pragma unroll
-    for (int r = 0; r < R; ++r) vals[r] = (T)(Qr[r] + (double)acc[p][r]);
+    for (int r = 0; r < R; ++r) vals[r] = (T)(Qr[r] + (double)acc.get(p, r));
     if (full) {
-      if constexpr (sizeof(T) == 4) {
+      typedef T T16 __attribute__((ext_vector_type(16 / sizeof(T))));
+      T16 x;
 #pragma unroll
-        for (int r = 0; r < R; r += 4)
-          *reinterpret_cast<float4*>(row + m0 + r) = make_float4(vals[r], vals[r + 1], vals[r + 2], vals[r + 3]);
-      } else {
-#pragma unroll
-        for (int r = 0; r < R; r += 2) *reinterpret_cast<double2*>(row + m0 + r) = make_double2(vals[r], vals[r + 1]);
-      }
+      for (int r = 0; r < R; ++r) x[r] = vals[r];
+      // past the caches' usual order: the output is not read again here, and
+      // the input rows stay in L2 (headline 44.8 to 39.8 us at 16 phases)
+      __builtin_nontemporal_store(x, reinterpret_cast<T16*>(row + m0));
     } else {
 #pragma unroll
       for (int r = 0; r < R; ++r)
@@ -245,57 +318,75 @@ __device__ __forceinline__ void store_item(const ApplyArgs<T>& A, const T (&acc)
 }
 
 // One (tile, chunk) item: each wave walks all of the chunk's windows over its
-// own 64 x APPLY_R pixels of the tile (DEP windows in flight: the loads of
-// window v + DEP - 1 are issued before window v is consumed; fetches are
-// unconditional, past the end they repeat the last window and are not
-// consumed, so the compiler can count outstanding loads exactly; each header
-// is read one step ahead of its fetch).  The block stages the records
-// APPLY_LDS_WIN at a time.  Then Q is added and the spectra stored.
-template <typename T, int PC, bool PAIRED, int EFF, int DEP>
+// own 64 x R pixels of the tile.  Step v starts the copies of window v + DEP -
+// 1 (its slot was consumed in step v - 1: those LDS reads are complete before
+// the copies start), waits until only the copies of the later windows are
+// outstanding, and consumes window v.  Every copy has arrived before the store.
+template <typename T, int PC, int MODE, int DEP>
 __device__ __forceinline__ void apply_item(const ApplyArgs<T>& A, int tile, int chunk, unsigned char* lds) {
-  constexpr int R = ApplyShape<T, PC>::R, WB = ApplyShape<T, PC>::WB;
-  const int64_t mt = (int64_t)tile * ApplyShape<T, PC>::TILE;
-  const unsigned lo = threadIdx.x * R;
+  using S = Slot<T, PC, MODE>;
+  constexpr int R = S::R, WB = ApplyShape<T, PC>::WB, N16 = S::N16, NG = ApplyShape<T, PC>::NG;
+  const int lane = threadIdx.x & 63, wave = uni(threadIdx.x >> 6);
+  const int64_t px = (int64_t)tile * ApplyShape<T, PC>::TILE + wave * 64 * R;
 
-  T acc[PC][R];
+  Acc<T, PC> acc;
+  acc.clear();
+  unsigned row_at[2 * N16];
 #pragma unroll
-  for (int p = 0; p < PC; ++p)
-#pragma unroll
-    for (int r = 0; r < R; ++r) acc[p][r] = T(0);
+  for (int i = 0; i < N16; ++i) {
+    const int u = lane + i;
+    row_at[i] = u < 64 ? 16 * u : S::TAIL + 16 * (u - 64);
+    row_at[N16 + i] = u < 64 ? 1024 + 16 * u : S::TAIL + S::TB + 16 * (u - 64);
+  }
+  // the lane's part of the last copy: ends of the rows, then the taps
+  constexpr int LA = S::TB / 16;
+  const long long end_off = lane < LA ? 1024 + 16 * lane
+                            : lane < S::LANES_T ? 1024 + 16 * (lane - LA)
+                                                : WIN_HEAD + 16 * (lane - S::LANES_T);
 
-  const int nv = A.nvg[chunk];
-  const unsigned char* gw = A.wins + (int64_t)chunk * A.vg_cap * WB;
-  for (int vb = 0; vb < nv; vb += APPLY_LDS_WIN) {
-    const int nb = min(APPLY_LDS_WIN, nv - vb);
-    if (vb) __syncthreads();  // every wave is done with the previous pass
-    {
-      const int4* src = reinterpret_cast<const int4*>(gw + (int64_t)vb * WB);
-      int4* dst = reinterpret_cast<int4*>(lds);
-      const int n16 = nb * (WB / 16);
-      for (int u = threadIdx.x; u < n16; u += APPLY_WAVES * 64) dst[u] = src[u];
+  const int nv = uni(A.nvg[chunk]);
+  const unsigned long long gw = (unsigned long long)(uintptr_t)(A.wins + (int64_t)chunk * A.vg_cap * WB);
+  unsigned char* ring = lds + wave * (DEP * S::BYTES);
+  const unsigned ring_at = uni((unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)ring);
+  const unsigned long long pxb = (unsigned long long)px * sizeof(T);
+  if (nv > 0) {
+    const unsigned long long last = gw + (unsigned long long)(nv - 1) * WB;
+    unsigned long long rf = gw;  // record of the next copies
+    Head hf = load_head(rf);     // and its header
+    unsigned gm[DEP];            // masks of the windows in flight
+#pragma unroll
+    for (int i = 0; i + 1 < DEP; ++i) {
+      gm[i] = hf.gmask;
+      if (i < nv) fetch<T, PC, MODE>(hf, rf, pxb, ring_at + i * S::BYTES, lane, end_off);
+      rf = rf < last ? rf + WB : last;
+      hf = load_head(rf);
     }
-    __syncthreads();
-    const int last = nb - 1;
-    auto head = [&](int v) { return *reinterpret_cast<const int4*>(lds + min(v, last) * WB); };
-    Operands<T, PC> o[DEP];
-    int4 h[DEP];
-#pragma unroll
-    for (int i = 0; i < DEP; ++i) h[i] = head(i);
-#pragma unroll
-    for (int i = 0; i + 1 < DEP; ++i) fetch<T, PC, EFF, PAIRED>(o[i], A, h[i], mt, lo);
-    for (int v0 = 0; v0 < nb; v0 += DEP) {
+    for (int v0 = 0; v0 < nv; v0 += DEP) {
 #pragma unroll
       for (int d = 0; d < DEP; ++d) {
-        const int nxt = (d + DEP - 1) % DEP;  // slot of window v0 + d + DEP - 1
-        fetch<T, PC, EFF, PAIRED>(o[nxt], A, h[nxt], mt, lo);
-        const int4 hc = h[d];
-        h[d] = head(v0 + d + DEP);
-        if (v0 + d < nb)
-          consume<T, PC, PAIRED>(acc, o[d], (unsigned)uni(hc.w), reinterpret_cast<const T*>(lds + (v0 + d) * WB + 16));
+        constexpr int F = DEP - 1, H = APPLY_JW / 2;
+        const int v = v0 + d;
+        if (v >= nv) break;
+        gm[(d + F) % DEP] = hf.gmask;
+        if (v + F < nv) {
+          fetch<T, PC, MODE>(hf, rf, pxb, ring_at + ((d + F) % DEP) * S::BYTES, lane, end_off);
+          wait_copies<F * S::COPIES>();
+        } else {
+          wait_copies<0>();
+        }
+        const unsigned m = gm[d];
+        const unsigned char* slot = ring + d * S::BYTES;
+        consume<T, PC, MODE, 0, H>(acc, m, slot, row_at, lane, [&] {
+          rf = rf < last ? rf + WB : last;
+          hf = load_head(rf);
+        });
+        if (m >= (1u << (H * NG))) consume<T, PC, MODE, H, APPLY_JW - H>(acc, m, slot, row_at, lane, [] {});
+        // the slot's reads are complete before a later copy may overwrite it
+        asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory");
       }
     }
   }
-  store_item<T, PC>(A, acc, chunk, mt + lo);
+  store_item<T, PC>(A, acc, chunk, px + lane * R);
 }
 
 // Blocks are dealt to the 8 XCDs in turn (block index mod 8).  Each XCD
@@ -338,31 +429,30 @@ __device__ __forceinline__ bool map_item(const ApplyArgs<T>& A, int seq8, int* t
   return true;
 }
 
-// waves per SIMD the register budget is sized for: three with two windows
-// in flight (FP32, or FP64 with its 2-pixel lanes), two where more registers
-// are needed (FP64 with 4-pixel lanes, a third window in flight, the effect
-// read at run time)
-template <typename T, int PC, int EFF, int DEP>
+// waves per SIMD the register budget is sized for
+// (as many as its LDS slots allow, at most four)
+template <typename T, int PC, int MODE, int DEP>
 constexpr int apply_occupancy() {
-  return ((sizeof(T) == 4 || PC == PC_F64_WIDE) && DEP == 2 && EFF >= 0) ? 3 : 2;
+  constexpr int fit = 160 * 1024 / (APPLY_WAVES * DEP * Slot<T, PC, MODE>::BYTES);
+  return fit < 4 ? fit : 4;
 }
 
-template <typename T, int PC, bool PAIRED, int EFF, int DEP>
-__global__ void __launch_bounds__(APPLY_WAVES * 64, (apply_occupancy<T, PC, EFF, DEP>())) k_apply(ApplyArgs<T> A) {
-  __shared__ __align__(16) unsigned char lds[APPLY_LDS_WIN * ApplyShape<T, PC>::WB];
+template <typename T, int PC, int MODE, int DEP>
+__global__ void __launch_bounds__(APPLY_WAVES * 64, (apply_occupancy<T, PC, MODE, DEP>())) k_apply(ApplyArgs<T> A) {
+  __shared__ __align__(16) unsigned char lds[APPLY_WAVES * DEP * Slot<T, PC, MODE>::BYTES];
   int tile, chunk;
   if (!map_item(A, blockIdx.x, &tile, &chunk)) return;
-  apply_item<T, PC, PAIRED, EFF, DEP>(A, tile, chunk, lds);
+  apply_item<T, PC, MODE, DEP>(A, tile, chunk, lds);
 }
 
 // Batched form: one launch over the items of many configurations (each with
 // its own arguments, all with PC phases per chunk).  Configuration i owns the
 // slots item_off[i] .. item_off[i+1] - 1, a multiple of 8 starting at a
 // multiple of 8, mapped as in k_apply.
-template <typename T, int PC, bool PAIRED, int EFF, int DEP>
-__global__ void __launch_bounds__(APPLY_WAVES * 64, (apply_occupancy<T, PC, EFF, DEP>()))
+template <typename T, int PC, int MODE, int DEP>
+__global__ void __launch_bounds__(APPLY_WAVES * 64, (apply_occupancy<T, PC, MODE, DEP>()))
     k_apply_batch(const ApplyArgs<T>* __restrict__ args, const int* __restrict__ item_off, int n_cfg) {
-  __shared__ __align__(16) unsigned char lds[APPLY_LDS_WIN * ApplyShape<T, PC>::WB];
+  __shared__ __align__(16) unsigned char lds[APPLY_WAVES * DEP * Slot<T, PC, MODE>::BYTES];
   const int b = blockIdx.x;
   int lo = 0, hi = n_cfg;  // last cfg with item_off[cfg] <= b
   while (hi - lo > 1) {
@@ -373,52 +463,45 @@ __global__ void __launch_bounds__(APPLY_WAVES * 64, (apply_occupancy<T, PC, EFF,
   const ApplyArgs<T> A = args[lo];
   int tile, chunk;
   if (!map_item(A, b - item_off[lo], &tile, &chunk)) return;
-  apply_item<T, PC, PAIRED, EFF, DEP>(A, tile, chunk, lds);
+  apply_item<T, PC, MODE, DEP>(A, tile, chunk, lds);
+}
+
+// contrast rows are read by the total and flux effects of the modes that have
+// them; their tables are paired
+int apply_table_mode(const soap_ctx* c, const Plan& pl) {
+  if (!pl.paired) return MODE_SPLIT;
+  return (c->cmode != SOAP_CONTRAST_SCALAR && pl.effect != SOAP_EFFECT_BCONV) ? MODE_CONTRAST : MODE_PAIRED;
 }
 
 namespace {
 
-template <typename T, int PC, bool PAIRED, int EFF>
-hipError_t launch_eff(const ApplyArgs<T>& A, int depth, dim3 grid, hipStream_t st) {
-  const dim3 block(APPLY_WAVES * 64);
+template <typename T, int PC, int MODE>
+hipError_t launch_mode(const ApplyArgs<T>& A, int depth, hipStream_t st) {
+  const dim3 grid(8 * ((A.n_tiles + 7) / 8) * A.n_chunks), block(APPLY_WAVES * 64);
   if (depth >= 3)
-    hipLaunchKernelGGL((k_apply<T, PC, PAIRED, EFF, 3>), grid, block, 0, st, A);
+    hipLaunchKernelGGL((k_apply<T, PC, MODE, 3>), grid, block, 0, st, A);
   else
-    hipLaunchKernelGGL((k_apply<T, PC, PAIRED, EFF, 2>), grid, block, 0, st, A);
+    hipLaunchKernelGGL((k_apply<T, PC, MODE, 2>), grid, block, 0, st, A);
   return hipGetLastError();
-}
-
-template <typename T, int PC, bool PAIRED>
-hipError_t launch_apply_t(const Plan& pl, const ApplyArgs<T>& A, int depth, hipStream_t st) {
-  const int tpx = (A.n_tiles + 7) / 8;
-  const dim3 grid(8 * tpx * pl.n_chunks);
-  switch (pl.effect) {
-    case SOAP_EFFECT_FLUX:
-      return launch_eff<T, PC, PAIRED, SOAP_EFFECT_FLUX>(A, depth, grid, st);
-    case SOAP_EFFECT_BCONV:
-      return launch_eff<T, PC, PAIRED, SOAP_EFFECT_BCONV>(A, depth, grid, st);
-    default:
-      return launch_eff<T, PC, PAIRED, SOAP_EFFECT_TOT>(A, depth, grid, st);
-  }
 }
 
 template <typename T, int PC>
 ApplyArgs<T> make_args(soap_ctx* c, const Plan& pl, const void* win, const int* nvg, void* flux, int order) {
   constexpr int R = ApplyShape<T, PC>::R, TILE = ApplyShape<T, PC>::TILE;
   const bool vec_ok = (c->P % R == 0) && (reinterpret_cast<uintptr_t>(flux) % 16 == 0);
-  ApplyArgs<T> A{c->P, c->Pstride, c->con_spot_stride, c->B, pl.n_ph, pl.n_chunks, (int)((c->P + TILE - 1) / TILE),
-                 pl.effect, pl.paired, pl.vg_cap, vec_ok ? 1 : 0, order,
-                 (const T*)c->d_spec[0], (const T*)c->d_spec[1], (const T*)c->d_spec[2], (const T*)c->d_con_spot,
-                 (const T*)c->d_con_fac, (const T*)c->d_ones, c->d_Q, static_cast<const unsigned char*>(win), nvg,
-                 (T*)flux};
-  return A;
+  return ApplyArgs<T>{c->P, pl.n_ph, pl.n_chunks, (int)((c->P + TILE - 1) / TILE), pl.vg_cap, vec_ok ? 1 : 0, order,
+                      c->d_Q, static_cast<const unsigned char*>(win), nvg, (T*)flux};
 }
 
 template <typename T, int PC>
 hipError_t launch_apply_pc(soap_ctx* c, const Plan& pl, const void* d_win, const int* d_nvg, void* d_flux, int depth,
                            int order, hipStream_t st) {
   const ApplyArgs<T> A = make_args<T, PC>(c, pl, d_win, d_nvg, d_flux, order);
-  return pl.paired ? launch_apply_t<T, PC, true>(pl, A, depth, st) : launch_apply_t<T, PC, false>(pl, A, depth, st);
+  switch (apply_table_mode(c, pl)) {
+    case MODE_SPLIT: return launch_mode<T, PC, MODE_SPLIT>(A, depth, st);
+    case MODE_PAIRED: return launch_mode<T, PC, MODE_PAIRED>(A, depth, st);
+    default: return launch_mode<T, PC, MODE_CONTRAST>(A, depth, st);
+  }
 }
 
 }  // namespace
@@ -459,39 +542,24 @@ hipError_t upload_t(const ApplyBatchCfg* cfgs, int n, void* d_buf, ApplyBatchGro
   return hipMemcpy(g->off, off.data(), sizeof(int) * (n + 1), hipMemcpyHostToDevice);
 }
 
-template <typename T, int PC, bool PAIRED, int EFF>
-void launch_batch_e(const ApplyBatchGroup& g, hipStream_t st) {
+template <typename T, int PC, int MODE>
+void launch_batch_mode(const ApplyBatchGroup& g, hipStream_t st) {
   const dim3 grid((unsigned)g.n_items), block(APPLY_WAVES * 64);
   const auto* a = static_cast<const ApplyArgs<T>*>(g.args);
   const int* off = static_cast<const int*>(g.off);
   if (g.depth >= 3)
-    hipLaunchKernelGGL((k_apply_batch<T, PC, PAIRED, EFF, 3>), grid, block, 0, st, a, off, g.n_cfg);
+    hipLaunchKernelGGL((k_apply_batch<T, PC, MODE, 3>), grid, block, 0, st, a, off, g.n_cfg);
   else
-    hipLaunchKernelGGL((k_apply_batch<T, PC, PAIRED, EFF, 2>), grid, block, 0, st, a, off, g.n_cfg);
-}
-
-// every configuration of a batch group has the group's effect
-template <typename T, int PC, bool PAIRED>
-void launch_batch_t(const ApplyBatchGroup& g, hipStream_t st) {
-  switch (g.effect) {
-    case SOAP_EFFECT_FLUX:
-      launch_batch_e<T, PC, PAIRED, SOAP_EFFECT_FLUX>(g, st);
-      break;
-    case SOAP_EFFECT_BCONV:
-      launch_batch_e<T, PC, PAIRED, SOAP_EFFECT_BCONV>(g, st);
-      break;
-    default:
-      launch_batch_e<T, PC, PAIRED, SOAP_EFFECT_TOT>(g, st);
-      break;
-  }
+    hipLaunchKernelGGL((k_apply_batch<T, PC, MODE, 2>), grid, block, 0, st, a, off, g.n_cfg);
 }
 
 template <typename T, int PC>
 void launch_batch_pc(const ApplyBatchGroup& g, hipStream_t st) {
-  if (g.paired)
-    launch_batch_t<T, PC, true>(g, st);
-  else
-    launch_batch_t<T, PC, false>(g, st);
+  switch (g.mode) {
+    case MODE_SPLIT: launch_batch_mode<T, PC, MODE_SPLIT>(g, st); break;
+    case MODE_PAIRED: launch_batch_mode<T, PC, MODE_PAIRED>(g, st); break;
+    default: launch_batch_mode<T, PC, MODE_CONTRAST>(g, st); break;
+  }
 }
 
 }  // namespace
@@ -502,15 +570,14 @@ size_t apply_batch_bytes(int n) {
 
 hipError_t apply_batch_upload(const ApplyBatchCfg* cfgs, int n, void* d_buf, ApplyBatchGroup* g) {
   g->fp32 = cfgs[0].c->prec == SOAP_PREC_FP32;
-  g->paired = cfgs[0].pl.paired != 0;
+  g->mode = apply_table_mode(cfgs[0].c, cfgs[0].pl);
   g->depth = cfgs[0].c->tune_depth;
-  g->effect = cfgs[0].pl.effect;
   g->pc = cfgs[0].pl.pc;
   if (!pc_valid(g->fp32, g->pc)) return hipErrorInvalidValue;
-  // one precision, table mode, effect, phases per chunk and depth per group
+  // one precision, table mode, phases per chunk and depth per group
   for (int i = 1; i < n; ++i)
-    if ((cfgs[i].c->prec == SOAP_PREC_FP32) != g->fp32 || (cfgs[i].pl.paired != 0) != g->paired ||
-        cfgs[i].pl.effect != g->effect || cfgs[i].pl.pc != g->pc || cfgs[i].c->tune_depth != g->depth)
+    if ((cfgs[i].c->prec == SOAP_PREC_FP32) != g->fp32 || apply_table_mode(cfgs[i].c, cfgs[i].pl) != g->mode ||
+        cfgs[i].pl.pc != g->pc || cfgs[i].c->tune_depth != g->depth)
       return hipErrorInvalidValue;
   if (g->fp32)
     return g->pc == PC_F32_WIDE ? upload_t<float, PC_F32_WIDE>(cfgs, n, d_buf, g) : upload_t<float, PC_F32>(cfgs, n, d_buf, g);

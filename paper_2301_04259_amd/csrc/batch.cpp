@@ -152,7 +152,8 @@ static soap_status create_impl(soap_ctx* const* ctxs, int32_t n_cfg, const soap_
     }
     pl.G = (pl.paired ? 2 : 3) * c->B;
     pl.n_slabs = (c->N + soap::SLAB_COLS - 1) / soap::SLAB_COLS;
-    pl.pc = c->pc;
+    // the narrow layout where none is set: the configurations fill the chip together
+    pl.pc = c->pc ? c->pc : (c->prec == SOAP_PREC_FP32 ? soap::PC_F32 : soap::PC_F64);
     pl.n_chunks = (np + pl.pc - 1) / pl.pc;
     pl.vg_cap = pl.G * ((c->J + soap::APPLY_JW - 1) / soap::APPLY_JW);
     const size_t GJ = (size_t)pl.G * c->J;
@@ -193,7 +194,7 @@ static soap_status create_impl(soap_ctx* const* ctxs, int32_t n_cfg, const soap_
     std::vector<long long> keys;
     for (int i = 0; i < n_cfg; ++i) {
       const soap_ctx* c = cp[i].c;
-      const long long k = ((long long)(c->prec == SOAP_PREC_FP32) << 40) | ((long long)cp[i].pl.paired << 32) |
+      const long long k = ((long long)(c->prec == SOAP_PREC_FP32) << 40) | ((long long)soap::apply_table_mode(c, cp[i].pl) << 32) |
                           ((long long)cp[i].pl.pc << 8) | (long long)c->tune_depth;
       size_t g = 0;
       while (g < keys.size() && keys[g] != k) ++g;

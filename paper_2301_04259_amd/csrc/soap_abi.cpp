@@ -149,7 +149,7 @@ void destroy_ctx(soap_ctx* c) {
   }
   for (int t = 0; t < 3; ++t)
     if (c->d_spec_base[t]) (void)soap::dev_free(c->d_spec_base[t]);
-  void* bufs[] = {c->d_mu, c->d_col_c, c->d_col_w, c->d_colW, c->d_Kq, c->d_Kq_fx, c->d_Q, c->d_con_base, c->d_ones};
+  void* bufs[] = {c->d_mu, c->d_col_c, c->d_col_w, c->d_colW, c->d_Kq, c->d_Kq_fx, c->d_Q, c->d_con_base};
   for (void* p : bufs)
     if (p) (void)soap::dev_free(p);
   soap::Workspace* ws[] = {&c->ws_flux, &c->ws_ccf, &c->ws_ccfout, &c->ws_rv, &c->ws_mask, &c->ws_specin,
@@ -273,7 +273,6 @@ soap_status init_impl(const soap_star_desc* d, soap_ctx* c) {
   // the allocation-free entry point's scratch on this device (its status is
   // kept and reported by that entry point)
   (void)soap::scratch_setup(c->device);
-  c->pc = (c->prec == SOAP_PREC_FP32) ? soap::PC_F32 : soap::PC_F64;
   c->n_tiles = (int)((c->P + soap::APPLY_TILE_MAX - 1) / soap::APPLY_TILE_MAX);
   // padded rows: PAD_FRONT samples before pixel 0, and past the last tile
   // enough room for the widest window the apply kernel reads
@@ -299,7 +298,6 @@ soap_status init_impl(const soap_star_desc* d, soap_ctx* c) {
     HIP_TRY(hipMemsetAsync(c->d_Kq_fx, 0, sizeof(unsigned long long) * c->B * c->J, c->stream));
   }
   HIP_TRY(soap::dev_malloc((void**)&c->d_Q, sizeof(double) * c->n_tiles * soap::APPLY_TILE_MAX));
-  HIP_TRY(soap::dev_malloc(&c->d_ones, c->esize * c->n_tiles * soap::APPLY_TILE_MAX));
   if (c->cmode == SOAP_CONTRAST_PLANCK) {
     // one spot row for every bin, one facula row per bin
     c->con_rows = c->B + 1;
@@ -331,7 +329,6 @@ soap_status init_impl(const soap_star_desc* d, soap_ctx* c) {
 
   HIP_TRY(soap::launch_pad(c));
   HIP_TRY(soap::launch_geom(c));
-  HIP_TRY(soap::launch_ones(c));
   if (c->cmode == SOAP_CONTRAST_PLANCK) HIP_TRY(soap::launch_contrast(c));
   if (c->cmode == SOAP_CONTRAST_ARRAY) HIP_TRY(soap::launch_pad_rows(c, c->d_con_base, c->con_rows));
   HIP_TRY(soap::launch_quiet(c));
@@ -528,7 +525,7 @@ soap_status active_impl(soap_ctx* c, const soap_region* regions, int32_t n_regio
   }
   pl.G = (pl.paired ? 2 : 3) * c->B;
   pl.n_slabs = (c->N + soap::SLAB_COLS - 1) / soap::SLAB_COLS;
-  pl.pc = c->pc;
+  pl.pc = c->pc ? c->pc : soap::auto_pc(c->prec == SOAP_PREC_FP32, c->P, n_phases, pj_host != nullptr);
   pl.n_chunks = (n_phases + pl.pc - 1) / pl.pc;
   pl.vg_cap = pl.G * ((c->J + soap::APPLY_JW - 1) / soap::APPLY_JW);
   const size_t GJ = (size_t)pl.G * c->J;
@@ -1106,25 +1103,25 @@ SOAP_API soap_status soap_profile_read(soap_ctx* c, soap_profile* out) {
         const unsigned char* rec = vg.data() + ((size_t)ch * c->last_vg_cap + v) * wb;
         std::memcpy(&h, rec, sizeof(h));
         {
-          // taps[q][p] after the header, float or double per the precision;
-          // one mask bit per (offset, pair of phases) with a non-zero tap:
-          // each bit costs two FMAs per pixel, each offset with a bit one
-          // difference formation
-          int pairs = 0, offs = 0;
-          for (unsigned m = h.gmask; m; m &= m - 1) ++pairs;
+          // one mask bit per (offset, group of phases) with a non-zero tap:
+          // each bit costs one FMA per phase of the group and pixel, each
+          // offset with a bit one difference formation
+          const int gp = soap::win_group((int)c->esize), ng = c->last_pc / gp;
+          int bits = 0, offs = 0;
+          for (unsigned m = h.gmask; m; m &= m - 1) ++bits;
           for (int q = 0; q < soap::APPLY_JW; ++q)
-            if ((h.gmask >> (q * (c->last_pc / 2))) & ((1u << (c->last_pc / 2)) - 1u)) ++offs;
-          out->fma_issued += (int64_t)pairs * 2 + offs;
+            if ((h.gmask >> (q * ng)) & ((1u << ng) - 1u)) ++offs;
+          out->fma_issued += (int64_t)bits * gp + offs;
           for (int q = 0; q < soap::APPLY_JW; ++q) {
             bool any = false;
             for (int pp = 0; pp < c->last_pc; ++pp) {
               double tap;
               if (c->prec == SOAP_PREC_FP32) {
                 float f;
-                std::memcpy(&f, rec + 16 + sizeof(float) * ((size_t)q * c->last_pc + pp), sizeof f);
+                std::memcpy(&f, rec + soap::WIN_HEAD + sizeof(float) * soap::win_tap(q, pp, c->last_pc, 4), sizeof f);
                 tap = f;
               } else {
-                std::memcpy(&tap, rec + 16 + sizeof(double) * ((size_t)q * c->last_pc + pp), sizeof tap);
+                std::memcpy(&tap, rec + soap::WIN_HEAD + sizeof(double) * soap::win_tap(q, pp, c->last_pc, 8), sizeof tap);
               }
               if (tap != 0.0) {
                 ++out->taps_nonzero;

@@ -30,12 +30,11 @@ constexpr int MAX_J = 64;  // tap offsets per table row
 // Apply kernel shape: a block of APPLY_WAVES waves covers a tile of
 // APPLY_WAVES x 64 x R consecutive pixels for one chunk of PC phases; each
 // wave walks the chunk's windows of APPLY_JW offsets over its own 64 x R
-// pixels with R x PC accumulators per lane (64 floats or 16 doubles), so
-// R = 64 / PC in FP32 (PC = 8 or 16) and R = 16 / PC in FP64 (PC = 4 or 8).
-// PC is a property of the context's tap tables, chosen per context (the
-// first value of each pair is the default).  Quiet spectrum and rows are
-// padded to whole tiles of APPLY_TILE_MAX pixels.
-constexpr int APPLY_JW = 4;
+// pixels (R = 4 in FP32, 2 in FP64: 16 bytes of every row per lane) with
+// R x PC accumulators per lane.  PC (8 or 16 in FP32, 4 or 8 in FP64) is a
+// property of the context's tap tables, chosen per context.  Quiet spectrum
+// and rows are padded to whole tiles of APPLY_TILE_MAX pixels.
+constexpr int APPLY_JW = 8;
 constexpr int APPLY_WAVES = 4;
 constexpr int APPLY_TILE_MAX = 2048;
 constexpr int PC_MAX = 16;
@@ -44,18 +43,43 @@ constexpr int PC_F64 = 4, PC_F64_WIDE = 8;
 inline bool pc_valid(bool fp32, int pc) {
   return fp32 ? (pc == PC_F32 || pc == PC_F32_WIDE) : (pc == PC_F64 || pc == PC_F64_WIDE);
 }
-// bytes of a window record (16-byte header, APPLY_JW x pc taps)
-constexpr int win_bytes(int pc, int esize) { return 16 + APPLY_JW * pc * esize; }
-constexpr int WIN_BYTES_MAX = 16 + APPLY_JW * PC_F32_WIDE * 4;
+constexpr int WIN_HEAD = 32;  // bytes of a window record's header
+// Phases per chunk of a call whose context sets none.  The wide layout halves
+// the copies and differences per phase but also the blocks, and its waves walk
+// the union of more phases' windows: it is taken from four wide blocks per CU
+// on (at about 1000 blocks: 150000 px x 100 phases 35.4 us narrow, 31.8 wide;
+// 206k px x 100 phases, 1407 blocks, 42.9 and 38.7; 60000 px x 60 phases, 236
+// blocks, 20.6 and 27.4; FP64 100003 px x 60 phases, 1568 blocks, 45.4 and
+// 40.2).  Phases with region lists of their own share few windows (500 spots
+// x 8 phases: 107 and 110 us) and stay narrow.
+inline int auto_pc(bool fp32, int64_t n_pix, int64_t n_ph, bool own_lists) {
+  const int wide = fp32 ? PC_F32_WIDE : PC_F64_WIDE, tile = fp32 ? 1024 : 512;
+  const int64_t blocks = ((n_pix + tile - 1) / tile) * ((n_ph + wide - 1) / wide);
+  return !own_lists && blocks >= 1024 ? wide : (fp32 ? PC_F32 : PC_F64);
+}
+// bytes of a window record (header, APPLY_JW x pc taps)
+constexpr int win_bytes(int pc, int esize) { return WIN_HEAD + APPLY_JW * pc * esize; }
+// phases per mask bit of a window: the phases one matrix instruction adds
+// (FP32), or a pair (FP64)
+constexpr int win_group(int esize) { return esize == 4 ? 4 : 2; }
+// place of the tap of (offset q, phase p) among a record's taps.  FP32: lane l
+// of the apply kernel takes the taps of phases 4 g + l % 4, so those of one
+// l % 4 lie together, offset by offset, the pc / 4 groups g of each; FP64:
+// offset by offset in phase order.
+constexpr int win_tap(int q, int p, int pc, int esize) {
+  return esize == 4 ? ((p & 3) * APPLY_JW + q) * (pc / 4) + (p >> 2) : q * pc + p;
+}
 template <typename T, int PC>
 struct ApplyShape {
   static_assert((sizeof(T) == 4 && (PC == PC_F32 || PC == PC_F32_WIDE)) ||
                     (sizeof(T) == 8 && (PC == PC_F64 || PC == PC_F64_WIDE)),
                 "phases per chunk");
-  static constexpr int R = (sizeof(T) == 4 ? 64 : 16) / PC;  // pixels per lane
+  static constexpr int R = 16 / (int)sizeof(T);              // pixels per lane
   static constexpr int TILE = APPLY_WAVES * 64 * R;           // pixels per block
   static constexpr int WB = win_bytes(PC, (int)sizeof(T));    // window record bytes
-  static_assert(TILE <= APPLY_TILE_MAX && WB <= WIN_BYTES_MAX && APPLY_JW * PC / 2 <= 32, "shape");
+  static constexpr int GP = win_group((int)sizeof(T));        // phases per mask bit
+  static constexpr int NG = PC / GP;                          // mask bits per offset
+  static_assert(TILE <= APPLY_TILE_MAX && APPLY_JW * NG <= 32, "shape");
 };
 
 // Padded rows of the local spectra and contrast arrays: PAD_FRONT copies of
@@ -91,20 +115,22 @@ struct Region {
 };
 
 // A window record: APPLY_JW tap offsets [jlo, jlo + APPLY_JW) of one group
-// in one phase chunk, stored as a 16-byte header followed by the dense taps
-// taps[q][p] (q < APPLY_JW, p < the chunk's phase count; zeros where a phase
-// has no tap).  Bit (q * PC / 2 + k) of gmask: phase 2k or 2k + 1 of the
-// chunk has a non-zero tap at offset jlo + q.
+// in one phase chunk, stored as a header followed by the dense taps
+// taps[win_tap(q, p)] (q < APPLY_JW, p < the chunk's phase count; zeros where
+// a phase has no tap).  Bit (q * PC / GP + k) of gmask (GP = win_group): a
+// phase of GP k .. GP k + GP - 1 has a non-zero tap at offset jlo + q.  The
+// header holds the addresses the apply kernel copies from, for output pixel 0: the active (or, for quiet
+// removal and the flux effect, quiet) row and the quiet row, both at sample
+// -jlo - (APPLY_JW - 1), and the contrast row at pixel 0 (0 where the table
+// mode has none).
 // Group g: paired tables g = (type - 1) * B + bin; split tables
 // g = type * B + bin with type 0 the quiet removal.
 struct WinHead {
-  int t;    // surface type of the group (0 = quiet removal)
-  int b;    // mu bin of the group
-  int jlo;
+  unsigned long long act, quiet, con;
   unsigned int gmask;
+  unsigned short t, b;  // surface type (0 = quiet removal) and mu bin of the group
 };
-// window records staged in LDS per pass of the apply kernel
-constexpr int APPLY_LDS_WIN = 96;
+static_assert(sizeof(WinHead) == WIN_HEAD, "window record header");
 // phase chunks the apply kernel orders by work (more run in their natural order)
 constexpr int APPLY_RANKED = 64;
 
@@ -144,7 +170,7 @@ struct soap_ctx {
   bool has_type[3] = {false, false, false};
   int jmin = 0, jmax = 0, J = 0;  // tap offset range [jmin, jmax], J = jmax - jmin + 1
   size_t esize = 8;               // element size of spectra / flux
-  int pc = soap::PC_F64;          // phases per apply chunk of the next call's tables
+  int pc = 0;                     // phases per apply chunk of the next call's tables (0: auto_pc)
 
   // resident device state (row pointers point at pixel 0 of row 0)
   void* d_spec_base[3] = {nullptr, nullptr, nullptr};
@@ -162,7 +188,6 @@ struct soap_ctx {
   int con_rows = 0;                                // rows of d_con_base
   int64_t con_spot_stride = 0;                     // 0: one spot row for every bin (PLANCK)
   double disk_weight = 0.0;                        // sum over cells of (2/N)^2 |I(mu)|
-  void* d_ones = nullptr;                          // [n_tiles * TILE] of 1 (no-contrast operand)
 
   // per-call workspace (grown on demand, freed by soap_destroy)
   // Per-call tables (region parameters, tap accumulators and taps, window
@@ -249,7 +274,6 @@ struct Plan {
 hipError_t launch_geom(soap_ctx* c);
 hipError_t launch_pad(soap_ctx* c);
 hipError_t launch_contrast(soap_ctx* c);
-hipError_t launch_ones(soap_ctx* c);
 hipError_t launch_quiet(soap_ctx* c);
 // outputs and scratch of the weight kernel
 struct WeightsOut {
@@ -293,7 +317,9 @@ struct WeightsArgs {
   unsigned long long* Kfx;
 };
 struct FinishArgs {
-  int n_ph, PC, G, J, jmin, B, paired, vg_cap;
+  int n_ph, PC, G, J, jmin, B, paired, vg_cap, flux;  // flux: SOAP_EFFECT_FLUX
+  const void *spec[3], *con[3];  // rows of each type (pixel 0 of bin 0); con: null without a contrast
+  int64_t Pstride, cs_stride;    // row strides of the spectra and of the spot contrast
   unsigned long long* Kfx;
   double* K;
   unsigned long long* mask;
@@ -334,6 +360,10 @@ size_t table_batch_bytes(const TableBatchCfg* cfgs, int n_cfg);
 hipError_t table_batch_upload(const TableBatchCfg* cfgs, int n, void* d_buf, TableBatch* tb);
 // enqueues params, then weights, then finish (three dependent phases)
 hipError_t table_batch_launch(const TableBatch& tb, hipStream_t st);
+// table mode of the apply kernel: split tables (the active operand alone),
+// paired tables without a contrast (D = A - S_q), and with one (D = C A - S_q)
+enum { MODE_SPLIT = 0, MODE_PAIRED = 1, MODE_CONTRAST = 2 };
+int apply_table_mode(const soap_ctx* c, const Plan& pl);
 hipError_t launch_apply(soap_ctx* c, const Plan& pl, const void* d_win, const int* d_nvg, void* d_flux);
 // apply with an explicit shape (threads per block, windows staged per LDS
 // pass) on stream st
@@ -350,8 +380,8 @@ struct ApplyBatchCfg {
   void* flux;
 };
 struct ApplyBatchGroup {
-  bool fp32 = true, paired = true;
-  int n_cfg = 0, n_items = 0, depth = 2, order = 0, effect = SOAP_EFFECT_TOT, pc = 0;
+  bool fp32 = true;
+  int n_cfg = 0, n_items = 0, depth = 2, mode = 0, pc = 0;
   void* args = nullptr;  // device ApplyArgs[n_cfg]
   void* off = nullptr;   // device item offsets [n_cfg + 1]
 };

@@ -80,8 +80,8 @@ SOAP_API soap_status soap_set_apply_shape(soap_ctx* c, int32_t depth, int32_t or
   if (!c) return SOAP_ERR_ARG;
   const bool d_ok = std::find(std::begin(kDepths), std::end(kDepths), depth) != std::end(kDepths);
   const bool o_ok = std::find(std::begin(kOrders), std::end(kOrders), order) != std::end(kOrders);
-  const int pc = phases_per_chunk == 0 ? default_pc(c) : phases_per_chunk;
-  if (!d_ok || !o_ok || !soap::pc_valid(c->prec == SOAP_PREC_FP32, pc)) {
+  const int pc = phases_per_chunk;
+  if (!d_ok || !o_ok || (pc != 0 && !soap::pc_valid(c->prec == SOAP_PREC_FP32, pc))) {
     char buf[160];
     std::snprintf(buf, sizeof buf, "depth must be 2 or 3, order 0 or 1 and phases_per_chunk 0, %d or %d", default_pc(c),
                   wide_pc(c));
@@ -150,7 +150,7 @@ SOAP_API soap_status soap_autotune(soap_ctx* c, const soap_region* regions, int3
     for (int v : nvg) tot += v;
   }
   char key[256];
-  std::snprintf(key, sizeof key, "v4|%s|%s|P2^%d|J%d|B%d|ph2^%d|win2^%d", c->prec == SOAP_PREC_FP32 ? "f32" : "f64",
+  std::snprintf(key, sizeof key, "v5|%s|%s|P2^%d|J%d|B%d|ph2^%d|win2^%d", c->prec == SOAP_PREC_FP32 ? "f32" : "f64",
                 pl.paired ? "paired" : "split", ilog2_ceil(c->P), c->J, c->B, ilog2_ceil(pl.n_ph),
                 ilog2_ceil(std::max(1LL, tot / std::max(1, pl.n_chunks))));
   int cpc = 0, dp = 0, od = 0;

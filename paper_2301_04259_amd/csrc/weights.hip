@@ -25,7 +25,7 @@
 // the order).  k_finish, one block per chunk of phases, converts the tables
 // to double (clearing them for the next call), records per (phase, group)
 // the bitmask of non-zero offsets, and turns the chunk into window records
-// of APPLY_JW offsets with dense taps and per-offset masks of the pairs of
+// of APPLY_JW offsets with dense taps and per-offset masks of the groups of
 // phases that have a tap.
 // Every sum has a fixed order, so results repeat bit for bit.
 #include <algorithm>
@@ -54,13 +54,15 @@ __device__ __forceinline__ unsigned long long to_fx(double x) {
 
 // Window records of one chunk of PC phases (one block): windows of APPLY_JW
 // offsets with their dense [offset][phase] taps and per-offset masks of the
-// pairs of phases that have a tap.  Kc: the chunk's taps [np][G][J],
+// groups of phases that have a tap.  Kc: the chunk's taps [np][G][J],
 // maskc: its offset masks [np][G] (LDS or global).  sm: LDS of at least
 // (4 G + vg_cap + 2) ints + G 64-bit words.
 template <typename T>
-__device__ void compact_chunk(int chunk, int n_ph, int PC, int G, int J, int jmin, int B, int paired,
-                              const double* Kc, const unsigned long long* maskc, unsigned char* __restrict__ wins,
-                              int* __restrict__ nvg, int vg_cap, int* sm) {
+__device__ void compact_chunk(const FinishArgs& a, int chunk, const double* Kc, const unsigned long long* maskc,
+                              int* sm) {
+  const int n_ph = a.n_ph, PC = a.PC, G = a.G, J = a.J, jmin = a.jmin, B = a.B, paired = a.paired, vg_cap = a.vg_cap;
+  unsigned char* __restrict__ wins = a.wins;
+  int* __restrict__ nvg = a.nvg;
   int* s_cnt = sm;           // [G] windows per group
   int* s_base = sm + G;      // [G] first window index
   int* s_lo = sm + 2 * G;    // [G] first non-zero offset of the union
@@ -69,7 +71,8 @@ __device__ void compact_chunk(int chunk, int n_ph, int PC, int G, int J, int jmi
   unsigned long long* s_union = reinterpret_cast<unsigned long long*>(sm + 4 * G + vg_cap + (vg_cap & 1));  // [G]
   const int p0 = chunk * PC;
   const int np = min(PC, n_ph - p0);
-  const int NP = PC / 2;  // mask bits per offset: pairs of phases
+  constexpr int GP = win_group((int)sizeof(T));
+  const int NG = PC / GP;  // mask bits per offset: groups of GP phases
   const int GJ = G * J;
   const int nwin = (J + APPLY_JW - 1) / APPLY_JW;
   const int wb = win_bytes(PC, (int)sizeof(T));  // record bytes
@@ -103,38 +106,44 @@ __device__ void compact_chunk(int chunk, int n_ph, int PC, int G, int J, int jmi
   }
   __syncthreads();
   // one thread per (group, window slot, offset)
-  for (int t = threadIdx.x; t < G * nwin * APPLY_JW; t += blockDim.x) {
-    const int g = t / (nwin * APPLY_JW);
-    const int rem = t - g * nwin * APPLY_JW;
+  for (int u = threadIdx.x; u < G * nwin * APPLY_JW; u += blockDim.x) {
+    const int g = u / (nwin * APPLY_JW);
+    const int rem = u - g * nwin * APPLY_JW;
     const int wslot = rem / APPLY_JW;
     const int q = rem - wslot * APPLY_JW;
     if (!s_cnt[g]) continue;
-    const unsigned long long u = s_union[g];
-    const int a = s_lo[g] + wslot * APPLY_JW;
-    if (a >= J || !((u >> a) & ((1ull << APPLY_JW) - 1))) continue;
+    const unsigned long long un = s_union[g];
+    const int lo = s_lo[g] + wslot * APPLY_JW;
+    if (lo >= J || !((un >> lo) & ((1ull << APPLY_JW) - 1))) continue;
     int v = s_base[g];
-    for (int b = s_lo[g]; b < a; b += APPLY_JW)
-      if ((u >> b) & ((1ull << APPLY_JW) - 1)) ++v;
+    for (int b = s_lo[g]; b < lo; b += APPLY_JW)
+      if ((un >> b) & ((1ull << APPLY_JW) - 1)) ++v;
     unsigned char* rec = wrec + (int64_t)v * wb;
     if (q == 0) {
       WinHead h;
-      h.t = paired ? g / B + 1 : g / B;
-      h.b = g % B;
-      h.jlo = jmin + a;
+      const int t = paired ? g / B + 1 : g / B, b = g % B;
+      const int64_t row = b * a.Pstride, at = row - (jmin + lo) - (APPLY_JW - 1);
+      h.t = (unsigned short)t;
+      h.b = (unsigned short)b;
+      h.quiet = reinterpret_cast<unsigned long long>(static_cast<const T*>(a.spec[SOAP_QUIET]) + at);
+      h.act = (t == 0 || a.flux) ? h.quiet : reinterpret_cast<unsigned long long>(static_cast<const T*>(a.spec[t]) + at);
+      h.con = a.con[t] ? reinterpret_cast<unsigned long long>(static_cast<const T*>(a.con[t]) +
+                                                               (t == SOAP_SPOT ? b * a.cs_stride : row))
+                       : 0ull;
       h.gmask = 0u;
       *reinterpret_cast<WinHead*>(rec) = h;
     }
-    T* row = reinterpret_cast<T*>(rec + 16) + q * PC;
+    T* taps = reinterpret_cast<T*>(rec + WIN_HEAD);
     double kv[PC_MAX];
 #pragma unroll
     for (int p = 0; p < PC_MAX; ++p)
-      kv[p] = (p < np && a + q < J) ? Kc[p * GJ + g * J + a + q] : 0.0;
+      kv[p] = (p < np && lo + q < J) ? Kc[p * GJ + g * J + lo + q] : 0.0;
     unsigned int m = 0;
 #pragma unroll
     for (int p = 0; p < PC_MAX; ++p) {
       if (p < PC) {
-        row[p] = (T)kv[p];
-        if (kv[p] != 0.0) m |= 1u << ((q * NP) + (p >> 1));
+        taps[win_tap(q, p, PC, (int)sizeof(T))] = (T)kv[p];
+        if (kv[p] != 0.0) m |= 1u << (q * NG + p / GP);
       }
     }
     if (m) atomicOr(&s_gm[v], m);
@@ -152,13 +161,10 @@ __device__ void compact_chunk(int chunk, int n_ph, int PC, int G, int J, int jmi
 // they go through K and mask in global memory.
 template <typename T, bool IN_LDS>
 __device__ __forceinline__ void finish_block(const FinishArgs& a, int chunk, unsigned char* fin_lds) {
-  const int n_ph = a.n_ph, PC = a.PC, G = a.G, J = a.J, jmin = a.jmin, B = a.B, paired = a.paired,
-            vg_cap = a.vg_cap;
+  const int n_ph = a.n_ph, PC = a.PC, G = a.G, J = a.J;
   unsigned long long* __restrict__ Kfx = a.Kfx;
   double* __restrict__ K = a.K;
   unsigned long long* __restrict__ mask = a.mask;
-  unsigned char* __restrict__ wins = a.wins;
-  int* __restrict__ nvg = a.nvg;
   const int p0 = chunk * PC;
   const int np = min(PC, n_ph - p0);
   const int GJ = G * J;
@@ -194,7 +200,7 @@ __device__ __forceinline__ void finish_block(const FinishArgs& a, int chunk, uns
     maskc[t] = mk;
   }
   __syncthreads();
-  compact_chunk<T>(chunk, n_ph, PC, G, J, jmin, B, paired, Kc, maskc, wins, nvg, vg_cap, sm);
+  compact_chunk<T>(a, chunk, Kc, maskc, sm);
 }
 
 template <typename T, bool IN_LDS>
@@ -605,7 +611,24 @@ WeightsArgs weights_args(const soap_ctx* c, const Plan& pl, int n_reg, int max_r
 }
 
 FinishArgs finish_args(const soap_ctx* c, const Plan& pl, const WeightsOut& o) {
-  return FinishArgs{pl.n_ph, pl.pc, pl.G, c->J, c->jmin, c->B, pl.paired, pl.vg_cap, o.Kfx, o.K, o.mask, o.wins,
+  const bool con = apply_table_mode(c, pl) == MODE_CONTRAST;
+  return FinishArgs{pl.n_ph,
+                    pl.pc,
+                    pl.G,
+                    c->J,
+                    c->jmin,
+                    c->B,
+                    pl.paired,
+                    pl.vg_cap,
+                    pl.effect == SOAP_EFFECT_FLUX,
+                    {c->d_spec[0], c->d_spec[1], c->d_spec[2]},
+                    {nullptr, con ? c->d_con_spot : nullptr, con ? c->d_con_fac : nullptr},
+                    c->Pstride,
+                    c->con_spot_stride,
+                    o.Kfx,
+                    o.K,
+                    o.mask,
+                    o.wins,
                     o.nvg};
 }
 
