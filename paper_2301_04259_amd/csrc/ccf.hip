@@ -315,106 +315,124 @@ constexpr double FWHM_PER_SIGMA = 2.3548200450309493;  // 2 sqrt(2 ln 2)
 constexpr int CCF_FIN_THREADS = 256;
 constexpr int64_t CCF_FIT_WAVES_FROM = 512;  // spectra per call above which one wave fits each
 
-// Sums of the fit at p, identical in every lane: S[0] = chi^2,
-// S[1..4] = g = J^T r, S[5..14] = J^T J (upper triangle, row by row),
-// S[15..19] = sum r d2f/dp_a dp_b for (amp, mu), (amp, sigma), (mu, mu),
-// (mu, sigma), (sigma, sigma) (the only second derivatives that are not
-// zero), with f = c0 - amp e, e = exp(-(v - mu)^2 / (2 sigma^2)), r = f - y
-// and parameters ordered (c0, amp, mu, sigma).
+// Sums of the fit at p = (c0, amp, mu, sigma), identical in every lane.  With
+// q = (v - mu) / sigma, e = exp(-q^2 / 2) and r = c0 - amp e - y they are the
+// sums over the samples of r^2, r, r e q^k (k = 0 .. 4), e q^k (k = 0 .. 2) and
+// e^2 q^k (k = 0 .. 4): every entry of J^T r, J^T J and of the residual-weighted
+// second derivatives is one or two of them, up to factors amp and sigma that
+// gf_solve leaves out by scaling the centre and width (15 sums in one
+// butterfly, where the 20 sums of the entries themselves took two).
+enum { GF_RR, GF_R, GF_RE, GF_RE1, GF_RE2, GF_RE3, GF_RE4, GF_E, GF_E1, GF_E2, GF_EE, GF_EE1, GF_EE2, GF_EE3, GF_EE4,
+       GF_N };  // GF_N: number of samples
+
 template <int NPT>
-__device__ void gf_eval(const double (&y)[NPT], int n_v, double v0, double dv, const double p[4],
-                        double S[20]) {
+__device__ __forceinline__ void gf_eval(const double (&y)[NPT], int n_v, double v0, double dv, const double p[4],
+                                        double S[16]) {
   const int lane = threadIdx.x & 63;
-  double v[16], w[16];
+  double v[16];
 #pragma unroll
-  for (int q = 0; q < 16; ++q) v[q] = w[q] = 0.0;
+  for (int q = 0; q < 16; ++q) v[q] = 0.0;
   const double is = 1.0 / p[3];
-  const double is2 = is * is;
+  // no branch per sample, so that the samples of a lane overlap: places past
+  // the grid count as e = r = 0
 #pragma unroll
   for (int t = 0; t < NPT; ++t) {
-    if (64 * t >= n_v) break;  // uniform
     const int i = lane + 64 * t;
-    if (i < n_v) {
-      const double x = v0 + dv * i;
-      const double d = x - p[2];
-      const double z = d * d * is2;  // (d / sigma)^2
-      const double e = exp(-0.5 * z);
-      const double ae = p[1] * e;
-      const double r = p[0] - ae - y[t];
-      const double g[4] = {1.0, -e, -ae * d * is2, -ae * z * is};
-      v[0] += r * r;
-#pragma unroll
-      for (int r0 = 0; r0 < 4; ++r0) v[1 + r0] += g[r0] * r;
-      int q = 5;
-#pragma unroll
-      for (int r0 = 0; r0 < 4; ++r0)
-#pragma unroll
-        for (int r1 = r0; r1 < 4; ++r1) v[q++] += g[r0] * g[r1];
-      const double re = r * e;
-      w[0] += re * (-d * is2);                       // (amp, mu)
-      w[1] += re * (-z * is);                        // (amp, sigma)
-      w[2] += r * (-ae * (z - 1.0) * is2);           // (mu, mu)
-      w[3] += r * (-ae * d * (z - 2.0) * is2 * is);  // (mu, sigma)
-      w[4] += r * (-ae * z * (z - 3.0) * is2);       // (sigma, sigma)
-    }
+    const bool in = i < n_v;
+    const double q = (v0 + dv * i - p[2]) * is;
+    const double q2 = q * q;
+    const double ex = exp(-0.5 * q2);
+    const double e = in ? ex : 0.0;
+    const double r = in ? p[0] - p[1] * ex - y[t] : 0.0;
+    const double e1 = e * q, e2 = e * q2, re2 = r * e2;
+    v[GF_RR] = fma(r, r, v[GF_RR]);
+    v[GF_R] += r;
+    v[GF_RE] = fma(r, e, v[GF_RE]);
+    v[GF_RE1] = fma(r, e1, v[GF_RE1]);
+    v[GF_RE2] += re2;
+    v[GF_RE3] = fma(re2, q, v[GF_RE3]);
+    v[GF_RE4] = fma(re2, q2, v[GF_RE4]);
+    v[GF_E] += e;
+    v[GF_E1] += e1;
+    v[GF_E2] += e2;
+    v[GF_EE] = fma(e, e, v[GF_EE]);
+    v[GF_EE1] = fma(e, e1, v[GF_EE1]);
+    v[GF_EE2] = fma(e1, e1, v[GF_EE2]);
+    v[GF_EE3] = fma(e1, e2, v[GF_EE3]);
+    v[GF_EE4] = fma(e2, e2, v[GF_EE4]);
   }
   const double tv = butterfly16_rows(v, lane);
-  const double tw = butterfly16_rows(w, lane);
 #pragma unroll
   for (int q = 0; q < 15; ++q) S[q] = read_lane(tv, q);
-#pragma unroll
-  for (int q = 0; q < 5; ++q) S[15 + q] = read_lane(tw, q);
+  S[GF_N] = (double)n_v;
 }
 
-// Solves (H + lam diag(J^T J)) x = -g by Cholesky, H = J^T J (+ the
-// second-derivative sums when newton is set).  False when the matrix is not
-// positive definite.
-__device__ bool gf_solve(const double S[20], bool newton, double lam, double x[4]) {
-  double A[4][4];
-  int q = 5;
-  for (int r0 = 0; r0 < 4; ++r0)
-    for (int r1 = r0; r1 < 4; ++r1) {
-      A[r0][r1] = S[q];
-      A[r1][r0] = S[q];
-      ++q;
-    }
+// 1 / x to rounding error (two Newton steps on the hardware estimate) for the
+// pivots of a small solve; not for x = 0, infinities or denormals
+__device__ __forceinline__ double fast_rcp(double x) {
+  double y = __builtin_amdgcn_rcp(x);
+  y = fma(fma(-x, y, 1.0), y, y);
+  return fma(fma(-x, y, 1.0), y, y);
+}
+
+// Solves (H + lam diag(J^T J)) x = b at p by L D L^T, H = J^T J (+ the
+// second-derivative sums when newton is set), for the parameters (c0, amp, mu,
+// sigma).  The system is formed for s = amp / sigma times the last two, whose
+// model derivatives are then -e q and -e q^2; b and x are in those scaled
+// parameters too (b = D^-1 b_p, x = D x_p with D = diag(1, 1, s, s)).  False
+// when the matrix is not positive definite.
+__device__ __forceinline__ bool gf_solve_scaled(const double S[16], const double p[4], bool newton, double lam,
+                                                const double b[4], double x[4]) {
+  double a01 = -S[GF_E], a02 = -S[GF_E1], a03 = -S[GF_E2], a12 = S[GF_EE1], a13 = S[GF_EE2], a23 = S[GF_EE3];
+  double a11 = S[GF_EE], a22 = S[GF_EE2], a33 = S[GF_EE4];
+  const double a00 = fma(lam, S[GF_N], S[GF_N]);
+  const double d11 = lam * a11, d22 = lam * a22, d33 = lam * a33;
   if (newton) {
-    A[1][2] += S[15];
-    A[2][1] += S[15];
-    A[1][3] += S[16];
-    A[3][1] += S[16];
-    A[2][2] += S[17];
-    A[2][3] += S[18];
-    A[3][2] += S[18];
-    A[3][3] += S[19];
+    const double ia = 1.0 / p[1];
+    a12 = fma(-ia, S[GF_RE1], a12);
+    a13 = fma(-ia, S[GF_RE2], a13);
+    a22 = fma(-ia, S[GF_RE2] - S[GF_RE], a22);
+    a23 = fma(-ia, S[GF_RE3] - 2.0 * S[GF_RE1], a23);
+    a33 = fma(-ia, S[GF_RE4] - 3.0 * S[GF_RE2], a33);
   }
-  const double dg[4] = {S[5], S[9], S[12], S[14]};  // diag(J^T J)
-  for (int r = 0; r < 4; ++r) A[r][r] += lam * dg[r];
-  double L[4][4] = {{0}}, rd[4];
-  for (int i = 0; i < 4; ++i) {
-    for (int j = 0; j <= i; ++j) {
-      double s = A[i][j];
-      for (int k = 0; k < j; ++k) s -= L[i][k] * L[j][k];
-      if (i == j) {
-        if (!(s > 0.0)) return false;
-        L[i][i] = sqrt(s);
-        rd[i] = 1.0 / L[i][i];
-      } else {
-        L[i][j] = s * rd[j];
-      }
-    }
-  }
-  double z[4];
-  for (int i = 0; i < 4; ++i) {
-    double s = -S[1 + i];
-    for (int k = 0; k < i; ++k) s -= L[i][k] * z[k];
-    z[i] = s * rd[i];
-  }
-  for (int i = 3; i >= 0; --i) {
-    double s = z[i];
-    for (int k = i + 1; k < 4; ++k) s -= L[k][i] * x[k];
-    x[i] = s * rd[i];
-  }
+  a11 += d11;
+  a22 += d22;
+  a33 += d33;
+  // pivots d0 .. d3, unit lower factor l
+  const double r0 = fast_rcp(a00);
+  const double l10 = a01 * r0, l20 = a02 * r0, l30 = a03 * r0;
+  const double d1 = fma(-l10, a01, a11);
+  const double m21 = fma(-l10, a02, a12), m31 = fma(-l10, a03, a13);
+  const double r1 = fast_rcp(d1);
+  const double l21 = m21 * r1, l31 = m31 * r1;
+  const double d2 = fma(-l21, m21, fma(-l20, a02, a22));
+  const double m32 = fma(-l21, m31, fma(-l20, a03, a23));
+  const double r2 = fast_rcp(d2);
+  const double l32 = m32 * r2;
+  const double d3 = fma(-l32, m32, fma(-l31, m31, fma(-l30, a03, a33)));
+  // every pivot positive and normal (false for NaN and infinities too)
+  const double tiny = 2.2250738585072014e-308, huge = 1.7976931348623157e308;
+  if (!(a00 >= tiny && d1 >= tiny && d2 >= tiny && d3 >= tiny && a00 <= huge && d1 <= huge && d2 <= huge &&
+        d3 <= huge))
+    return false;
+  const double z0 = b[0];
+  const double z1 = fma(-l10, z0, b[1]);
+  const double z2 = fma(-l21, z1, fma(-l20, z0, b[2]));
+  const double z3 = fma(-l32, z2, fma(-l31, z1, fma(-l30, z0, b[3])));
+  x[3] = z3 * fast_rcp(d3);
+  x[2] = fma(-l32, x[3], z2 * r2);
+  x[1] = fma(-l31, x[3], fma(-l21, x[2], z1 * r1));
+  x[0] = fma(-l30, x[3], fma(-l20, x[2], fma(-l10, x[1], z0 * r0)));
+  return true;
+}
+
+// The step x = -(H + lam diag(J^T J))^-1 J^T r in the parameters themselves
+__device__ __forceinline__ bool gf_solve(const double S[16], const double p[4], bool newton, double lam, double x[4]) {
+  const double b[4] = {-S[GF_R], S[GF_RE], S[GF_RE1], S[GF_RE2]};
+  if (!gf_solve_scaled(S, p, newton, lam, b, x)) return false;
+  const double f = p[3] / p[1];
+  x[2] *= f;
+  x[3] *= f;
   return true;
 }
 
@@ -424,56 +442,43 @@ __device__ bool gf_solve(const double S[20], bool newton, double lam, double x[4
 // described at k_ccf_fit.
 template <int NPT>
 __device__ soap_rv fit_wave(const double (&y)[NPT], int n_v, double v0, double dv, double p[4],
-                            double S[20]) {
+                            double S[16]) {
   const int lane = threadIdx.x & 63;
-  // start values: max, first argmin, half-depth width
+  // start values: max, first argmin, half-depth width.  The extremes are wave
+  // reductions; sample positions come from ballots, samples by readlane.
   double ymax = -1e308, ymin = 1e308;
-  int kmin = n_v;
 #pragma unroll
   for (int t = 0; t < NPT; ++t) {
-    const int i = lane + 64 * t;
-    if (i < n_v) {
+    if (lane + 64 * t < n_v) {
       ymax = fmax(ymax, y[t]);
-      if (y[t] < ymin) {
-        ymin = y[t];
-        kmin = i;
-      }
+      ymin = fmin(ymin, y[t]);
     }
   }
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    ymax = fmax(ymax, __shfl_xor(ymax, off, 64));
-    const double om = __shfl_xor(ymin, off, 64);
-    const int ok = __shfl_xor(kmin, off, 64);
-    if (om < ymin || (om == ymin && ok < kmin)) {
-      ymin = om;
-      kmin = ok;
-    }
-  }
+  ymax = read_lane(wave_max_f64(ymax), 0);
+  ymin = read_lane(-wave_max_f64(-ymin), 0);
   const double c0 = ymax;
   const double a0 = c0 - ymin;
   const double half = c0 - 0.5 * a0;
-  int first = n_v, last = -1;
+  int kmin = n_v, first = n_v, last = -1;
 #pragma unroll
   for (int t = 0; t < NPT; ++t) {
-    const int i = lane + 64 * t;
-    if (i < n_v && y[t] <= half) {
-      first = min(first, i);
-      last = max(last, i);
+    const bool in = lane + 64 * t < n_v;
+    const unsigned long long at_min = __ballot(in && y[t] == ymin), low = __ballot(in && y[t] <= half);
+    if (at_min && kmin == n_v) kmin = 64 * t + (int)__builtin_ctzll(at_min);
+    if (low) {
+      if (first == n_v) first = 64 * t + (int)__builtin_ctzll(low);
+      last = 64 * t + 63 - (int)__builtin_clzll(low);
     }
-  }
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    first = min(first, __shfl_xor(first, off, 64));
-    last = max(last, __shfl_xor(last, off, 64));
   }
   // sample i of the CCF in every lane (i uniform, 0 <= i < n_v)
   auto at = [&](int i) {
-    double v = y[0];
+    double v = read_lane(y[0], i & 63);
 #pragma unroll
-    for (int t = 1; t < NPT; ++t)
-      if ((i >> 6) == t) v = y[t];
-    return __shfl(v, i & 63, 64);
+    for (int t = 1; t < NPT; ++t) {
+      const double w = read_lane(y[t], i & 63);
+      v = (i >> 6) == t ? w : v;
+    }
+    return v;
   };
   // half-depth crossings interpolated between samples, and the minimum's
   // position from the parabola through it and its neighbours
@@ -519,8 +524,8 @@ __device__ soap_rv fit_wave(const double (&y)[NPT], int n_v, double v0, double d
     res.status = 1;
     for (; it < 100; ++it) {
       double x[4];
-      double Sn[20];
-      bool ok = gf_solve(S, true, lam, x) || gf_solve(S, false, lam, x);
+      double Sn[16];
+      bool ok = gf_solve(S, p, true, lam, x) || gf_solve(S, p, false, lam, x);
       bool tiny = false;
       if (ok) {
         const double sig = fabs(p[3]);
@@ -540,7 +545,7 @@ __device__ soap_rv fit_wave(const double (&y)[NPT], int n_v, double v0, double d
         if (Sn[0] <= S[0]) {
           const double dchi = S[0] - Sn[0];
           for (int q = 0; q < 4; ++q) p[q] = pn[q];
-          for (int q = 0; q < 20; ++q) S[q] = Sn[q];
+          for (int q = 0; q < 16; ++q) S[q] = Sn[q];
           ++accepted;
           lam = (lam > 1e-9) ? lam * 0.1 : 0.0;
           const double sgn = fabs(p[3]);
@@ -569,11 +574,14 @@ __device__ soap_rv fit_wave(const double (&y)[NPT], int n_v, double v0, double d
         // ever accepted) the fit failed.
         bool conv = false;
         double xn[4];
-        if (accepted > 0 && (gf_solve(S, true, 0.0, xn) || gf_solve(S, false, 0.0, xn))) {
+        if (accepted > 0 && (gf_solve(S, p, true, 0.0, xn) || gf_solve(S, p, false, 0.0, xn))) {
           const double sg = fabs(p[3]);
           const bool small = fabs(xn[0]) <= 1e-7 * fabs(p[0]) && fabs(xn[1]) <= 1e-7 * fabs(p[1]) &&
                              fabs(xn[2]) <= 1e-7 * sg && fabs(xn[3]) <= 1e-7 * sg;
-          const double dec = -0.5 * (S[1] * xn[0] + S[2] * xn[1] + S[3] * xn[2] + S[4] * xn[3]);
+          // J^T r . x, with J = (1, -e, -s e q, -s e q^2), s = amp / sigma
+          const double s = p[1] / p[3];
+          const double dec =
+              -0.5 * (S[GF_R] * xn[0] - S[GF_RE] * xn[1] - s * (S[GF_RE1] * xn[2] + S[GF_RE2] * xn[3]));
           conv = small || (isfinite(dec) && dec <= 1e-12 * S[0]);
         }
         res.status = conv ? 0 : 3;
@@ -617,6 +625,14 @@ __device__ soap_rv fit_wave(const double (&y)[NPT], int n_v, double v0, double d
 // was accepted and the undamped Newton step there is of rounding size
 // (status 0); otherwise the fit failed (status 3).  A CCF with a non-finite
 // sample or no depth is degenerate (status 2).
+//
+// Bound by the latency of the fit's chain: 100 spectra of 161 velocities and
+// 125 partial rows take 13.5 us, about 5 of them for the sums and 1.2 an
+// iteration (four on the headline).  As 20 sums in two butterflies with a
+// Cholesky solve (square roots and divisions in the chain), extremes by
+// shuffles and a branch per sample: 16.9 us; 4000 spectra, a wave each, 40.4
+// and now 30.1 (170 registers instead of 195: three waves per SIMD); 300
+// spectra of 401 velocities 43.0 and 30.4.
 template <int NPT, typename PT>
 __device__ __forceinline__ void fit_block(int n_lb, int64_t n_spec, int n_v, double v0, double dv,
                                           const PT* __restrict__ part, double* __restrict__ ccf, int fit,
@@ -673,7 +689,7 @@ __device__ __forceinline__ void fit_block(int n_lb, int64_t n_spec, int n_v, dou
     if (i < n_v) ccf[s * n_v + i] = a;
   }
   if (!fit) return;
-  double p[4], S[20];
+  double p[4], S[16];
   const soap_rv res = fit_wave(y, n_v, v0, dv, p, S);
   if (lane == 0) out[s] = res;
 }
@@ -732,7 +748,7 @@ __device__ __forceinline__ void fit_one_wave(int n_lb, int64_t n_spec, int n_v, 
     if (i < n_v) ccf[s * n_v + i] = a;
   }
   if (!fit) return;
-  double p[4], S[20];
+  double p[4], S[16];
   const soap_rv res = fit_wave(y, n_v, v0, dv, p, S);
   if (lane == 0) out[s] = res;
 }
@@ -1027,7 +1043,8 @@ constexpr int sg_rows_in_flight() {
 //     coef[i][k] basis[k] (double, increasing k: the same sums as
 //     k_ccf_linear), SS = sg_samples samples per wave sharing every basis
 //     row loaded;
-//   k_sg_fit: its Gaussian fit (fit_wave), one wave per sample, and the RV
+//   k_sg_fit: its Gaussian fit (fit_wave), one wave per sample (issue-bound:
+//     88 us per 1e4 samples with the fit's former 20 sums, 64 now), and the RV
 //     sensitivity g = J H^-1 e_mu at the fit: the fitted parameters move by
 //     dp = H^-1 J^T dy for a CCF change dy (H the Hessian of chi^2 / 2 at the
 //     fit, J the model Jacobian), so dRV = g . dy;
@@ -1117,32 +1134,24 @@ __global__ void __launch_bounds__(64) k_sg_fit(int64_t n, int n_v, double v0, do
   double y[NPT];
 #pragma unroll
   for (int t = 0; t < NPT; ++t) y[t] = Y[i * n_v + min(lane + 64 * t, n_v - 1)];
-  double p[4], S[20];
+  double p[4], S[16];
   soap_rv res = fit_wave(y, n_v, v0, dv, p, S);
   bool bad = res.status != 0 || !row_ok;
   double z[4] = {0.0, 0.0, 0.0, 0.0};
   if (!bad) {
-    // z = H^-1 e_mu (full Hessian; J^T J where that is not positive definite)
-    double Sz[20];
-#pragma unroll
-    for (int q = 0; q < 20; ++q) Sz[q] = S[q];
-    Sz[1] = 0.0;
-    Sz[2] = 0.0;
-    Sz[3] = -1.0;  // gf_solve solves A x = -S[1..4]
-    Sz[4] = 0.0;
-    if (!(gf_solve(Sz, true, 0.0, z) || gf_solve(Sz, false, 0.0, z))) bad = true;
+    // z = H^-1 e_mu (full Hessian; J^T J where that is not positive definite),
+    // for the scaled centre and width (z[2], z[3] times amp / sigma)
+    const double b[4] = {0.0, 0.0, p[3] / p[1], 0.0};
+    if (!(gf_solve_scaled(S, p, true, 0.0, b, z) || gf_solve_scaled(S, p, false, 0.0, b, z))) bad = true;
   }
   const double is = 1.0 / p[3];
-  const double is2 = is * is;
 #pragma unroll
   for (int t = 0; t < NPT; ++t) {
     const int v = lane + 64 * t;
     if (v < n_v) {
-      const double d = v0 + dv * v - p[2];
-      const double zz = d * d * is2;
-      const double e = exp(-0.5 * zz);
-      const double ae = p[1] * e;
-      G[i * n_v + v] = bad ? 0.0 : z[0] - e * z[1] - ae * d * is2 * z[2] - ae * zz * is * z[3];
+      const double q = (v0 + dv * v - p[2]) * is;
+      const double e = exp(-0.5 * q * q);
+      G[i * n_v + v] = bad ? 0.0 : z[0] - e * (z[1] + q * (z[2] + q * z[3]));
     }
   }
   if (lane == 0) {

@@ -37,13 +37,49 @@ __device__ __forceinline__ double wave_sum_f64(double v) {
   return ((read_lane(v, 0) + read_lane(v, 16)) + read_lane(v, 32)) + read_lane(v, 48);
 }
 
+// Sum / maximum of a value over the four 16-lane rows, for every lane:
+// exchanges with the row beside (rows 0 and 1, 2 and 3) and then with the other
+// half of the wave, by register swaps (no LDS).
+__device__ __forceinline__ void swap_rows(double v, double* a, double* b) {
+  const auto lo = __builtin_amdgcn_permlane16_swap(__double2loint(v), __double2loint(v), false, false);
+  const auto hi = __builtin_amdgcn_permlane16_swap(__double2hiint(v), __double2hiint(v), false, false);
+  *a = __hiloint2double(hi[0], lo[0]);
+  *b = __hiloint2double(hi[1], lo[1]);
+}
+__device__ __forceinline__ void swap_halves(double v, double* a, double* b) {
+  const auto lo = __builtin_amdgcn_permlane32_swap(__double2loint(v), __double2loint(v), false, false);
+  const auto hi = __builtin_amdgcn_permlane32_swap(__double2hiint(v), __double2hiint(v), false, false);
+  *a = __hiloint2double(hi[0], lo[0]);
+  *b = __hiloint2double(hi[1], lo[1]);
+}
+__device__ __forceinline__ double rows_sum_f64(double v) {
+  double a, b;
+  swap_rows(v, &a, &b);
+  v = a + b;
+  swap_halves(v, &a, &b);
+  return a + b;
+}
+
+// Largest value over the 64 lanes of a wave (all lanes active), NaNs skipped
+__device__ __forceinline__ double wave_max_f64(double v) {
+  v = fmax(v, dpp_f64<DPP_PAIR>(v));
+  v = fmax(v, dpp_f64<DPP_QUAD>(v));
+  v = fmax(v, dpp_f64<DPP_HALF_MIRROR>(v));
+  v = fmax(v, dpp_f64<DPP_MIRROR>(v));
+  double a, b;
+  swap_rows(v, &a, &b);
+  v = fmax(a, b);
+  swap_halves(v, &a, &b);
+  return fmax(a, b);
+}
+
 // Sum v[0..15] over the 64 lanes of a wave (all lanes active); lane l ends
 // with the total of slot l & 15.  The four in-row levels are transposed
 // butterflies on DPP exchanges, partner lanes differing in one lane-index
 // bit within the row (row mirror: bit 3, half-row mirror: bit 2, quad swaps:
 // bits 1 and 0); each level sends half of the remaining slots to the
 // partner and keeps the other half.  The last value is then added over the
-// four rows with two shuffles.  The order of additions is fixed.
+// four rows by register swaps.  The order of additions is fixed.
 __device__ __forceinline__ double butterfly16_rows(double (&v)[16], int lane) {
   const bool b3 = lane & 8, b2 = lane & 4, b1 = lane & 2, b0 = lane & 1;
 #pragma unroll
@@ -69,10 +105,7 @@ __device__ __forceinline__ double butterfly16_rows(double (&v)[16], int lane) {
     const double keep = b0 ? v[1] : v[0];
     v[0] = keep + dpp_f64<DPP_PAIR>(send);
   }
-  double s = v[0];
-  s += __shfl_xor(s, 16, 64);
-  s += __shfl_xor(s, 32, 64);
-  return s;
+  return rows_sum_f64(v[0]);
 }
 
 // OR over the 64 lanes of a wave (all lanes active): in-row swaps by DPP
