@@ -70,6 +70,8 @@ struct ApplyArgs {
   const unsigned char* wins;
   const int* nvg;
   T* out;
+  unsigned* started;  // host word that takes seq when the kernel begins (null: none)
+  unsigned seq;
 };
 
 __device__ __forceinline__ int uni(int x) { return __builtin_amdgcn_readfirstlane(x); }
@@ -440,6 +442,9 @@ constexpr int apply_occupancy() {
 template <typename T, int PC, int MODE, int DEP>
 __global__ void __launch_bounds__(APPLY_WAVES * 64, (apply_occupancy<T, PC, MODE, DEP>())) k_apply(ApplyArgs<T> A) {
   __shared__ __align__(16) unsigned char lds[APPLY_WAVES * DEP * Slot<T, PC, MODE>::BYTES];
+  // what was enqueued before this launch is done
+  if (A.started && blockIdx.x == 0 && threadIdx.x == 0)
+    __hip_atomic_store(A.started, A.seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   int tile, chunk;
   if (!map_item(A, blockIdx.x, &tile, &chunk)) return;
   apply_item<T, PC, MODE, DEP>(A, tile, chunk, lds);
@@ -495,8 +500,10 @@ ApplyArgs<T> make_args(soap_ctx* c, const Plan& pl, const void* win, const int* 
 
 template <typename T, int PC>
 hipError_t launch_apply_pc(soap_ctx* c, const Plan& pl, const void* d_win, const int* d_nvg, void* d_flux, int depth,
-                           int order, hipStream_t st) {
-  const ApplyArgs<T> A = make_args<T, PC>(c, pl, d_win, d_nvg, d_flux, order);
+                           int order, hipStream_t st, unsigned* started, unsigned seq) {
+  ApplyArgs<T> A = make_args<T, PC>(c, pl, d_win, d_nvg, d_flux, order);
+  A.started = started;
+  A.seq = seq;
   switch (apply_table_mode(c, pl)) {
     case MODE_SPLIT: return launch_mode<T, PC, MODE_SPLIT>(A, depth, st);
     case MODE_PAIRED: return launch_mode<T, PC, MODE_PAIRED>(A, depth, st);
@@ -506,19 +513,26 @@ hipError_t launch_apply_pc(soap_ctx* c, const Plan& pl, const void* d_win, const
 
 }  // namespace
 
-hipError_t launch_apply(soap_ctx* c, const Plan& pl, const void* d_win, const int* d_nvg, void* d_flux) {
-  return launch_apply_shape(c, pl, d_win, d_nvg, d_flux, c->tune_depth, c->tune_order, c->stream);
+namespace {
+
+hipError_t launch_apply_any(soap_ctx* c, const Plan& pl, const void* d_win, const int* d_nvg, void* d_flux, int depth,
+                            int order, hipStream_t st, unsigned* started, unsigned seq) {
+  const bool fp32 = c->prec == SOAP_PREC_FP32;
+  if (!pc_valid(fp32, pl.pc)) return hipErrorInvalidValue;
+  auto* f = fp32 ? (pl.pc == PC_F32_WIDE ? launch_apply_pc<float, PC_F32_WIDE> : launch_apply_pc<float, PC_F32>)
+                 : (pl.pc == PC_F64_WIDE ? launch_apply_pc<double, PC_F64_WIDE> : launch_apply_pc<double, PC_F64>);
+  return f(c, pl, d_win, d_nvg, d_flux, depth, order, st, started, seq);
+}
+
+}  // namespace
+
+hipError_t launch_apply(soap_ctx* c, const Plan& pl, const void* d_win, const int* d_nvg, void* d_flux, unsigned seq) {
+  return launch_apply_any(c, pl, d_win, d_nvg, d_flux, c->tune_depth, c->tune_order, c->stream, c->started, seq);
 }
 
 hipError_t launch_apply_shape(soap_ctx* c, const Plan& pl, const void* d_win, const int* d_nvg, void* d_flux,
                               int depth, int order, hipStream_t st) {
-  const bool fp32 = c->prec == SOAP_PREC_FP32;
-  if (!pc_valid(fp32, pl.pc)) return hipErrorInvalidValue;
-  if (fp32)
-    return pl.pc == PC_F32_WIDE ? launch_apply_pc<float, PC_F32_WIDE>(c, pl, d_win, d_nvg, d_flux, depth, order, st)
-                                : launch_apply_pc<float, PC_F32>(c, pl, d_win, d_nvg, d_flux, depth, order, st);
-  return pl.pc == PC_F64_WIDE ? launch_apply_pc<double, PC_F64_WIDE>(c, pl, d_win, d_nvg, d_flux, depth, order, st)
-                              : launch_apply_pc<double, PC_F64>(c, pl, d_win, d_nvg, d_flux, depth, order, st);
+  return launch_apply_any(c, pl, d_win, d_nvg, d_flux, depth, order, st, nullptr, 0);
 }
 
 // ---- batched shift-and-sum over many configurations ------------------------

@@ -8,6 +8,7 @@
 #include <rocprofiler-sdk-roctx/roctx.h>
 
 #include <algorithm>
+#include <chrono>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -158,18 +159,16 @@ void destroy_ctx(soap_ctx* c) {
   for (auto& S : c->prep) {
     soap::Workspace* pw[] = {&S.par, &S.Kfx, &S.K, &S.mask64, &S.vg, &S.nvg};
     for (auto* w : pw) free_ws(*w);
-    if (S.prep_done) (void)hipEventDestroy(S.prep_done);
-    if (S.apply_done) (void)hipEventDestroy(S.apply_done);
+    if (S.done) (void)hipEventDestroy(S.done);
   }
   if (c->side) (void)hipStreamDestroy(c->side);
   for (auto& p : c->pending) {
     (void)hipEventDestroy(p.a);
     (void)hipEventDestroy(p.b);
   }
-  for (int k = 0; k < soap_ctx::NSLOT; ++k) {
-    if (c->slot[k]) (void)hipHostFree(c->slot[k]);
-    if (c->slot_done[k]) (void)hipEventDestroy(c->slot_done[k]);
-  }
+  for (void* p : c->slot)
+    if (p) (void)hipHostFree(p);
+  if (c->started) (void)hipHostFree(c->started);
   if (c->pinned) (void)hipHostFree(c->pinned);
   if (c->pinned_done) (void)hipEventDestroy(c->pinned_done);
   delete c;
@@ -320,13 +319,6 @@ soap_status init_impl(const soap_star_desc* d, soap_ctx* c) {
     }
   }
   HIP_TRY(hipEventCreateWithFlags(&c->pinned_done, hipEventDisableTiming));
-  for (int k = 0; k < soap_ctx::NSLOT; ++k) HIP_TRY(hipEventCreateWithFlags(&c->slot_done[k], hipEventDisableTiming));
-  HIP_TRY(hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking));
-  for (auto& S : c->prep) {
-    HIP_TRY(hipEventCreateWithFlags(&S.prep_done, hipEventDisableTiming));
-    HIP_TRY(hipEventCreateWithFlags(&S.apply_done, hipEventDisableTiming));
-  }
-
   HIP_TRY(soap::launch_pad(c));
   HIP_TRY(soap::launch_geom(c));
   if (c->cmode == SOAP_CONTRAST_PLANCK) HIP_TRY(soap::launch_contrast(c));
@@ -498,12 +490,71 @@ SOAP_API soap_status soap_quiet_spectrum(soap_ctx* c, void* out, int32_t out_on_
 
 namespace {
 
+// Waits until the apply kernel of call `seq` has begun: whatever was enqueued
+// before it is done.  The kernel writes its call's number to a host word; an
+// event would put a marker between the kernels of the stream, 5 to 10 us each.
+// An idle stream ends the wait too (a call whose apply was never launched).
+hipError_t wait_started(soap_ctx* c, unsigned seq) {
+  auto passed = [&] { return (int)(__atomic_load_n(c->started, __ATOMIC_ACQUIRE) - seq) >= 0; };
+  for (;;) {
+    const auto t0 = std::chrono::steady_clock::now();
+    do {
+      for (int i = 0; i < 32; ++i) {
+        if (passed()) return hipSuccess;
+        __builtin_ia32_pause();
+      }
+    } while (std::chrono::steady_clock::now() - t0 < std::chrono::milliseconds(2));
+    const hipError_t e = hipStreamQuery(c->stream);
+    if (e != hipErrorNotReady) return e;
+  }
+}
+
+// The table set of the next call.  Set 0 runs on the context stream.  When the
+// caller is ahead of the device (the last call's apply has not begun) the
+// table kernels, short and far from filling the chip, run beside what is
+// pending instead: a 100-phase series enqueued over and over takes 76 us a
+// call so, 100 on one stream.
+// Otherwise the second queue only adds its hand-over and host time: the same
+// series with a wait after each call, 133 us with the second queue, 112 us on
+// one stream.
+hipError_t choose_prep(soap_ctx* c, int* sidx) {
+  hipError_t e;
+  if (c->tables_open) {  // the last call stopped half-way: nothing of it may run on
+    if ((e = hipStreamSynchronize(c->stream)) != hipSuccess) return e;
+    if (c->side && (e = hipStreamSynchronize(c->side)) != hipSuccess) return e;
+    c->tables_open = false;
+  }
+  if (!c->started) {
+    if ((e = hipHostMalloc(reinterpret_cast<void**>(&c->started), 64, hipHostMallocMapped | hipHostMallocCoherent)) !=
+        hipSuccess)
+      return e;
+    *c->started = c->call_seq;
+  }
+  *sidx = 0;
+  if (__atomic_load_n(c->started, __ATOMIC_ACQUIRE) == c->call_seq) return hipSuccess;
+  if (!c->side && (e = hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking)) != hipSuccess) return e;
+  soap_ctx::Prep& S = c->prep[c->prep_next];
+  if (!S.done && (e = hipEventCreateWithFlags(&S.done, hipEventDisableTiming)) != hipSuccess) return e;
+  // the set's last apply is over once a later one has begun
+  if (S.used && (e = wait_started(c, S.seq + 1)) != hipSuccess) return e;
+  *sidx = c->prep_next;
+  c->prep_next = c->prep_next % (soap_ctx::NPREP - 1) + 1;
+  return hipSuccess;
+}
+
 // Shared body of soap_active_spectra and soap_active_spectra_jobs.  With
 // pj_host == NULL every phase uses regions[0 .. n_regions); otherwise phase
 // p uses pj_host[p] = (first region, count).  Arguments are validated.
 soap_status active_impl(soap_ctx* c, const soap_region* regions, int32_t n_regions, int max_reg,
                         const int2* pj_host, const double* phases, int32_t n_phases, int32_t effect, void* flux,
                         int32_t flux_on_device) {
+  // a captured call would replay from a parameter slot that later calls rewrite
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  HIP_TRY(hipStreamIsCapturing(c->stream, &cap));
+  if (cap != hipStreamCaptureStatusNone) {
+    setf(c->err, "the context's stream is being captured: synthesis calls cannot be replayed (use a batch)");
+    return SOAP_ERR_HIP;
+  }
   // per-call plan: paired tables when every active weight equals its
   // removal weight (chromatic contrast, the convective effect, or unit
   // scalar contrasts); otherwise split tables with explicit removal rows
@@ -536,11 +587,11 @@ soap_status active_impl(soap_ctx* c, const soap_region* regions, int32_t n_regio
   const size_t reg_bytes = 256 * ((sizeof(soap::Region) * n_reg_slots + 255) / 256);
   const size_t ph_bytes = 256 * ((sizeof(double) * n_phases + 255) / 256);
   const size_t par_bytes = reg_bytes + ph_bytes + (pj_host ? sizeof(int2) * n_phases : 0);
-  // this call's table set; its kernels run on the side stream after the
-  // apply that last read the set (two calls ago) is done
-  const int sidx = c->prep_next;
-  soap_ctx::PrepSet& S = c->prep[sidx];
-  c->prep_next ^= 1;
+  const unsigned seq = c->call_seq + 1;
+  int sidx = 0;
+  HIP_TRY(choose_prep(c, &sidx));
+  soap_ctx::Prep& S = c->prep[sidx];
+  const hipStream_t st = sidx ? c->side : c->stream;
   const size_t reg_dev = reg_bytes;
   const size_t pj_dev = 256 * ((sizeof(int2) * (size_t)n_phases + 255) / 256);
   const size_t cen_dev = 256 * ((sizeof(double4) * (size_t)n_phases * std::max(1, max_reg) + 255) / 256);
@@ -555,20 +606,19 @@ soap_status active_impl(soap_ctx* c, const soap_region* regions, int32_t n_regio
   if (regrow) {
     // buffers are replaced only with both streams idle
     HIP_TRY(hipStreamSynchronize(c->stream));
-    HIP_TRY(hipStreamSynchronize(c->side));
+    if (c->side) HIP_TRY(hipStreamSynchronize(c->side));
     HIP_TRY(grow(S.par, par_dev));
     HIP_TRY(grow(S.K, k_bytes));
     HIP_TRY(grow(S.mask64, m_bytes));
     HIP_TRY(grow(S.vg, vg_bytes));
     HIP_TRY(grow(S.nvg, nvg_bytes));
   }
-  HIP_TRY(hipStreamWaitEvent(c->side, S.apply_done, 0));
   if (S.Kfx.bytes < kfx_bytes || S.kfx_dirty) {
     // fixed-point tap accumulators: zero when allocated; every call that
     // accumulates also clears them, so they are zeroed again only after an
     // interrupted call
     HIP_TRY(grow(S.Kfx, kfx_bytes));
-    HIP_TRY(hipMemsetAsync(S.Kfx.ptr, 0, S.Kfx.bytes, c->side));
+    HIP_TRY(hipMemsetAsync(S.Kfx.ptr, 0, S.Kfx.bytes, st));
     S.kfx_dirty = false;
   }
   const size_t out_bytes = (size_t)n_phases * c->P * c->esize;
@@ -591,9 +641,8 @@ soap_status active_impl(soap_ctx* c, const soap_region* regions, int32_t n_regio
     }
     dsyn = c->ws_lsf.ptr;
   }
-  const int k = c->slot_next;
-  c->slot_next = (k + 1) % soap_ctx::NSLOT;
-  HIP_TRY(hipEventSynchronize(c->slot_done[k]));
+  const int k = (int)(seq % soap_ctx::NSLOT);
+  HIP_TRY(wait_started(c, seq - soap_ctx::NSLOT));
   if (c->slot_bytes[k] < par_bytes) {
     if (c->slot[k]) HIP_TRY(hipHostFree(c->slot[k]));
     c->slot[k] = nullptr;
@@ -616,11 +665,10 @@ soap_status active_impl(soap_ctx* c, const soap_region* regions, int32_t n_regio
   if (pj_host) std::memcpy(host + reg_bytes + ph_bytes, pj_host, sizeof(int2) * n_phases);
   void* dev_view = nullptr;
   HIP_TRY(hipHostGetDevicePointer(&dev_view, c->slot[k], 0));
-  const soap::Region* d_reg = static_cast<const soap::Region*>(dev_view);
-  const double* d_ph = reinterpret_cast<const double*>(static_cast<const unsigned char*>(dev_view) + reg_bytes);
-  const int2* d_pj =
-      pj_host ? reinterpret_cast<const int2*>(static_cast<const unsigned char*>(dev_view) + reg_bytes + ph_bytes)
-              : nullptr;
+  const unsigned char* dev_par = static_cast<const unsigned char*>(dev_view);
+  const soap::Region* d_reg = reinterpret_cast<const soap::Region*>(dev_par);
+  const double* d_ph = reinterpret_cast<const double*>(dev_par + reg_bytes);
+  const int2* d_pj = pj_host ? reinterpret_cast<const int2*>(dev_par + reg_bytes + ph_bytes) : nullptr;
 
   soap::WeightsOut wo;
   wo.reg = static_cast<soap::Region*>(S.par.ptr);
@@ -632,33 +680,38 @@ soap_status active_impl(soap_ctx* c, const soap_region* regions, int32_t n_regio
   wo.mask = static_cast<unsigned long long*>(S.mask64.ptr);
   wo.wins = static_cast<unsigned char*>(S.vg.ptr);
   wo.nvg = static_cast<int*>(S.nvg.ptr);
+  c->tables_open = true;
+  c->call_seq = seq;
   S.kfx_dirty = true;
   {
-    StageTimer t(c, ST_WEIGHTS, c->side);
-    HIP_TRY(soap::launch_weights(c, pl, d_reg, n_regions, std::max(1, max_reg), d_ph, d_pj, wo, c->side));
+    StageTimer t(c, ST_WEIGHTS, st);
+    HIP_TRY(soap::launch_weights(c, pl, d_reg, n_regions, std::max(1, max_reg), d_ph, d_pj, wo, st));
     t.done();
   }
-  HIP_TRY(hipEventRecord(c->slot_done[k], c->side));
   {
-    StageTimer t(c, ST_COMPACT, c->side);
-    HIP_TRY(soap::launch_finish(c, pl, wo, c->side));
+    StageTimer t(c, ST_COMPACT, st);
+    HIP_TRY(soap::launch_finish(c, pl, wo, st));
     t.done();
   }
   S.kfx_dirty = false;
-  HIP_TRY(hipEventRecord(S.prep_done, c->side));
-  HIP_TRY(hipStreamWaitEvent(c->stream, S.prep_done, 0));
+  if (sidx) {
+    HIP_TRY(hipEventRecord(S.done, st));
+    HIP_TRY(hipStreamWaitEvent(c->stream, S.done, 0));
+  }
   {
     StageTimer t(c, ST_APPLY);
-    HIP_TRY(soap::launch_apply(c, pl, S.vg.ptr, static_cast<const int*>(S.nvg.ptr), dsyn));
+    HIP_TRY(soap::launch_apply(c, pl, S.vg.ptr, static_cast<const int*>(S.nvg.ptr), dsyn, seq));
     t.done();
   }
-  HIP_TRY(hipEventRecord(S.apply_done, c->stream));
+  c->tables_open = false;
+  S.seq = seq;
+  S.used = true;
+  c->last_prep = sidx;
   if (lower) {
     StageTimer t(c, ST_LSF);
     HIP_TRY(soap::launch_lsf(c, c->lsf, dsyn, dflux, n_phases, c->stream));
     t.done();
   }
-  c->last_prep = sidx;
   c->active_calls++;
   c->last_phases = n_phases;
   c->last_effect = effect;
@@ -1047,7 +1100,7 @@ SOAP_API soap_status soap_surrogate_rv(soap_ctx* c, const float* coef, const flo
 
 SOAP_API soap_status soap_profile_enable(soap_ctx* c, int32_t on) {
   if (!c) return SOAP_ERR_ARG;
-  HIP_TRY(hipStreamSynchronize(c->side));
+  if (c->side) HIP_TRY(hipStreamSynchronize(c->side));
   HIP_TRY(hipStreamSynchronize(c->stream));
   for (auto& p : c->pending) {
     (void)hipEventDestroy(p.a);
@@ -1064,7 +1117,7 @@ SOAP_API soap_status soap_profile_read(soap_ctx* c, soap_profile* out) {
   if (!c) return SOAP_ERR_ARG;
   std::string& err = c->err;
   ARG_CHECK(out != nullptr, "out is NULL");
-  HIP_TRY(hipStreamSynchronize(c->side));
+  if (c->side) HIP_TRY(hipStreamSynchronize(c->side));
   HIP_TRY(hipStreamSynchronize(c->stream));
   for (auto& p : c->pending) {
     float ms = 0.f;
@@ -1091,7 +1144,7 @@ SOAP_API soap_status soap_profile_read(soap_ctx* c, soap_profile* out) {
     const size_t wb = (size_t)soap::win_bytes(c->last_pc, (int)c->esize);
     std::vector<int> nvg(n_chunks);
     std::vector<unsigned char> vg((size_t)n_chunks * c->last_vg_cap * wb);
-    const soap_ctx::PrepSet& S = c->prep[c->last_prep];
+    const soap_ctx::Prep& S = c->prep[c->last_prep];
     HIP_TRY(hipMemcpy(nvg.data(), S.nvg.ptr, sizeof(int) * n_chunks, hipMemcpyDeviceToHost));
     HIP_TRY(hipMemcpy(vg.data(), S.vg.ptr, vg.size(), hipMemcpyDeviceToHost));
     std::vector<char> src(3 * c->B, 0), con(3 * c->B, 0);
@@ -1151,7 +1204,7 @@ SOAP_API soap_status soap_profile_read(soap_ctx* c, soap_profile* out) {
 
 SOAP_API soap_status soap_sync(soap_ctx* c) {
   if (!c) return SOAP_ERR_ARG;
-  HIP_TRY(hipStreamSynchronize(c->side));
+  if (c->side) HIP_TRY(hipStreamSynchronize(c->side));
   HIP_TRY(hipStreamSynchronize(c->stream));
   return SOAP_OK;
 }

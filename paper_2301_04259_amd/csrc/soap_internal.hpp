@@ -191,23 +191,27 @@ struct soap_ctx {
 
   // per-call workspace (grown on demand, freed by soap_destroy)
   // Per-call tables (region parameters, tap accumulators and taps, window
-  // records), in two sets used by alternate calls.  Their kernels run on
-  // the side stream, so the tables of the next call are built while the
-  // context stream still runs the previous call's later stages.
-  struct PrepSet {
+  // records).  Table kernels run on the context stream, in set 0, or, when
+  // the caller is ahead of the device, on the side stream, in the next of the
+  // other sets, beside what is running; the context stream then waits for
+  // them before the apply.
+  struct Prep {
     soap::Workspace par;     // regions, per-phase region centres and bounding boxes
     soap::Workspace Kfx;     // [n_phases][G][J] fixed-point tap accumulators (kept zero)
     soap::Workspace K;       // [n_phases][G][J] double
     soap::Workspace mask64;  // [n_phases][G] bitmask of nonzero offsets
     soap::Workspace vg;      // [n_chunks][vg_cap] window records (win_bytes(pc) each)
     soap::Workspace nvg;     // [n_chunks] int
-    bool kfx_dirty = false;  // a call stopped between accumulation and clearing
-    hipEvent_t prep_done = nullptr;   // side stream: this set's tables are built
-    hipEvent_t apply_done = nullptr;  // context stream: the apply that read them is done
+    hipEvent_t done = nullptr;  // side sets: recorded on the side stream after the tables
+    unsigned seq = 0;           // call that last used the set
+    bool used = false;          // by any call
+    bool kfx_dirty = false;     // a call stopped between accumulation and clearing
   };
-  PrepSet prep[2];
-  int prep_next = 0, last_prep = 0;
-  hipStream_t side = nullptr;  // stream of the per-call table kernels
+  static constexpr int NPREP = 4;  // set 0, and three for the side stream
+  Prep prep[NPREP];
+  int prep_next = 1, last_prep = 0;
+  hipStream_t side = nullptr;  // created by the first call that uses it
+  bool tables_open = false;    // a call stopped between its table kernels and its apply
   soap::Workspace ws_flux;     // host-output staging for fluxes
   soap::Workspace ws_ccf;      // partial CCFs
   soap::Workspace ws_ccfout;   // [n_spec][n_v] double
@@ -217,14 +221,15 @@ struct soap_ctx {
   void* pinned = nullptr;      // host staging for the mask upload
   size_t pinned_bytes = 0;
   hipEvent_t pinned_done = nullptr;
-  // ring of pinned parameter slots (regions + phases) read in place by the
-  // weights kernel; a slot is rewritten only after the kernel that read it
-  // has finished
+  // ring of pinned parameter slots (regions + phases) that the parameter kernel
+  // reads in place.  Calls are numbered; a call's apply kernel writes the
+  // number to `started` (pinned) when it begins, and with that its parameter
+  // slot and the table sets of the calls before it are free
   static constexpr int NSLOT = 4;
   void* slot[NSLOT] = {nullptr, nullptr, nullptr, nullptr};
   size_t slot_bytes[NSLOT] = {0, 0, 0, 0};
-  hipEvent_t slot_done[NSLOT] = {nullptr, nullptr, nullptr, nullptr};
-  int slot_next = 0;
+  unsigned call_seq = 0;
+  unsigned* started = nullptr;
 
   // profiling (soap_profile_enable / soap_profile_read)
   bool prof = false;
@@ -264,7 +269,7 @@ struct Plan {
   int effect = 0;
   int paired = 0;   // 1: one tap table per active (type, bin); removal implied
   int G = 0;        // groups per table: 2B (paired) or 3B (split)
-  int n_slabs = 0;
+  int n_slabs = 0;  // slabs of SLAB_COLS disk columns (batch work lists)
   int n_chunks = 0;
   int vg_cap = 0;   // virtual groups per chunk
   int pc = 0;       // phases per chunk of the tables
@@ -294,7 +299,7 @@ hipError_t launch_finish(soap_ctx* c, const Plan& pl, const WeightsOut& o, hipSt
 // Arguments of the table kernels for one configuration (region parameters,
 // weights, tap lists); the batched forms take an array of them.
 struct ParamsArgs {
-  int N, n_reg, max_reg, n_ph;
+  int N, n_reg, max_reg, n_ph, lanes;  // lanes: threads per phase (params_lanes)
   double incl, diff_rot;
   const Region* reg;
   const double* phases;
@@ -305,7 +310,7 @@ struct ParamsArgs {
   int4* box;
 };
 struct WeightsArgs {
-  int N, B, J, jmin, G, paired, n_slabs, effect, n_reg_all, max_reg;
+  int N, B, J, jmin, G, paired, n_parts, effect, n_reg_all, max_reg;
   double u1, u2;
   const double* mu_b;
   const int* col_c;
@@ -364,7 +369,7 @@ hipError_t table_batch_launch(const TableBatch& tb, hipStream_t st);
 // paired tables without a contrast (D = A - S_q), and with one (D = C A - S_q)
 enum { MODE_SPLIT = 0, MODE_PAIRED = 1, MODE_CONTRAST = 2 };
 int apply_table_mode(const soap_ctx* c, const Plan& pl);
-hipError_t launch_apply(soap_ctx* c, const Plan& pl, const void* d_win, const int* d_nvg, void* d_flux);
+hipError_t launch_apply(soap_ctx* c, const Plan& pl, const void* d_win, const int* d_nvg, void* d_flux, unsigned seq);
 // apply with an explicit shape (threads per block, windows staged per LDS
 // pass) on stream st
 hipError_t launch_apply_shape(soap_ctx* c, const Plan& pl, const void* d_win, const int* d_nvg, void* d_flux,

@@ -143,7 +143,7 @@ SOAP_API soap_status soap_autotune(soap_ctx* c, const soap_region* regions, int3
   // key: the work's shape, with the window count of the default layout
   long long tot = 0;
   {
-    soap_ctx::PrepSet& S = c->prep[c->last_prep];
+    soap_ctx::Prep& S = c->prep[c->last_prep];
     std::vector<int> nvg(pl.n_chunks);
     if (hipMemcpy(nvg.data(), S.nvg.ptr, sizeof(int) * pl.n_chunks, hipMemcpyDeviceToHost) != hipSuccess)
       return fail(SOAP_ERR_HIP, "autotune: reading window counts failed");
@@ -184,7 +184,7 @@ SOAP_API soap_status soap_autotune(soap_ctx* c, const soap_region* regions, int3
         return fail(st, nullptr);
       }
     }
-    soap_ctx::PrepSet& S = c->prep[c->last_prep];
+    soap_ctx::Prep& S = c->prep[c->last_prep];
     for (int d : kDepths) {
       for (int o : kOrders) {
         for (int r = 0; r < 2; ++r)

@@ -1,6 +1,7 @@
 // Per-phase active-region weights (section 3.3, Algorithm 5).
 //
-// k_weights: one block per (phase, slab of SLAB_COLS disk columns), flattened
+// k_weights: n_parts blocks per phase, each a share of the columns that the
+//   phase's caps reach
 //   1. rotates every region centre to the phase (longitude + 360 deg * phase,
 //      axis tilted by the inclination) and bounds the visible caps;
 //   2. one wave64 per column, one lane per cell: a cell belongs to a region
@@ -95,14 +96,24 @@ __device__ void compact_chunk(const FinishArgs& a, int chunk, const double* Kc, 
   }
   for (int v = threadIdx.x; v < vg_cap; v += blockDim.x) s_gm[v] = 0u;
   __syncthreads();
-  if (threadIdx.x == 0) {
+  if (threadIdx.x < 64) {  // first window of every group: a scan by one wave
     int acc = 0;
-    for (int g = 0; g < G; ++g) {
-      s_base[g] = acc;
-      acc += s_cnt[g];
+    for (int g0 = 0; g0 < G; g0 += 64) {
+      const int g = g0 + threadIdx.x;
+      const int cnt = g < G ? s_cnt[g] : 0;
+      int sum = cnt;
+#pragma unroll
+      for (int off = 1; off < 64; off *= 2) {
+        const int o = __shfl_up(sum, off, 64);
+        if ((int)threadIdx.x >= off) sum += o;
+      }
+      if (g < G) s_base[g] = acc + sum - cnt;
+      acc += __shfl(sum, 63, 64);
     }
-    nvg[chunk] = acc;
-    *s_nv = acc;
+    if (threadIdx.x == 0) {
+      nvg[chunk] = acc;
+      *s_nv = acc;
+    }
   }
   __syncthreads();
   // one thread per (group, window slot, offset)
@@ -174,32 +185,48 @@ __device__ __forceinline__ void finish_block(const FinishArgs& a, int chunk, uns
   unsigned long long* maskc =
       IN_LDS ? reinterpret_cast<unsigned long long*>(fin_lds + (size_t)PC * GJ * sizeof(double)) : mask + (int64_t)p0 * G;
   int* sm = reinterpret_cast<int*>(fin_lds + (IN_LDS ? (size_t)PC * (GJ + G) * sizeof(double) : 0));
-  // eight accumulators per thread and round, loaded together
-  for (int t0 = threadIdx.x; t0 < n; t0 += 8 * FINISH_THREADS) {
-    unsigned long long v[8];
+  if (IN_LDS) {
+    for (int t = threadIdx.x; t < np * G; t += FINISH_THREADS) maskc[t] = 0ull;
+    __syncthreads();
+  }
+  // Twelve accumulators per thread and round, loaded together; the masks fall
+  // out of the conversion and the first windows out of a scan, since every
+  // serial pass over a chunk's groups is on this kernel's critical path (13
+  // blocks for 100 phases: 12.6 us with a mask pass and a serial sum, 10 so).
+  constexpr int U = 12;
+  for (int t0 = threadIdx.x; t0 < n; t0 += U * FINISH_THREADS) {
+    unsigned long long v[U];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
+    for (int u = 0; u < U; ++u) {
       const int t = t0 + u * FINISH_THREADS;
-      v[u] = t < n ? Kfx[base + t] : 0ull;
+      v[u] = Kfx[base + min(t, n - 1)];
     }
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
+    for (int u = 0; u < U; ++u) {
       const int t = t0 + u * FINISH_THREADS;
       if (t < n) {
-        Kfx[base + t] = 0ull;
         Kc[t] = (double)(long long)v[u] * FX_INV;
+        if (v[u]) {
+          Kfx[base + t] = 0ull;
+          if (IN_LDS) {
+            const int r = t / J;
+            atomicOr(&maskc[r], 1ull << (t - r * J));
+          }
+        }
       }
     }
   }
   __syncthreads();
-  for (int t = threadIdx.x; t < np * G; t += blockDim.x) {
-    const double* kr = Kc + (int64_t)t * J;
-    unsigned long long mk = 0;
-    for (int j = 0; j < J; ++j)
-      if (kr[j] != 0.0) mk |= 1ull << j;
-    maskc[t] = mk;
+  if (!IN_LDS) {
+    for (int t = threadIdx.x; t < np * G; t += blockDim.x) {
+      const double* kr = Kc + (int64_t)t * J;
+      unsigned long long mk = 0;
+      for (int j = 0; j < J; ++j)
+        if (kr[j] != 0.0) mk |= 1ull << j;
+      maskc[t] = mk;
+    }
+    __syncthreads();
   }
-  __syncthreads();
   compact_chunk<T>(a, chunk, Kc, maskc, sm);
 }
 
@@ -209,50 +236,50 @@ __global__ void __launch_bounds__(FINISH_THREADS) k_finish(FinishArgs a) {
   finish_block<T, IN_LDS>(a, blockIdx.x, fin_lds);
 }
 
-// Per phase (one thread each): every region centre rotated to the phase
-// (longitude + 360 deg * phase, axis tilted by the inclination), cos(alpha),
-// and the disk-cell bounding box of the caps that reach the visible
-// hemisphere.  The regions and phases are read once from the caller's
-// parameter block, so the weight kernel's many blocks read device memory.
-// Block bid of nblk (128 threads each).
+// threads per phase of the parameter kernel: a power of two that holds the
+// longest region list, at most a wave
+int params_lanes(int max_reg) {
+  int l = 1;
+  while (l < max_reg && l < 64) l *= 2;
+  return l;
+}
+
+// Per phase: every region centre rotated to the phase (longitude + 360 deg *
+// phase, axis tilted by the inclination), cos(alpha), and the disk-cell
+// bounding box of the caps that reach the visible hemisphere.  One lane per
+// (phase, region), since a centre's sines and cosines are the kernel's time
+// (100 phases of 3 regions: 9.0 us with one thread per phase walking its
+// regions, 6.5 so; 50 of 6 regions: 14.6 and 8.2).  The regions and phases are read once from the
+// caller's parameter block, so the weight kernel's many blocks read device
+// memory.  Block bid of nblk (PARAMS_THREADS each).
+constexpr int PARAMS_THREADS = 128;
 __device__ __forceinline__ void params_block(const ParamsArgs& a, int bid, int nblk) {
-  const int N = a.N, n_reg = a.n_reg, max_reg = a.max_reg, n_ph = a.n_ph;
+  const int N = a.N, n_reg = a.n_reg, max_reg = a.max_reg, n_ph = a.n_ph, lanes = a.lanes;
   const double incl = a.incl, diff_rot = a.diff_rot;
   const Region* __restrict__ reg = a.reg;
-  const double* __restrict__ phases = a.phases;
   const int2* __restrict__ pj = a.pj;
-  Region* __restrict__ reg_out = a.reg_out;
-  int2* __restrict__ pj_out = a.pj_out;
-  double4* __restrict__ cen = a.cen;
-  int4* __restrict__ box = a.box;
-  // one region list for every phase (pj == NULL): staged in LDS; per-phase
-  // lists (pj[ph] = first region, count): read from the parameter block
-  __shared__ Region s_reg[MAX_REGIONS];
-  if (!pj)
-    for (int r = threadIdx.x; r < n_reg; r += blockDim.x) s_reg[r] = reg[r];
-  for (int r = bid * blockDim.x + threadIdx.x; r < n_reg; r += nblk * blockDim.x) reg_out[r] = reg[r];
-  __syncthreads();
-  const int ph = bid * blockDim.x + threadIdx.x;
-  if (ph >= n_ph) return;
-  const double phase = phases[ph];
-  int2 rl = make_int2(0, n_reg);
+  const int t = bid * PARAMS_THREADS + threadIdx.x;
+  for (int r = t; r < n_reg; r += nblk * PARAMS_THREADS) a.reg_out[r] = reg[r];
+  const int ph = t / lanes, lr = t - ph * lanes;
+  if (ph >= n_ph) return;  // whole groups of lanes
+  const double phase = a.phases[ph];
+  int2 rl = make_int2(0, n_reg);  // one region list for every phase, or pj[ph] = (first region, count)
   if (pj) {
     rl = pj[ph];
-    pj_out[ph] = rl;
+    if (lr == 0) a.pj_out[ph] = rl;
   }
-  const Region* R = pj ? reg + rl.x : s_reg;
   // a cap point p satisfies |p - c| <= 2 sin(alpha / 2) = sqrt(2 - 2 cos
   // alpha), which bounds its projected distance from the centre
   double xlo = 2.0, xhi = -2.0, ylo = 2.0, yhi = -2.0;
-  for (int r = 0; r < rl.y; ++r) {
-    const Region g = R[r];
+  for (int r = lr; r < rl.y; r += lanes) {
+    const Region g = reg[rl.x + r];
     double cx, cy, cz, rc;
     region_centre(g.lat_deg, g.lon_deg, phase, incl, diff_rot, &cx, &cy, &cz);
     {
 #pragma clang fp contract(off)
       rc = sqrt(1.0 - g.radius * g.radius);
     }
-    cen[(int64_t)ph * max_reg + r] = make_double4(cx, cy, cz, rc);
+    a.cen[(int64_t)ph * max_reg + r] = make_double4(cx, cy, cz, rc);
     const double rad = sqrt(fmax(0.0, 1.0 - rc * rc));
     if (cz <= -rad - 1e-12) continue;
     const double d = sqrt(fmax(0.0, 2.0 - 2.0 * rc)) + 1e-9;
@@ -261,17 +288,28 @@ __device__ __forceinline__ void params_block(const ParamsArgs& a, int bid, int n
     ylo = fmin(ylo, cy - d);
     yhi = fmax(yhi, cy + d);
   }
+  for (int off = 1; off < lanes; off *= 2) {
+    xlo = fmin(xlo, __shfl_xor(xlo, off, 64));
+    xhi = fmax(xhi, __shfl_xor(xhi, off, 64));
+    ylo = fmin(ylo, __shfl_xor(ylo, off, 64));
+    yhi = fmax(yhi, __shfl_xor(yhi, off, 64));
+  }
+  if (lr) return;
   const int i0 = (int)floor((xlo + 1.0) * 0.5 * N) - 1;
   const int i1 = (int)ceil((xhi + 1.0) * 0.5 * N) + 1;
   const int k0 = (int)floor((ylo + 1.0) * 0.5 * N) - 1;
   const int k1 = (int)ceil((yhi + 1.0) * 0.5 * N) + 1;
-  box[ph] = make_int4(i0, i1, max(k0, 0), min(k1, N - 1));
+  a.box[ph] = make_int4(i0, i1, max(k0, 0), min(k1, N - 1));
 }
 
-__global__ void __launch_bounds__(128) k_params(ParamsArgs a) { params_block(a, blockIdx.x, gridDim.x); }
+__global__ void __launch_bounds__(PARAMS_THREADS) k_params(ParamsArgs a) { params_block(a, blockIdx.x, gridDim.x); }
 
+int params_blocks(int n_ph, int lanes) { return (int)(((int64_t)n_ph * lanes + PARAMS_THREADS - 1) / PARAMS_THREADS); }
+
+// Columns c0 + wave, c0 + wave + step, .. below c1 of phase ph, counted from
+// the first column of the phase's bounding box (from_box) or of the disk.
 template <bool KAHAN32>
-__device__ __forceinline__ void weights_block(const WeightsArgs& a, int ph, int slab) {
+__device__ __forceinline__ void weights_block(const WeightsArgs& a, int ph, bool from_box, int c0, int c1, int step) {
   const int N = a.N, B = a.B, J = a.J, jmin = a.jmin, G = a.G, paired = a.paired, effect = a.effect,
             n_reg_all = a.n_reg_all, max_reg = a.max_reg;
   const double u1 = a.u1, u2 = a.u2;
@@ -289,18 +327,16 @@ __device__ __forceinline__ void weights_block(const WeightsArgs& a, int ph, int 
   __shared__ int rtype[MAX_REGIONS];
   __shared__ unsigned long long s_tab[WEIGHT_WAVES][3 * MAX_MU];  // per-wave column table
 
-  const int nw = blockDim.x >> 6;
   const int wave = threadIdx.x >> 6;
   const int lane = threadIdx.x & 63;
   const int GJ = G * J;
   const double area = (2.0 / N) * (2.0 / N);
 
-  // uniform: the slab's part of the phase's bounding box
+  // uniform: the block's part of the phase's bounding box
   const int4 bx = pbox[ph];
-  const int i0 = max(bx.x, slab * SLAB_COLS);
-  const int i1 = min(bx.y, min(N, (slab + 1) * SLAB_COLS) - 1);
-  const int k0 = bx.z, k1 = bx.w;
-  if (i0 > i1 || k0 > k1) return;  // nothing of this slab is covered
+  const int b0 = max(bx.x, 0), b1 = min(bx.y, N - 1), k0 = bx.z, k1 = bx.w;
+  const int i0 = from_box ? b0 + c0 : max(b0, c0), i1 = from_box ? b1 : min(b1, c1 - 1);
+  if (i0 > i1 || k0 > k1) return;  // nothing of these columns is covered
   for (int b = threadIdx.x; b < B; b += blockDim.x) s_mub[b] = mu_b[b];
   // this phase's region list (uniform)
   int rbase = 0, n_reg = n_reg_all;
@@ -327,7 +363,7 @@ __device__ __forceinline__ void weights_block(const WeightsArgs& a, int ph, int 
   unsigned long long* Kph = Kfx + (int64_t)ph * GJ;
   unsigned long long* tab = s_tab[wave];
 
-  for (int i = i0 + wave; i <= i1; i += nw) {
+  for (int i = i0 + wave; i <= i1; i += step) {
     const double x = cell_coord(i, N);
     // rows of this column that any cap can reach: the hull of the chords of
     // the discs of radius reach around the projected centres
@@ -473,10 +509,21 @@ __device__ __forceinline__ void weights_block(const WeightsArgs& a, int ph, int 
   }
 }
 
+// n_parts blocks per phase, each taking every n_parts-th set of WEIGHT_WAVES
+// columns of the phase's bounding box
 template <bool KAHAN32>
 __global__ void __launch_bounds__(WEIGHT_WAVES * 64) k_weights(WeightsArgs a) {
-  const int ph = blockIdx.x / a.n_slabs;
-  weights_block<KAHAN32>(a, ph, blockIdx.x - ph * a.n_slabs);
+  const int ph = blockIdx.x / a.n_parts, part = blockIdx.x - ph * a.n_parts;
+  weights_block<KAHAN32>(a, ph, true, part * WEIGHT_WAVES, 0, a.n_parts * WEIGHT_WAVES);
+}
+
+// Blocks per phase of the weight kernels: enough to fill the chip with few
+// phases, few enough that a call over many phases is not spent on launching
+// blocks (500 spots x 8 phases, 75 blocks per phase, most of them without a
+// column: 93 us; 34 with 4).
+int weight_parts(int N, int n_ph) {
+  const int cols = (N + WEIGHT_WAVES - 1) / WEIGHT_WAVES;
+  return std::min(cols, std::max(4, 2048 / std::max(1, n_ph)));
 }
 
 // Differential rotation: the cells of one column no longer share a shift, so
@@ -489,7 +536,7 @@ __global__ void __launch_bounds__(WEIGHT_WAVES * 64) k_weights(WeightsArgs a) {
 // precisions; the fixed-point sums are exact, so the totals do not depend
 // on the order of cells, lanes or columns.
 __global__ void __launch_bounds__(WEIGHT_WAVES * 64) k_weights_dr(
-    int N, int B, int J, int jmin, int G, int paired, int n_slabs, double u1, double u2, int effect, double vsini,
+    int N, int B, int J, int jmin, int G, int paired, int n_parts, double u1, double u2, int effect, double vsini,
     double diff_rot, double sin_i, double cos_i, double dln, const double* __restrict__ mu_b,
     const Region* __restrict__ reg, int n_reg_all, int max_reg, const int2* __restrict__ pj,
     const double4* __restrict__ cen, const int4* __restrict__ pbox, unsigned long long* __restrict__ Kfx) {
@@ -499,19 +546,18 @@ __global__ void __launch_bounds__(WEIGHT_WAVES * 64) k_weights_dr(
   __shared__ int rtype[MAX_REGIONS];
   extern __shared__ unsigned long long s_drtab[];  // [WEIGHT_WAVES][G * J]
 
-  const int ph = blockIdx.x / n_slabs;
-  const int slab = blockIdx.x - ph * n_slabs;
-  const int nw = blockDim.x >> 6;
+  const int ph = blockIdx.x / n_parts;
+  const int part = blockIdx.x - ph * n_parts;
   const int wave = threadIdx.x >> 6;
   const int lane = threadIdx.x & 63;
   const int GJ = G * J;
   const double area = (2.0 / N) * (2.0 / N);
 
   const int4 bx = pbox[ph];
-  const int i0 = max(bx.x, slab * SLAB_COLS);
-  const int i1 = min(bx.y, min(N, (slab + 1) * SLAB_COLS) - 1);
+  const int i0 = max(bx.x, 0) + part * WEIGHT_WAVES;  // every n_parts-th set of columns of the box
+  const int i1 = min(bx.y, N - 1);
   const int k0 = bx.z, k1 = bx.w;
-  if (i0 > i1 || k0 > k1) return;  // nothing of this slab is covered
+  if (i0 > i1 || k0 > k1) return;  // nothing of these columns is covered
   for (int b = threadIdx.x; b < B; b += blockDim.x) s_mub[b] = mu_b[b];
   int rbase = 0, n_reg = n_reg_all;
   if (pj) {
@@ -535,7 +581,7 @@ __global__ void __launch_bounds__(WEIGHT_WAVES * 64) k_weights_dr(
   for (int e = lane; e < GJ; e += 64) tab[e] = 0ull;
   __syncthreads();
 
-  for (int i = i0 + wave; i <= i1; i += nw) {
+  for (int i = i0 + wave; i <= i1; i += n_parts * WEIGHT_WAVES) {
     const double x = cell_coord(i, N);
     double ylo = 2.0, yhi = -2.0;
     for (int r = 0; r < n_reg; ++r) {
@@ -600,12 +646,12 @@ namespace {
 
 ParamsArgs params_args(const soap_ctx* c, const Plan& pl, const Region* d_reg, int n_reg, int max_reg,
                        const double* d_ph, const int2* d_pj, const WeightsOut& o) {
-  return ParamsArgs{c->N, n_reg, max_reg, pl.n_ph, c->incl, c->diff_rot, d_reg, d_ph, d_pj, o.reg, o.pj, o.cen, o.box};
+  return ParamsArgs{c->N, n_reg, max_reg, pl.n_ph, params_lanes(max_reg), c->incl, c->diff_rot, d_reg, d_ph, d_pj, o.reg, o.pj, o.cen, o.box};
 }
 
 WeightsArgs weights_args(const soap_ctx* c, const Plan& pl, int n_reg, int max_reg, const int2* pj,
                          const WeightsOut& o) {
-  return WeightsArgs{c->N,     c->B,  c->J,       c->jmin,    pl.G,      pl.paired, pl.n_slabs,
+  return WeightsArgs{c->N,     c->B,  c->J,       c->jmin,    pl.G,      pl.paired, weight_parts(c->N, pl.n_ph),
                      pl.effect, n_reg, max_reg,   c->u1,      c->u2,     c->d_mu,   c->d_col_c,
                      c->d_col_w, o.reg, pj,       o.cen,      o.box,     o.Kfx};
 }
@@ -655,7 +701,7 @@ __device__ __forceinline__ int find_cfg(const int* __restrict__ off, int n, int 
 }  // namespace
 
 // Work-list forms: configuration i owns blocks off[i] .. off[i + 1] - 1.
-__global__ void __launch_bounds__(128) k_params_batch(const ParamsArgs* __restrict__ args, const int* __restrict__ off,
+__global__ void __launch_bounds__(PARAMS_THREADS) k_params_batch(const ParamsArgs* __restrict__ args, const int* __restrict__ off,
                                                       int n) {
   const int i = find_cfg(off, n, blockIdx.x);
   const ParamsArgs a = args[i];
@@ -668,7 +714,7 @@ __global__ void __launch_bounds__(WEIGHT_WAVES * 64) k_weights_batch(const Weigh
                                                                      const int4* __restrict__ blk) {
   const int4 t = blk[blockIdx.x];
   const WeightsArgs a = args[t.x];
-  weights_block<KAHAN32>(a, t.y, t.z);
+  weights_block<KAHAN32>(a, t.y, false, t.z * SLAB_COLS, (t.z + 1) * SLAB_COLS, WEIGHT_WAVES);
 }
 
 template <typename T, bool IN_LDS>
@@ -682,17 +728,18 @@ __global__ void __launch_bounds__(FINISH_THREADS) k_finish_batch(const FinishArg
 
 hipError_t launch_weights(soap_ctx* c, const Plan& pl, const Region* d_reg, int n_reg, int max_reg,
                           const double* d_ph, const int2* d_pj, const WeightsOut& o, hipStream_t st) {
-  hipLaunchKernelGGL(k_params, dim3((unsigned)((pl.n_ph + 127) / 128)), dim3(128), 0, st,
-                     params_args(c, pl, d_reg, n_reg, max_reg, d_ph, d_pj, o));
+  const ParamsArgs pa = params_args(c, pl, d_reg, n_reg, max_reg, d_ph, d_pj, o);
+  hipLaunchKernelGGL(k_params, dim3((unsigned)params_blocks(pl.n_ph, pa.lanes)), dim3(PARAMS_THREADS), 0, st, pa);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const int2* pj = d_pj ? o.pj : nullptr;
-  dim3 grid((unsigned)pl.n_slabs * (unsigned)pl.n_ph);
+  const int parts = weight_parts(c->N, pl.n_ph);
+  dim3 grid((unsigned)parts * (unsigned)pl.n_ph);
   if (c->diff_rot != 0.0) {
     const size_t lds = (size_t)WEIGHT_WAVES * pl.G * c->J * sizeof(unsigned long long);
     if (pl.G * c->J > DR_TAB_MAX) return hipErrorInvalidValue;  // refused at init
     hipLaunchKernelGGL(k_weights_dr, grid, dim3(64 * WEIGHT_WAVES), lds, st, c->N, c->B, c->J, c->jmin, pl.G,
-                       pl.paired, pl.n_slabs, c->u1, c->u2, pl.effect, c->vsini, c->diff_rot, c->sin_i, c->cos_i,
+                       pl.paired, parts, c->u1, c->u2, pl.effect, c->vsini, c->diff_rot, c->sin_i, c->cos_i,
                        c->dln, c->d_mu, o.reg, n_reg, max_reg, pj, o.cen, o.box, o.Kfx);
     return hipGetLastError();
   }
@@ -802,7 +849,7 @@ hipError_t table_batch_upload(const TableBatchCfg* cfgs, int n, void* d_buf, Tab
     const soap_ctx* c = q.c;
     if (c->diff_rot != 0.0 || !pc_valid(c->prec == SOAP_PREC_FP32, q.pl.pc)) return hipErrorInvalidValue;
     pa.push_back(params_args(c, q.pl, q.d_reg, q.n_reg, q.max_reg, q.d_ph, nullptr, q.o));
-    pb.push_back((q.pl.n_ph + 127) / 128);
+    pb.push_back(params_blocks(q.pl.n_ph, pa.back().lanes));
     const int w = c->prec == SOAP_PREC_FP32 ? 0 : 1;
     const int wi = (int)wa[w].size();
     wa[w].push_back(weights_args(c, q.pl, q.n_reg, q.max_reg, nullptr, q.o));
@@ -842,7 +889,7 @@ hipError_t table_batch_upload(const TableBatchCfg* cfgs, int n, void* d_buf, Tab
 
 hipError_t table_batch_launch(const TableBatch& tb, hipStream_t st) {
   if (tb.params.n_blocks > 0)
-    hipLaunchKernelGGL(k_params_batch, dim3((unsigned)tb.params.n_blocks), dim3(128), 0, st,
+    hipLaunchKernelGGL(k_params_batch, dim3((unsigned)tb.params.n_blocks), dim3(PARAMS_THREADS), 0, st,
                        static_cast<const ParamsArgs*>(tb.params.args), tb.params.off, tb.params.n_cfg);
   const dim3 wblock(64 * WEIGHT_WAVES), fblock(FINISH_THREADS);
   const TableBatch::Launch* W = tb.weights;
