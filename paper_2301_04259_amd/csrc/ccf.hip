@@ -32,7 +32,9 @@ namespace soap {
 
 constexpr int CCF_LB = 32;        // mask lines per block (one partial CCF row each)
 constexpr int CCF_SB = 8;         // spectra per block
-constexpr int CCF_THREADS = 192;  // one thread per velocity (A velocities each past 192)
+constexpr int CCF_THREADS = 512;  // most threads of a block: one per velocity, two velocities each past 512
+constexpr int CCF_MIN_THREADS = 192;  // fewest: the block also stages the pixels
+constexpr int CCF_NV_MAX = 768;   // velocities per grid
 constexpr int CCF_STG_MAX = 512;  // widest staged span of a batch, in pixels
 // a line's hole centre, in pixels, is kept within this margin of the grid:
 // lines further out reach no pixel
@@ -43,32 +45,23 @@ int ccf_span_pixels(bool) { return CCF_STG_MAX; }
 
 namespace {
 
-// 4 consecutive elements of 16-byte-aligned memory in their own type
+// 16 bytes of elements
 template <typename T>
-__device__ __forceinline__ void get4t(T* x, const T* p) {
-  if constexpr (sizeof(T) == 4) {
-    const float4 v = *reinterpret_cast<const float4*>(p);
-    x[0] = v.x;
-    x[1] = v.y;
-    x[2] = v.z;
-    x[3] = v.w;
-  } else {
-    const double2 a = reinterpret_cast<const double2*>(p)[0];
-    const double2 b = reinterpret_cast<const double2*>(p)[1];
-    x[0] = a.x;
-    x[1] = a.y;
-    x[2] = b.x;
-    x[3] = b.y;
-  }
-}
+struct Quad {
+  static constexpr int N = 16 / (int)sizeof(T);
+  T x[N];
+};
 
 }  // namespace
 
 // One block per (CCF_LB mask lines, CCF_SB spectra).  The block walks the
 // batches of its lines (host-built: consecutive lines whose holes, at every
 // trial velocity, stay inside a span of STG pixels).  A batch's span of the
-// block's spectra is staged pixel-major in LDS, [pixel][spectrum], so that
-// one thread reads the SB values of a pixel with 16-byte loads; two stage
+// block's spectra is staged in LDS in planes of 16 bytes of spectra per pixel,
+// so that one thread reads the SB values of a pixel with 16-byte loads and
+// without bank conflicts (rows of all SB values had 2.4 conflict cycles per
+// load: 76 us against 71 for 300 spectra of 150001 pixels, 3000 lines and 401
+// velocities); two stage
 // buffers alternate, the next batch's loads are in flight while one is
 // used, and one barrier per batch separates them.  Pixels outside the
 // spectrum are staged as zeros.  Each thread computes its holes' pixel
@@ -84,12 +77,17 @@ __device__ __forceinline__ void ccf_block(int P, int64_t n_spec, const T* __rest
                                           const int4* __restrict__ batches, const int* __restrict__ bfirst,
                                           int n_v, T* __restrict__ part, int lb, int sb) {
   constexpr int SB = CCF_SB;
-  constexpr int R = (STG + CCF_THREADS - 1) / CCF_THREADS;  // staged pixels per thread
-  static_assert(SB % 4 == 0, "16-byte stage rows");
-  __shared__ __align__(16) T st[2][STG][SB];
+  constexpr int R = (STG + CCF_MIN_THREADS - 1) / CCF_MIN_THREADS;  // staged pixels per thread
+  constexpr int QN = Quad<T>::N, NQ = SB / QN;
+  static_assert(SB % QN == 0, "whole 16-byte pieces");
+  __shared__ __align__(16) Quad<T> st[2][NQ][STG];
   __shared__ double2 s_line[CCF_LB];
-  __shared__ double2 s_ed[A * CCF_THREADS];
-  const int tid = threadIdx.x;
+  // the edges on their way to registers: past the first stage buffer, which
+  // is filled meanwhile, or over both
+  constexpr bool OVER = sizeof(st[1]) < sizeof(double2) * A * CCF_THREADS;
+  static_assert(sizeof(st) >= sizeof(double2) * (A == 1 ? CCF_THREADS : CCF_NV_MAX), "edges fit");
+  double2* s_ed = reinterpret_cast<double2*>(&st[OVER ? 0 : 1][0][0]);
+  const int tid = threadIdx.x, nt = blockDim.x;
   const int64_t s0 = (int64_t)sb * SB;
   const int ns = (int)min<int64_t>(SB, n_spec - s0);
   const int b0 = bfirst[lb], b1 = bfirst[lb + 1];
@@ -99,18 +97,19 @@ __device__ __forceinline__ void ccf_block(int P, int64_t n_spec, const T* __rest
   // lanes past the velocity grid repeat its last velocity (results dropped);
   // the edges go through LDS so that no global load is pending in the loop
 #pragma unroll
-  for (int a = 0; a < A; ++a) s_ed[tid + a * CCF_THREADS] = edges[min(tid + a * CCF_THREADS, n_v - 1)];
+  for (int a = 0; a < A; ++a) s_ed[tid + a * nt] = edges[min(tid + a * nt, n_v - 1)];
   __syncthreads();
   double alo[A], ahi[A];
   T acc[A][SB];
 #pragma unroll
   for (int a = 0; a < A; ++a) {
-    const double2 e = s_ed[tid + a * CCF_THREADS];
+    const double2 e = s_ed[tid + a * nt];
     alo[a] = e.x;
     ahi[a] = e.y;
 #pragma unroll
     for (int s = 0; s < SB; ++s) acc[a][s] = T(0);
   }
+  if constexpr (OVER) __syncthreads();
   T vals[R][SB];
   // only the batch's read span (batches[bi].w <= STG pixels) is loaded and
   // staged: no hole of the batch reads past it
@@ -119,8 +118,8 @@ __device__ __forceinline__ void ccf_block(int P, int64_t n_spec, const T* __rest
     const int lo = batches[bi].x, span = batches[bi].w;
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-      if (tid + r * CCF_THREADS < span) {
-        const int m = min(max(lo + tid + r * CCF_THREADS, 0), P - 1);
+      if (tid + r * nt < span) {
+        const int m = min(max(lo + tid + r * nt, 0), P - 1);
 #pragma unroll
         for (int s = 0; s < SB; ++s) vals[r][s] = F[(s0 + min(s, ns - 1)) * (int64_t)P + m];
       }
@@ -129,15 +128,20 @@ __device__ __forceinline__ void ccf_block(int P, int64_t n_spec, const T* __rest
   auto put = [&](int bi) {
     if (bi >= b1) return;
     const int lo = batches[bi].x, span = batches[bi].w;
-    T(*sb)[SB] = st[(bi - b0) & 1];
+    Quad<T>(*sb)[STG] = st[(bi - b0) & 1];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-      const int i = tid + r * CCF_THREADS;
+      const int i = tid + r * nt;
       if (i < span) {
         const int m = lo + i;
         const bool ok = m >= 0 && m < P;
 #pragma unroll
-        for (int s = 0; s < SB; ++s) sb[i][s] = ok ? vals[r][s] : T(0);
+        for (int q = 0; q < NQ; ++q) {
+          Quad<T> v;
+#pragma unroll
+          for (int s = 0; s < QN; ++s) v.x[s] = ok ? vals[r][q * QN + s] : T(0);
+          sb[q][i] = v;
+        }
       }
     }
   };
@@ -147,7 +151,7 @@ __device__ __forceinline__ void ccf_block(int P, int64_t n_spec, const T* __rest
   __syncthreads();
   for (int bi = b0; bi < b1; ++bi) {
     const int4 B = batches[bi];
-    const T(*sb)[SB] = st[(bi - b0) & 1];
+    const Quad<T>(*sb)[STG] = st[(bi - b0) & 1];
     for (int l = B.y; l < B.z; ++l) {
       const double2 mw = s_line[l - l0];
 #pragma unroll
@@ -174,12 +178,13 @@ __device__ __forceinline__ void ccf_block(int P, int64_t n_spec, const T* __rest
         }
 #pragma unroll
         for (int px = 0; px < NPX; ++px) {
-          T f[SB];
-#pragma unroll
-          for (int c = 0; c < SB / 4; ++c) get4t(&f[4 * c], &sb[i0 + px][4 * c]);
           const T wp = (T)w[px];
 #pragma unroll
-          for (int s = 0; s < SB; ++s) acc[a][s] = fma(wp, f[s], acc[a][s]);
+          for (int q = 0; q < NQ; ++q) {
+            const Quad<T> f = sb[q][i0 + px];
+#pragma unroll
+            for (int s = 0; s < QN; ++s) acc[a][q * QN + s] = fma(wp, f.x[s], acc[a][q * QN + s]);
+          }
         }
       }
     }
@@ -189,7 +194,7 @@ __device__ __forceinline__ void ccf_block(int P, int64_t n_spec, const T* __rest
   }
 #pragma unroll
   for (int a = 0; a < A; ++a) {
-    const int k = tid + a * CCF_THREADS;
+    const int k = tid + a * nt;
     if (k >= n_v) break;
 #pragma unroll
     for (int s = 0; s < SB; ++s)
@@ -777,11 +782,19 @@ __global__ void __launch_bounds__(CCF_FIN_THREADS) k_ccf_fit_batch(const CcfBatc
                         t.y);
 }
 
+// Whole waves that hold the velocity grid, so that a grid is not rounded up to
+// a fixed block: 401 velocities run on 448 lanes (300 spectra of 150001 pixels,
+// 3000 lines: 103 us on 768 lanes, 71 so).
+template <int A>
+static unsigned ccf_threads(int n_v) {
+  return (unsigned)std::max(CCF_MIN_THREADS, 64 * ((n_v + 64 * A - 1) / (64 * A)));
+}
+
 template <typename T, int A, int NPX, int STG>
 static void launch_ccf_a(const CcfPlan& q, hipStream_t st, dim3 grid, const void* d_flux, int64_t n_spec,
                          void* d_part) {
   const unsigned char* base = q.tables;
-  hipLaunchKernelGGL((k_ccf<T, A, NPX, STG>), grid, dim3(CCF_THREADS), 0, st, (int)q.P, n_spec,
+  hipLaunchKernelGGL((k_ccf<T, A, NPX, STG>), grid, dim3(ccf_threads<A>(q.nv)), 0, st, (int)q.P, n_spec,
                      static_cast<const T*>(d_flux), reinterpret_cast<const double2*>(base),
                      reinterpret_cast<const double2*>(base + q.off_edges),
                      reinterpret_cast<const int4*>(base + q.off_batch),
@@ -792,8 +805,7 @@ template <typename T, int NPX, int STG>
 static void launch_ccf_n(const CcfPlan& q, hipStream_t st, dim3 grid, const void* d_flux, int64_t n_spec,
                          void* d_part) {
   if (q.nv <= CCF_THREADS) launch_ccf_a<T, 1, NPX, STG>(q, st, grid, d_flux, n_spec, d_part);
-  else if (q.nv <= 2 * CCF_THREADS) launch_ccf_a<T, 2, NPX, STG>(q, st, grid, d_flux, n_spec, d_part);
-  else launch_ccf_a<T, 4, NPX, STG>(q, st, grid, d_flux, n_spec, d_part);
+  else launch_ccf_a<T, 2, NPX, STG>(q, st, grid, d_flux, n_spec, d_part);
 }
 
 template <typename T, int STG>
@@ -898,15 +910,14 @@ size_t al256c(size_t b) { return 256 * ((b + 255) / 256); }
 
 template <typename T, int A, int NPX, int STG>
 void launch_ccf_batch_a(const CcfBatch& cb, hipStream_t st) {
-  hipLaunchKernelGGL((k_ccf_batch<T, A, NPX, STG>), dim3((unsigned)cb.n_ccf_blocks), dim3(CCF_THREADS), 0, st,
-                     cb.sets, cb.ccf_blk, cb.shape.nv);
+  hipLaunchKernelGGL((k_ccf_batch<T, A, NPX, STG>), dim3((unsigned)cb.n_ccf_blocks),
+                     dim3(ccf_threads<A>(cb.shape.nv)), 0, st, cb.sets, cb.ccf_blk, cb.shape.nv);
 }
 
 template <typename T, int NPX, int STG>
 void launch_ccf_batch_n(const CcfBatch& cb, hipStream_t st) {
   if (cb.shape.nv <= CCF_THREADS) launch_ccf_batch_a<T, 1, NPX, STG>(cb, st);
-  else if (cb.shape.nv <= 2 * CCF_THREADS) launch_ccf_batch_a<T, 2, NPX, STG>(cb, st);
-  else launch_ccf_batch_a<T, 4, NPX, STG>(cb, st);
+  else launch_ccf_batch_a<T, 2, NPX, STG>(cb, st);
 }
 
 template <typename T, int STG>
