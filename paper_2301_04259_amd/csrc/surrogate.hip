@@ -167,12 +167,11 @@ __global__ void __launch_bounds__(256) k_mse(int B, int n_out, const float* __re
   if (lane == 0) row_se[(int64_t)e * B + i] = (float)tot;
 }
 
-// per member: loss = sum of row_se / (B n_out), rows added in order by one
+// one member's loss = sum of row_se / (B n_out), rows added in order by one
 // block of 256 threads (strided partials, then a fixed tree)
-__global__ void __launch_bounds__(256) k_loss_sum(int B, int n_out, const float* __restrict__ row_se,
-                                                  float* __restrict__ loss) {
+__device__ __forceinline__ void loss_block(int B, int n_out, const float* __restrict__ row_se,
+                                           float* __restrict__ loss, int e) {
   __shared__ float s[256];
-  const int e = blockIdx.x;
   float a = 0.f;
   for (int i = threadIdx.x; i < B; i += 256) a += row_se[(int64_t)e * B + i];
   s[threadIdx.x] = a;
@@ -182,6 +181,11 @@ __global__ void __launch_bounds__(256) k_loss_sum(int B, int n_out, const float*
     __syncthreads();
   }
   if (threadIdx.x == 0) loss[e] = s[0] / ((float)B * (float)n_out);
+}
+
+__global__ void __launch_bounds__(256) k_loss_sum(int B, int n_out, const float* __restrict__ row_se,
+                                                  float* __restrict__ loss) {
+  loss_block(B, n_out, row_se, loss, blockIdx.x);
 }
 
 // db[j] = sum_i D[i][j] per member, in two fixed-order stages: partial sums
@@ -221,26 +225,470 @@ __global__ void k_bf16_to_f32(int64_t n, const __bf16* __restrict__ a, float* __
   if (t < n) b[t] = (float)a[t];
 }
 
-// Adam on the FP32 masters (all members), then the BF16 copies
-__global__ void k_adam(int64_t n, float lr, float b1, float b2, float eps, float c1, float c2,
-                       float* __restrict__ P, const float* __restrict__ G, float* __restrict__ Mm,
-                       float* __restrict__ Vm, __bf16* __restrict__ Pb) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= n) return;
-  const float g = G[t];
-  const float m = b1 * Mm[t] + (1.0f - b1) * g;
-  const float v = b2 * Vm[t] + (1.0f - b2) * g * g;
-  Mm[t] = m;
-  Vm[t] = v;
-  const float mh = m / c1, vh = v / c2;
-  const float p = P[t] - lr * mh / (sqrtf(vh) + eps);
-  P[t] = p;
-  Pb[t] = (__bf16)p;
+struct AdamArgs {
+  float lr, b1, b2, eps, c1, c2;
+};
+
+// the parameter after its Adam step (the contractions written out, so that every
+// kernel rounds alike)
+__device__ __forceinline__ float adam(const AdamArgs& a, float g, float p, float* m_, float* v_) {
+  const float m = fmaf(1.0f - a.b1, g, a.b1 * *m_);
+  const float v = fmaf((1.0f - a.b2) * g, g, a.b2 * *v_);
+  *m_ = m;
+  *v_ = v;
+  const float mh = m / a.c1, vh = v / a.c2;
+  return p - a.lr * mh / (sqrtf(vh) + a.eps);
 }
 
-__global__ void k_f32_to_bf16(int64_t n, const float* __restrict__ a, __bf16* __restrict__ b) {
+// Fragment order of a BF16 matrix X[row][k] (rows a multiple of 16, K of 32):
+// the 16 x 32 pieces that one MFMA reads, each in lane order (1 KiB that a wave
+// loads as 16 bytes per lane), k steps of a row tile after one another.
+__device__ __forceinline__ int64_t frag(int row, int64_t k, int64_t K) {
+  return (int64_t)(row >> 4) * 16 * K + (k >> 5) * 512 + ((row & 15) + 16 * ((k >> 3) & 3)) * 8 + (k & 7);
+}
+
+// The BF16 copies of parameter t: transposed in fragment order (the forward
+// products), and in fragment order (bfrag) or as it lies (backward)
+__device__ __forceinline__ void put_bf16(int64_t t, const SgLayout& L, int H, int O, int bfrag, __bf16 v,
+                                         __bf16* __restrict__ b, __bf16* __restrict__ bt) {
+  const int64_t e = t / L.n_params, q = t - e * L.n_params;
+  int64_t base = -1;
+  int rows = 0, cols = 0;
+  if (q < L.b1) base = L.W1, rows = SG_K0, cols = H;
+  else if (q >= L.W2 && q < L.b2) base = L.W2, rows = H, cols = H;
+  else if (q >= L.W3 && q < L.b3) base = L.W3, rows = H, cols = O;
+  if (base < 0) return;  // biases are read in FP32
+  const int64_t m = e * L.n_params + base;
+  const int i = (int)((q - base) / cols), j = (int)((q - base) - (int64_t)i * cols);
+  b[bfrag ? m + frag(i, j, cols) : t] = v;
+  bt[m + frag(j, i, rows)] = v;
+}
+
+// Adam on the FP32 masters (all members), then the BF16 copies
+__global__ void k_adam(int64_t n, AdamArgs a, SgLayout L, int H, int O, int bfrag, float* __restrict__ P,
+                       const float* __restrict__ G, float* __restrict__ Mm, float* __restrict__ Vm,
+                       __bf16* __restrict__ Pb, __bf16* __restrict__ PbT) {
   const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t < n) b[t] = (__bf16)a[t];
+  if (t >= n) return;
+  const float p = adam(a, G[t], P[t], Mm + t, Vm + t);
+  P[t] = p;
+  put_bf16(t, L, H, O, bfrag, (__bf16)p, Pb, PbT);
+}
+
+__global__ void k_f32_to_bf16(int64_t n, SgLayout L, int H, int O, int bfrag, const float* __restrict__ a,
+                              __bf16* __restrict__ b, __bf16* __restrict__ bt) {
+  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (t < n) put_bf16(t, L, H, O, bfrag, (__bf16)a[t], b, bt);
+}
+
+// ---- row kernels: a network in one launch, its gradients in another ----------
+//
+// Everything but the weight gradients is local to a row of the batch: the three
+// layers, the output error and the two back-propagated layers.  A block takes
+// 16 MT rows of one member through all of them, activations in LDS, weights
+// read from L2 as the MFMA's B operand, whole cache lines in fragment order.
+// What the weight gradients need goes out transposed in the same order, so that
+// k_sg_grads reads both operands straight into registers; it also updates the
+// parameters.
+// Every output is one MFMA chain over k in steps of 32, and the column sums
+// keep their order, so a step gives bit for bit what the general kernels give.
+// Bound by launches and latency at the usual sizes: a step of batch 512, hidden
+// 256, 128 outputs and 4 members takes 17 us of rows (about 3.5 of them before the
+// first product, 2 a layer, of those 1.5 of VALU work on two waves' SiLUs) and 12
+// of gradients, 31 us in all against 139 as 20 launches; batch 4096, 96 against
+// 460.  Row-major weights (64-byte pieces at power-of-two strides) took 26 and
+// 27 us, eight waves a block 19.
+constexpr int sr_waves(bool train) { return train ? 16 : 8; }  // waves per block
+constexpr int SR_MT = 2;  // row tiles per block of large inference batches
+
+namespace {
+
+struct SgRows {
+  int B, n_in, H, O;
+  SgLayout L;
+  const float* x;
+  const float* target;
+  const float* P;
+  const __bf16 *Pb, *PbT;
+  float* Y;  // inference: [E][B][O]
+  // training
+  __bf16 *XT, *H1T, *H2T, *dYT, *dZ2T, *dZ1T;  // [E][width][B] (XT: one for all members)
+  float *dYf, *dZ2f, *dZ1f;                    // [E][B][width]
+  float* row_se;                               // [E][B]
+};
+
+// bytes of LDS of a block of R rows
+size_t sg_rows_lds(int R, int H, int O, bool train) {
+  size_t b = 2 * ((size_t)R * (SG_K0 + 8) + 2 * (size_t)R * (H + 8)) + 4 * (size_t)(2 * H + O);
+  if (train) b += 2 * (size_t)R * (O + 8) + 4 * (2 * (size_t)R * (H + 4) + (size_t)R * (O + 4));
+  return b;
+}
+
+typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
+
+// Barrier for data that passes through LDS: unlike __syncthreads it does not
+// wait for the global loads and stores in flight, the next layer's weights
+// among them.
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+// A wave's weights of NT column tiles over SR_S k steps (past K the last step
+// is read again and not used)
+constexpr int SR_S = 8;
+template <int NT>
+struct RowsB {
+  bf16x8 v[SR_S][NT];
+};
+
+template <int NT>
+__device__ __forceinline__ void rows_load(RowsB<NT>& o, const __bf16* __restrict__ Bf, int K, int t, int k0) {
+  const __bf16* bp = Bf + (int64_t)t * 16 * K + 8 * (threadIdx.x & 63);
+#pragma unroll
+  for (int s = 0; s < SR_S; ++s)
+#pragma unroll
+    for (int n = 0; n < NT; ++n)
+      o.v[s][n] = *reinterpret_cast<const bf16x8*>(bp + n * 16 * K + 16 * min(k0 + 32 * s, K - 32));
+}
+
+// the first weights that rows_mm uses: loaded one layer ahead, so that their
+// latency is spent under the layer before (waves past N load tile 0)
+template <int NT>
+__device__ __forceinline__ void rows_first(RowsB<NT>& o, const __bf16* Bf, int K, int N) {
+  const int t = NT * __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  rows_load(o, Bf, K, 16 * t < N ? t : 0, 0);
+}
+
+// out[16 MT][N] = As[16 MT][K] B[N][K]^T for the block's rows, B in fragment
+// order, NT column
+// tiles at a time per wave of W (N is a multiple of 32).  next() runs after the
+// wave's last product, before its results are stored: loads that it issues don't
+// queue behind those stores.  ep(row, column, values of
+// rows row .. row + 3).
+template <int MT, int NT, int W, bool PRE, typename NEXT, typename EP>
+__device__ __forceinline__ void rows_mm(RowsB<NT>& first, const __bf16* As, int lda, const __bf16* __restrict__ Bf, int K,
+                                        int N, NEXT&& next, EP&& ep) {
+  const int l = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int c = l & 15, q = 4 * (l >> 4);
+  const __bf16* ap = As + c * lda + 2 * q;
+  if (16 * NT * w >= N) next();
+  for (int t = NT * w; 16 * t < N; t += NT * W) {
+    f32x4 acc[MT][NT];
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+      for (int n = 0; n < NT; ++n) acc[m][n] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int k0 = 0; k0 < K; k0 += 32 * SR_S) {
+      if (!PRE || t != NT * w || k0) rows_load(first, Bf, K, t, k0);
+#pragma unroll
+      for (int s = 0; s < SR_S; ++s) {
+        if (k0 + 32 * s >= K) break;
+        bf16x8 av[MT];
+#pragma unroll
+        for (int m = 0; m < MT; ++m) av[m] = *reinterpret_cast<const bf16x8*>(ap + m * 16 * lda + k0 + 32 * s);
+#pragma unroll
+        for (int m = 0; m < MT; ++m)
+#pragma unroll
+          for (int n = 0; n < NT; ++n)
+            acc[m][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[m], first.v[s][n], acc[m][n], 0, 0, 0);
+      }
+    }
+    if (16 * (t + NT * W) >= N) next();
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+      for (int n = 0; n < NT; ++n) ep(16 * m + q, 16 * (t + n) + c, acc[m][n]);
+  }
+}
+
+}  // namespace
+
+template <int MT, bool TRAIN>
+__global__ void __launch_bounds__(64 * sr_waves(TRAIN), MT == 1 ? 1 : 4) k_sg_rows(SgRows a) {
+  extern __shared__ __align__(16) unsigned char lds[];
+  constexpr int R = 16 * MT;
+  constexpr int W = sr_waves(TRAIN), NT = 16 / W;
+  constexpr bool PRE = MT == 1;
+  const int H = a.H, O = a.O, B = a.B, e = blockIdx.y;
+  const int ldx = SG_K0 + 8, ldh = H + 8, ldo = O + 8, ldz = H + 4, ldd = O + 4;
+  __bf16* Xs = reinterpret_cast<__bf16*>(lds);
+  __bf16* H1s = Xs + R * ldx;
+  __bf16* H2s = H1s + R * ldh;
+  float* bias = reinterpret_cast<float*>(H2s + R * ldh);   // b1, b2, b3
+  __bf16* dYs = reinterpret_cast<__bf16*>(bias + 2 * H + O);  // training only, as are the next three
+  float* Z1 = reinterpret_cast<float*>(dYs + R * ldo);
+  float* Z2 = Z1 + R * ldz;
+  float* Df = Z2 + R * ldz;                               // the targets, then the errors
+  __bf16* dZ2s = H1s;                                    // layer 2 is done with H1 by then
+  const int64_t r0 = (int64_t)blockIdx.x * R;
+  const float* P = a.P + e * a.L.n_params;
+  const __bf16* Pb = a.Pb + e * a.L.n_params;
+  const __bf16* PbT = a.PbT + e * a.L.n_params;
+  RowsB<NT> wa, wb;
+  auto first = [](RowsB<NT>& o, const __bf16* Bf, int K, int N) {
+    return [&, Bf, K, N] {
+      if (PRE && N) rows_first(o, Bf, K, N);
+    };
+  };
+  first(wa, PbT + a.L.W1, SG_K0, H)();
+  first(wb, PbT + a.L.W2, H, H)();
+  // the inputs, zero padded to one k step; rows past the batch repeat its last
+  for (int t = threadIdx.x; t < R * SG_K0; t += 64 * W) {
+    const int i = t / SG_K0, k = t - i * SG_K0;
+    const int64_t row = min(r0 + i, (int64_t)B - 1);
+    Xs[i * ldx + k] = (__bf16)(k < a.n_in ? a.x[row * a.n_in + k] : 0.f);
+  }
+  for (int t = threadIdx.x; t < 2 * H + O; t += 64 * W)
+    bias[t] = P[t < H ? a.L.b1 + t : t < 2 * H ? a.L.b2 + t - H : a.L.b3 + t - 2 * H];
+  if constexpr (TRAIN)
+    for (int t = threadIdx.x; t < R * O; t += 64 * W) {
+      const int i = t / O, j = t - i * O;
+      Df[i * ldd + j] = a.target[(r0 + i) * O + j];
+    }
+  lds_barrier();
+  if constexpr (TRAIN) {
+    if (e == 0)
+      for (int t = threadIdx.x; t < R * SG_K0; t += 64 * W) {
+        const int k = t / R, i = t - k * R;
+        a.XT[frag(k, r0 + i, B)] = Xs[i * ldx + k];
+      }
+  }
+  auto column = [&](__bf16* T, int width, int col, int row, bf16x4 v) {  // rows row .. row + 3 of a transposed matrix
+    *reinterpret_cast<bf16x4*>(T + (int64_t)e * width * B + frag(col, r0 + row, B)) = v;
+  };
+  auto hidden = [&](const float* bv, float* Z, __bf16* Hs, __bf16* HT) {
+    return [=](int row, int col, f32x4 v) {
+      const float b = bv[col];
+      bf16x4 h;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const float z = v[r] + b;
+        h[r] = (__bf16)silu(z);
+        Hs[(row + r) * ldh + col] = h[r];
+        if constexpr (TRAIN) Z[(row + r) * ldz + col] = z;
+      }
+      if constexpr (TRAIN) column(HT, H, col, row, h);
+    };
+  };
+  rows_mm<MT, NT, W, PRE>(wa, Xs, ldx, PbT + a.L.W1, SG_K0, H, first(wa, PbT + a.L.W3, H, O), hidden(bias, Z1, H1s, a.H1T));
+  lds_barrier();
+  rows_mm<MT, NT, W, PRE>(wb, H1s, ldh, PbT + a.L.W2, H, H, first(wb, Pb + a.L.W3, O, TRAIN ? H : 0), hidden(bias + H, Z2, H2s, a.H2T));
+  lds_barrier();
+  const float* b3 = bias + 2 * H;
+  if constexpr (!TRAIN) {
+    rows_mm<MT, NT, W, PRE>(wa, H2s, ldh, PbT + a.L.W3, H, O, [] {}, [=](int row, int col, f32x4 v) {
+      if (r0 + __builtin_amdgcn_readfirstlane(row & ~15) >= B) return;  // uniform: the batch is a multiple of 16
+      const float b = b3[col];
+      float* y = a.Y + ((int64_t)e * B + r0 + row) * O + col;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) y[(int64_t)r * O] = v[r] + b;
+    });
+  } else {
+    const float sc = 2.0f / ((float)B * (float)O);
+    rows_mm<MT, NT, W, PRE>(wa, H2s, ldh, PbT + a.L.W3, H, O, first(wa, Pb + a.L.W2, H, H), [=](int row, int col, f32x4 v) {
+      const float b = b3[col];
+      bf16x4 d;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const float y = v[r] + b;
+        const float df = y - Df[(row + r) * ldd + col];
+        d[r] = (__bf16)(sc * df);
+        Df[(row + r) * ldd + col] = df;
+        dYs[(row + r) * ldo + col] = d[r];
+        a.dYf[((int64_t)e * B + r0 + row + r) * O + col] = (float)d[r];
+      }
+      column(a.dYT, O, col, row, d);
+    });
+    lds_barrier();
+    // squared error of each row, one wave per row
+    for (int i = threadIdx.x >> 6; i < R; i += W) {
+      const int lane = threadIdx.x & 63;
+      float se = 0.f;
+      for (int j = lane; j < O; j += 64) {
+        const float df = Df[i * ldd + j];
+        se = fmaf(df, df, se);
+      }
+      const double tot = wave_sum_f64((double)se);
+      if (lane == 0) a.row_se[(int64_t)e * B + r0 + i] = (float)tot;
+    }
+    // dZ2 = (dY W3^T) SiLU'(Z2), dZ1 = (dZ2 W2^T) SiLU'(Z1)
+    rows_mm<MT, NT, W, PRE>(wb, dYs, ldo, Pb + a.L.W3, O, H, [] {}, [=](int row, int col, f32x4 v) {
+      bf16x4 d;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const float dz = v[r] * silu_grad(Z2[(row + r) * ldz + col]);
+        d[r] = (__bf16)dz;
+        dZ2s[(row + r) * ldh + col] = d[r];
+        a.dZ2f[((int64_t)e * B + r0 + row + r) * H + col] = dz;
+      }
+      column(a.dZ2T, H, col, row, d);
+    });
+    lds_barrier();
+    rows_mm<MT, NT, W, PRE>(wa, dZ2s, ldh, Pb + a.L.W2, H, H, [] {}, [=](int row, int col, f32x4 v) {
+      bf16x4 d;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const float dz = v[r] * silu_grad(Z1[(row + r) * ldz + col]);
+        d[r] = (__bf16)dz;
+        a.dZ1f[((int64_t)e * B + r0 + row + r) * H + col] = dz;
+      }
+      column(a.dZ1T, H, col, row, d);
+    });
+  }
+}
+
+namespace {
+
+struct SgGrads {
+  int B, H, O;
+  SgLayout L;
+  const __bf16 *XT, *H1T, *H2T, *dYT, *dZ2T, *dZ1T;
+  const float *dYf, *dZ2f, *dZ1f, *row_se;
+  float *P, *G, *M, *V, *loss;
+  __bf16 *Pb, *PbT;
+  AdamArgs adam;
+  int blk_w, blk_b;  // blocks of weight tiles, then of bias columns, then one for the loss
+};
+
+constexpr int SG_S = 4, SG_D = 3;  // weight gradients: k steps per set, sets in flight
+// bias columns of one block
+constexpr int SG_BIAS_COLS = 16;
+
+// Sum over rows of 16 columns of D[B][N] and the bias update.  Rows are taken
+// in chunks of SG_COLSUM_ROWS, a chunk in four interleaved phases: lane 16 g + j
+// adds phase g of column j, a wave per chunk; phases, then chunks, in order.
+__device__ __forceinline__ void bias_step(const SgGrads& a, int e, const float* __restrict__ D, int N, int col0,
+                                          int64_t off) {
+  __shared__ float s_part[4][SG_BIAS_COLS];
+  const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int j = l & 15, g = l >> 4;
+  const int n_chunks = (a.B + SG_COLSUM_ROWS - 1) / SG_COLSUM_ROWS;
+  const float* src = D + (int64_t)e * a.B * N + col0 + j;
+  const int64_t o = e * a.L.n_params + off + col0 + j;
+  const float p_ = a.P[o];  // the optimiser state, loaded ahead of the sums
+  float m_ = a.M[o], v_ = a.V[o], sum = 0.f;
+  for (int c0 = 0; c0 < n_chunks; c0 += 4) {
+    const int r0 = (c0 + w) * SG_COLSUM_ROWS, r1 = min(a.B, r0 + SG_COLSUM_ROWS);
+    float p = 0.f;
+    constexpr int U = SG_COLSUM_ROWS / 4;
+    float v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u] = src[(int64_t)min(r0 + g + 4 * u, a.B - 1) * N];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (r0 + g + 4 * u < r1) p += v[u];
+    const float p0 = __shfl(p, j, 64), p1 = __shfl(p, j + 16, 64), p2 = __shfl(p, j + 32, 64),
+                p3 = __shfl(p, j + 48, 64);
+    if (l < SG_BIAS_COLS) s_part[w][j] = ((p0 + p1) + p2) + p3;
+    __syncthreads();
+    for (int c = 0; c < min(4, n_chunks - c0); ++c) sum += s_part[c][j];
+    __syncthreads();
+  }
+  if (threadIdx.x >= SG_BIAS_COLS) return;
+  a.P[o] = adam(a.adam, sum, p_, &m_, &v_);
+  a.M[o] = m_;
+  a.V[o] = v_;
+  a.G[o] = sum;
+}
+
+}  // namespace
+
+// Weight gradients dW[i][j] = sum_b AT[i][b] DT[j][b] and the parameters'
+// Adam step.  A wave makes a 16 x 32 tile, all operands in registers (8 k steps
+// of 16-byte loads in flight); bias columns and the loss have blocks of their
+// own in the same launch.
+__global__ void __launch_bounds__(256) k_sg_grads(SgGrads a) {
+  const int e = blockIdx.y, H = a.H, O = a.O, B = a.B;
+  int b = blockIdx.x;
+  if (b >= a.blk_w) {
+    b -= a.blk_w;
+    if (b < a.blk_b) {
+      const int nh = H / SG_BIAS_COLS;
+      if (b < nh) bias_step(a, e, a.dZ1f, H, b * SG_BIAS_COLS, a.L.b1);
+      else if (b < 2 * nh) bias_step(a, e, a.dZ2f, H, (b - nh) * SG_BIAS_COLS, a.L.b2);
+      else bias_step(a, e, a.dYf, O, (b - 2 * nh) * SG_BIAS_COLS, a.L.b3);
+    } else {
+      loss_block(B, O, a.row_se, a.loss, e);
+    }
+    return;
+  }
+  const int l = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  int t = 4 * b + w;  // wave tile: W2, then W3, then W1
+  const int n2 = (H / 16) * (H / 32), n3 = (H / 16) * (O / 32), n1 = (SG_K0 / 16) * (H / 32);
+  const __bf16 *AT, *DT;
+  int M, N;
+  int64_t off;
+  if (t < n2) {
+    AT = a.H1T + (int64_t)e * H * B, DT = a.dZ2T + (int64_t)e * H * B, M = H, N = H, off = a.L.W2;
+  } else if (t < n2 + n3) {
+    t -= n2;
+    AT = a.H2T + (int64_t)e * H * B, DT = a.dYT + (int64_t)e * O * B, M = H, N = O, off = a.L.W3;
+  } else if (t < n2 + n3 + n1) {
+    t -= n2 + n3;
+    AT = a.XT, DT = a.dZ1T + (int64_t)e * H * B, M = SG_K0, N = H, off = a.L.W1;
+  } else {
+    return;
+  }
+  const int i0 = 16 * (t / (N / 32)), j0 = 32 * (t % (N / 32));
+  const int c = l & 15, q = 4 * (l >> 4);
+  const __bf16* ap = AT + (int64_t)i0 * B + 8 * l;
+  const __bf16* dp = DT + (int64_t)j0 * B + 8 * l;
+  // the optimiser state of the tile, loaded before the product
+  const int64_t base = e * a.L.n_params + off;
+  float p_[2][4], m_[2][4], v_[2][4];
+#pragma unroll
+  for (int n = 0; n < 2; ++n)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int64_t o = base + (int64_t)(i0 + q + r) * N + j0 + 16 * n + c;
+      p_[n][r] = a.P[o];
+      m_[n][r] = a.M[o];
+      v_[n][r] = a.V[o];
+    }
+  f32x4 acc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+  // a ring of SG_D sets of SG_S k steps (past the batch the last step again)
+  struct Set {
+    bf16x8 a[SG_S], d[SG_S][2];
+  };
+  auto load = [&](Set& o, int k0) {
+#pragma unroll
+    for (int s = 0; s < SG_S; ++s) {
+      const int64_t k = 16 * (int64_t)min(k0 + 32 * s, B - 32);
+      o.a[s] = *reinterpret_cast<const bf16x8*>(ap + k);
+      o.d[s][0] = *reinterpret_cast<const bf16x8*>(dp + k);
+      o.d[s][1] = *reinterpret_cast<const bf16x8*>(dp + (int64_t)16 * B + k);
+    }
+  };
+  Set o[SG_D];
+#pragma unroll
+  for (int d = 0; d + 1 < SG_D; ++d) load(o[d], 32 * SG_S * d);
+  for (int k0 = 0; k0 < B; k0 += 32 * SG_S * SG_D) {
+#pragma unroll
+    for (int d = 0; d < SG_D; ++d) {
+      load(o[(d + SG_D - 1) % SG_D], k0 + 32 * SG_S * (d + SG_D - 1));
+#pragma unroll
+      for (int s = 0; s < SG_S; ++s) {
+        if (k0 + 32 * (SG_S * d + s) >= B) break;
+        acc[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(o[d].a[s], o[d].d[s][0], acc[0], 0, 0, 0);
+        acc[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(o[d].a[s], o[d].d[s][1], acc[1], 0, 0, 0);
+      }
+    }
+  }
+#pragma unroll
+  for (int n = 0; n < 2; ++n) {
+    const int j = j0 + 16 * n + c;
+    bf16x4 pb;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int64_t o = base + (int64_t)(i0 + q + r) * N + j;
+      const float p = adam(a.adam, acc[n][r], p_[n][r], &m_[n][r], &v_[n][r]);
+      pb[r] = (__bf16)p;
+      a.G[o] = acc[n][r];
+      a.M[o] = m_[n][r];
+      a.V[o] = v_[n][r];
+      a.P[o] = p;
+      a.Pb[base + frag(i0 + q + r, j, N)] = pb[r];
+    }
+    *reinterpret_cast<bf16x4*>(a.PbT + base + frag(j, i0 + q, M)) = pb;
+  }
 }
 
 // ensemble mean of the outputs (members added in order)
@@ -542,25 +990,126 @@ hipError_t sg_backward(soap_surrogate* s, const float* target, int B) {
   return colsum(st, E, B, H, s->dZf2, sBH, s->colpart, s->G + L.b1, sP);
 }
 
-hipError_t sg_adam(soap_surrogate* s, float lr) {
+namespace {
+
+// the next step's constants
+AdamArgs next_adam(soap_surrogate* s, float lr) {
   s->step += 1;
   const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
-  const float c1 = 1.0f - powf(b1, (float)s->step), c2 = 1.0f - powf(b2, (float)s->step);
+  return AdamArgs{lr, b1, b2, eps, 1.0f - powf(b1, (float)s->step), 1.0f - powf(b2, (float)s->step)};
+}
+
+template <int MT, bool TRAIN>
+hipError_t launch_rows(soap_surrogate* s, const SgRows& a) {
+  const size_t lds = sg_rows_lds(16 * MT, a.H, a.O, TRAIN);
+  if (lds > 64 * 1024) {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_sg_rows<MT, TRAIN>),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL((k_sg_rows<MT, TRAIN>), dim3((unsigned)((a.B + 16 * MT - 1) / (16 * MT)), s->n_ens),
+                     dim3(64 * sr_waves(TRAIN)), lds, s->stream, a);
+  return hipGetLastError();
+}
+
+constexpr size_t SR_LDS = 160 * 1024;  // of a compute unit
+
+SgRows rows_args(soap_surrogate* s, const float* x, int B) {
+  SgRows a{};
+  a.B = B;
+  a.n_in = s->n_in;
+  a.H = s->hidden;
+  a.O = s->n_out;
+  a.L = s->lay;
+  a.x = x;
+  a.P = s->P;
+  a.Pb = s->Pb;
+  a.PbT = s->PbT;
+  return a;
+}
+
+}  // namespace
+
+// networks past about 740 (training) or 2200 (inference) hidden units keep the
+// general kernels
+bool sg_rows_fit(int hidden, int n_out, bool train) { return sg_rows_lds(16, hidden, n_out, train) <= SR_LDS; }
+
+// 32 rows a block when that leaves every compute unit two blocks, since each
+// block reads all weights (10000 rows, hidden 256, 128 outputs, 4 members: 34 us
+// against 56 with 16 rows and their weights loaded ahead, 36 without, 38 with 48
+// or 64 rows; three launches of the general kernels 66); else 16, to fill the
+// chip, and there the weights' latency counts
+hipError_t sg_rows_forward(soap_surrogate* s, const float* x, int B, float* Y) {
+  SgRows a = rows_args(s, x, B);
+  a.Y = Y;
+  const bool wide = (int64_t)B * s->n_ens >= 16 * SR_MT * 512 && 2 * sg_rows_lds(16 * SR_MT, a.H, a.O, false) <= SR_LDS;
+  return wide ? launch_rows<SR_MT, false>(s, a) : launch_rows<1, false>(s, a);
+}
+
+hipError_t sg_rows_step(soap_surrogate* s, const float* x, const float* target, int B, float lr) {
+  SgRows a = rows_args(s, x, B);
+  a.target = target;
+  a.XT = s->XT;
+  a.H1T = s->H1T;
+  a.H2T = s->H2T;
+  a.dYT = s->dYT;
+  a.dZ2T = s->dZ2T;
+  a.dZ1T = s->dZ1T;
+  a.dYf = s->dYf;
+  a.dZ2f = s->dZf;
+  a.dZ1f = s->dZf2;
+  a.row_se = s->row_se;
+  SG_TRY((launch_rows<1, true>(s, a)));
+  const int H = a.H, O = a.O;
+  SgGrads g{};
+  g.B = B;
+  g.H = H;
+  g.O = O;
+  g.L = s->lay;
+  g.XT = s->XT;
+  g.H1T = s->H1T;
+  g.H2T = s->H2T;
+  g.dYT = s->dYT;
+  g.dZ2T = s->dZ2T;
+  g.dZ1T = s->dZ1T;
+  g.dYf = s->dYf;
+  g.dZ2f = s->dZf;
+  g.dZ1f = s->dZf2;
+  g.row_se = s->row_se;
+  g.P = s->P;
+  g.G = s->G;
+  g.M = s->M;
+  g.V = s->V;
+  g.loss = s->loss;
+  g.Pb = s->Pb;
+  g.PbT = s->PbT;
+  g.adam = next_adam(s, lr);
+  const int tiles = (H / 16) * (H / 32) + (H / 16) * (O / 32) + (SG_K0 / 16) * (H / 32);
+  g.blk_w = (tiles + 3) / 4;
+  g.blk_b = (2 * H + O) / SG_BIAS_COLS;
+  hipLaunchKernelGGL(k_sg_grads, dim3((unsigned)(g.blk_w + g.blk_b + 1), s->n_ens), dim3(256), 0, s->stream, g);
+  return hipGetLastError();
+}
+
+hipError_t sg_adam(soap_surrogate* s, float lr) {
+  const AdamArgs a = next_adam(s, lr);
   const int64_t n = (int64_t)s->n_ens * s->lay.n_params;
-  hipLaunchKernelGGL(k_adam, blocks(n), dim3(256), 0, s->stream, n, lr, b1, b2, eps, c1, c2, s->P, s->G, s->M, s->V,
-                     s->Pb);
+  hipLaunchKernelGGL(k_adam, blocks(n), dim3(256), 0, s->stream, n, a, s->lay, s->hidden, s->n_out,
+                     sg_rows_fit(s->hidden, s->n_out, true) ? 1 : 0, s->P,
+                     s->G, s->M, s->V, s->Pb, s->PbT);
   return hipGetLastError();
 }
 
 hipError_t sg_sync_bf16(soap_surrogate* s) {
   const int64_t n = (int64_t)s->n_ens * s->lay.n_params;
-  hipLaunchKernelGGL(k_f32_to_bf16, blocks(n), dim3(256), 0, s->stream, n, s->P, s->Pb);
+  hipLaunchKernelGGL(k_f32_to_bf16, blocks(n), dim3(256), 0, s->stream, n, s->lay, s->hidden, s->n_out,
+                     sg_rows_fit(s->hidden, s->n_out, true) ? 1 : 0, s->P, s->Pb, s->PbT);
   return hipGetLastError();
 }
 
-hipError_t sg_ens_mean(soap_surrogate* s, int B, float* mean) {
+hipError_t sg_ens_mean(soap_surrogate* s, int B, const float* Y, float* mean) {
   const int64_t n = (int64_t)B * s->n_out;
-  hipLaunchKernelGGL(k_ens_mean, blocks(n), dim3(256), 0, s->stream, n, s->n_ens, s->Y, mean);
+  hipLaunchKernelGGL(k_ens_mean, blocks(n), dim3(256), 0, s->stream, n, s->n_ens, Y, mean);
   return hipGetLastError();
 }
 

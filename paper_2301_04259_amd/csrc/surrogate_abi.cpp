@@ -104,14 +104,42 @@ hipError_t alloc(T*& p, size_t n) {
 }
 
 void free_all(soap_surrogate* s) {
-  void* ps[] = {s->P, s->G, s->M, s->V, s->Pb, s->X, s->Z1, s->Z2, s->H1, s->H2, s->Y, s->dY, s->dYf,
+  void* ps[] = {s->P, s->G, s->M, s->V, s->Pb, s->PbT, s->XT, s->H1T, s->H2T, s->dYT, s->dZ2T, s->dZ1T, s->X, s->Z1, s->Z2, s->H1, s->H2, s->Y, s->dY, s->dYf,
                 s->dZf, s->dZf2, s->dZb, s->dZb2, s->row_se, s->loss, s->colpart};
   for (void* p : ps)
     if (p) (void)soap::dev_free(p);
 }
 
+soap_status ensure_y(soap_surrogate* s, int B) {
+  if (B <= s->cap_y) return SOAP_OK;
+  SG_HIP(hipStreamSynchronize(s->stream));
+  s->cap_y = 0;
+  SG_HIP(alloc(s->Y, (size_t)s->n_ens * B * s->n_out));
+  s->cap_y = B;
+  return SOAP_OK;
+}
+
+// training buffers of the row kernels
+soap_status ensure_rows(soap_surrogate* s, int B) {
+  if (B <= s->cap_rows) return SOAP_OK;
+  SG_HIP(hipStreamSynchronize(s->stream));
+  s->cap_rows = 0;
+  const size_t E = s->n_ens, H = s->hidden, O = s->n_out;
+  SG_HIP(alloc(s->XT, (size_t)B * soap::SG_K0));
+  for (__bf16** p : {&s->H1T, &s->H2T, &s->dZ2T, &s->dZ1T}) SG_HIP(alloc(*p, E * B * H));
+  SG_HIP(alloc(s->dYT, E * B * O));
+  SG_HIP(alloc(s->dYf, E * B * O));
+  SG_HIP(alloc(s->dZf, E * B * H));
+  SG_HIP(alloc(s->dZf2, E * B * H));
+  SG_HIP(alloc(s->row_se, E * B));
+  s->cap_rows = B;
+  return SOAP_OK;
+}
+
+// buffers of the general kernels
 soap_status ensure_batch(soap_surrogate* s, int B) {
   if (B <= s->cap) return SOAP_OK;
+  s->cap = 0;
   SG_HIP(hipStreamSynchronize(s->stream));
   const size_t E = s->n_ens, H = s->hidden, O = s->n_out;
   SG_HIP(alloc(s->X, (size_t)B * soap::SG_K0));
@@ -119,7 +147,10 @@ soap_status ensure_batch(soap_surrogate* s, int B) {
   SG_HIP(alloc(s->Z2, E * B * H));
   SG_HIP(alloc(s->H1, E * B * H));
   SG_HIP(alloc(s->H2, E * B * H));
-  SG_HIP(alloc(s->Y, E * B * O));
+  {
+    const soap_status st = ensure_y(s, B);
+    if (st != SOAP_OK) return st;
+  }
   SG_HIP(alloc(s->dY, E * B * O));
   SG_HIP(alloc(s->dYf, E * B * O));
   SG_HIP(alloc(s->dZf, E * B * H));
@@ -166,7 +197,8 @@ SOAP_API soap_status soap_surrogate_create(int32_t n_in, int32_t hidden, int32_t
   if (hipGetDevice(&s->device) != hipSuccess) return fail(SOAP_ERR_HIP);
   const size_t np = (size_t)n_ensemble * L.n_params;
   if (alloc(s->P, np) != hipSuccess || alloc(s->G, np) != hipSuccess || alloc(s->M, np) != hipSuccess ||
-      alloc(s->V, np) != hipSuccess || alloc(s->Pb, np) != hipSuccess || alloc(s->loss, n_ensemble) != hipSuccess)
+      alloc(s->V, np) != hipSuccess || alloc(s->Pb, np) != hipSuccess ||
+      alloc(s->PbT, np) != hipSuccess || alloc(s->loss, n_ensemble) != hipSuccess)
     return fail(SOAP_ERR_OOM);
   // Glorot-uniform weights from the seeded generator (one stream per
   // member), zero biases
@@ -200,11 +232,17 @@ SOAP_API soap_status soap_surrogate_train_step(soap_surrogate* s, const float* x
   SG_ARG(x_dev && y_dev, "x and y must be device arrays");
   SG_ARG(batch >= 32 && batch % 32 == 0 && batch <= (1 << 20), "batch must be a multiple of 32 in [32, 2^20]");
   SG_ARG(std::isfinite(lr) && lr > 0.f, "lr must be > 0");
-  soap_status st = ensure_batch(s, batch);
-  if (st != SOAP_OK) return st;
-  SG_HIP(soap::sg_forward(s, x_dev, batch));
-  SG_HIP(soap::sg_backward(s, y_dev, batch));
-  SG_HIP(soap::sg_adam(s, lr));
+  if (soap::sg_rows_fit(s->hidden, s->n_out, true)) {
+    soap_status st = ensure_rows(s, batch);
+    if (st != SOAP_OK) return st;
+    SG_HIP(soap::sg_rows_step(s, x_dev, y_dev, batch, lr));
+  } else {
+    soap_status st = ensure_batch(s, batch);
+    if (st != SOAP_OK) return st;
+    SG_HIP(soap::sg_forward(s, x_dev, batch));
+    SG_HIP(soap::sg_backward(s, y_dev, batch));
+    SG_HIP(soap::sg_adam(s, lr));
+  }
   if (loss_out) {
     std::vector<float> l(s->n_ens);
     SG_HIP(hipStreamSynchronize(s->stream));
@@ -221,10 +259,21 @@ SOAP_API soap_status soap_surrogate_predict(soap_surrogate* s, const float* x_de
   if (!s) return SOAP_ERR_ARG;
   SG_ARG(x_dev && coef_dev, "x and coef must be device arrays");
   SG_ARG(batch >= 16 && batch % 16 == 0 && batch <= (1 << 20), "batch must be a multiple of 16 in [16, 2^20]");
+  if (soap::sg_rows_fit(s->hidden, s->n_out, false)) {
+    float* Y = members_dev;
+    if (!Y) {
+      soap_status st = ensure_y(s, batch);
+      if (st != SOAP_OK) return st;
+      Y = s->Y;
+    }
+    SG_HIP(soap::sg_rows_forward(s, x_dev, batch, Y));
+    SG_HIP(soap::sg_ens_mean(s, batch, Y, coef_dev));
+    return SOAP_OK;
+  }
   soap_status st = ensure_batch(s, batch);
   if (st != SOAP_OK) return st;
   SG_HIP(soap::sg_forward(s, x_dev, batch));
-  SG_HIP(soap::sg_ens_mean(s, batch, coef_dev));
+  SG_HIP(soap::sg_ens_mean(s, batch, s->Y, coef_dev));
   if (members_dev)
     SG_HIP(hipMemcpyAsync(members_dev, s->Y, sizeof(float) * (size_t)s->n_ens * batch * s->n_out,
                           hipMemcpyDeviceToDevice, s->stream));

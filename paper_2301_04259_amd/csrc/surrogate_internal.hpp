@@ -13,7 +13,7 @@ namespace soap {
 constexpr int SG_K0 = 32;            // input width padded to one MFMA K step
 constexpr int SG_RAW = 8;            // raw sample description (soap_surrogate_features)
 constexpr int SG_FEATURES = 12;      // network inputs made from it
-constexpr int SG_COLSUM_ROWS = 128;  // rows per partial column sum
+constexpr int SG_COLSUM_ROWS = 128;  // rows per partial column sum, taken in 4 interleaved phases
 
 enum { MM_PLAIN = 0, MM_HIDDEN = 1, MM_OUTPUT = 2, MM_DHIDDEN = 3 };
 
@@ -37,9 +37,19 @@ struct soap_surrogate {
   float* G = nullptr;
   float* M = nullptr;
   float* V = nullptr;
+  // BF16 copies of the weight matrices at the same offsets: transposed in
+  // fragment order, and in fragment order (networks that train with the row
+  // kernels) or as they lie
   __bf16* Pb = nullptr;
-  // per-batch activations (grown on demand)
-  int cap = 0;  // rows the buffers hold
+  __bf16* PbT = nullptr;
+  // per-batch activations (grown on demand).  Networks that sg_rows_fit uses
+  // the row kernels: the six matrices of the weight gradients, transposed, in
+  // fragment order, and the FP32 terms of the bias gradients
+  int cap_rows = 0;  // training rows these hold
+  __bf16 *XT = nullptr, *H1T = nullptr, *H2T = nullptr, *dYT = nullptr, *dZ2T = nullptr, *dZ1T = nullptr;
+  int cap_y = 0;     // rows that Y holds
+  // wider networks: every layer's activations
+  int cap = 0;       // rows the buffers hold
   __bf16* X = nullptr;                // [cap][SG_K0]
   float *Z1 = nullptr, *Z2 = nullptr;  // [E][cap][H]
   __bf16 *H1 = nullptr, *H2 = nullptr;
@@ -57,8 +67,14 @@ namespace soap {
 hipError_t sg_forward(soap_surrogate* s, const float* x, int B);
 hipError_t sg_backward(soap_surrogate* s, const float* target, int B);
 hipError_t sg_adam(soap_surrogate* s, float lr);
+// whether the rows of a block and their activations fit in LDS
+bool sg_rows_fit(int hidden, int n_out, bool train);
+// outputs of every member to Y[n_ens][B][n_out] (row kernel)
+hipError_t sg_rows_forward(soap_surrogate* s, const float* x, int B, float* Y);
+// one Adam step (row kernel, then weight gradients and update)
+hipError_t sg_rows_step(soap_surrogate* s, const float* x, const float* target, int B, float lr);
 hipError_t sg_sync_bf16(soap_surrogate* s);
-hipError_t sg_ens_mean(soap_surrogate* s, int B, float* mean);
+hipError_t sg_ens_mean(soap_surrogate* s, int B, const float* Y, float* mean);
 hipError_t sg_gate(hipStream_t st, const soap_rv* rv, int64_t n, int E, double calib, double thr, double* rv_kms,
                    double* err_kms, int* fallback);
 // network inputs [n][SG_FEATURES] of raw sample descriptions [n][SG_RAW]
