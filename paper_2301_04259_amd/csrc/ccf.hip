@@ -1036,99 +1036,138 @@ __global__ void __launch_bounds__(256) k_ccf_linear(int64_t n, int k, int n_v, c
 
 constexpr int SG_MAX_ENS = 16;
 
-// samples per wave of k_sg_lin and k_sg_spread (they share every basis row
-// loaded) and basis rows in flight, by CCF points per lane
-template <int NPT>
-constexpr int sg_samples() {
-  return NPT <= 3 ? 4 : (NPT <= 6 ? 2 : 1);
-}
-template <int NPT>
-constexpr int sg_rows_in_flight() {
-  return NPT <= 3 ? 8 : (NPT <= 6 ? 4 : 2);
-}
-
-// Surrogate RVs and their gate in three launches (so that each keeps few
-// registers and many waves in flight):
+// Surrogate RVs and their gate in three launches:
 //   k_sg_lin: CCF of the ensemble-mean prediction by linearity, base (the
 //     sample's row base[base_idx[i]] when base_idx is given) + sum_k
-//     coef[i][k] basis[k] (double, increasing k: the same sums as
-//     k_ccf_linear), SS = sg_samples samples per wave sharing every basis
-//     row loaded;
+//     coef[i][k] basis[k];
 //   k_sg_fit: its Gaussian fit (fit_wave), one wave per sample (issue-bound:
-//     88 us per 1e4 samples with the fit's former 20 sums, 64 now), and the RV
+//     88 us per 1e4 samples with the fit's former 20 sums, 62 now), and the RV
 //     sensitivity g = J H^-1 e_mu at the fit: the fitted parameters move by
 //     dp = H^-1 J^T dy for a CCF change dy (H the Hessian of chi^2 / 2 at the
 //     fit, J the model Jacobian), so dRV = g . dy;
 //   k_sg_spread: each member's RV change dRV_e = sum_k h_k (y_e,k - coef_k)
-//     with h = basis g (dy_e = sum_k (y_e,k - coef_k) basis[k]), SS samples
-//     per wave; err = calib x the sample standard deviation of the dRV_e;
-//     fallback when err is not below thr or the fit did not converge.
-// Every sum of a sample keeps one fixed order.
+//     with h = basis g (dy_e = sum_k (y_e,k - coef_k) basis[k]); err = calib x
+//     the sample standard deviation of the dRV_e; fallback when err is not
+//     below thr or the fit did not converge.
+// The first and the last are matrix products in double, on the matrix cores
+// (v_mfma_f64_16x16x4_f64: lane l holds A(l % 16, l / 16) and B(l / 16, l % 16)
+// and ends with C(l / 16 + 4 r, l % 16), r < 4; step s of a group of 16 takes
+// the four terms 4 (l / 16) + s, so that a lane's operands of a group are
+// contiguous).  A block of SG_W waves takes 16 samples, each wave its share of
+// the columns.  Bound by the first-level cache, so the samples' operands pass
+// through LDS and the basis is read 16 bytes a lane.
+// 10000 samples, 128 components, 161 velocities: 19 and 26 us, against
+// 42 and 52 as vector FMAs with 4 samples a wave.  Every sum of a sample keeps
+// one fixed order.
+constexpr int SG_W = 4;
+constexpr int SG_KC = 128;  // components per LDS pass of k_sg_lin
+constexpr int SG_VC = 192;  // velocities per LDS pass of k_sg_spread
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+typedef double f64x2 __attribute__((ext_vector_type(2)));
+typedef double f64x2u __attribute__((ext_vector_type(2), aligned(8)));
+
+// NPT column tiles per wave: SG_W NPT 16 = 64 NPT columns
 template <int NPT>
-__global__ void __launch_bounds__(64) k_sg_lin(int64_t n, int k, int n_v, const float* __restrict__ coef,
-                                               const double* __restrict__ base, const int* __restrict__ base_idx,
-                                               int n_base, const double* __restrict__ basis,
-                                               double* __restrict__ Y, int* __restrict__ flag) {
-  constexpr int SS = sg_samples<NPT>();
-  constexpr int JU = sg_rows_in_flight<NPT>();
-  __shared__ double s_c[SS][64];
-  const int lane = threadIdx.x;
-  const int64_t i0 = (int64_t)blockIdx.x * SS;
-  // Loads are unconditional, with indices clamped into the rows (lanes past
-  // the grid and samples past n compute values that are never stored): a
-  // load under a branch is waited for before the next one is issued.  A
-  // sample whose star row does not exist reads row 0 and is flagged.
-  int64_t ii[SS];
-  bool row_ok[SS];
-  const double* bs[SS];
+__global__ void __launch_bounds__(64 * SG_W, NPT <= 3 ? 3 : 1) k_sg_lin(int64_t n, int k, int n_v, const float* __restrict__ coef,
+                                                      const double* __restrict__ base,
+                                                      const int* __restrict__ base_idx, int n_base,
+                                                      const double* __restrict__ basis, double* __restrict__ Y,
+                                                      int* __restrict__ flag) {
+  __shared__ float s_a[16][SG_KC + 4];
+  const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int c = l & 15, g = l >> 4;
+  const int64_t i0 = (int64_t)blockIdx.x * 16;
+  // The wave's columns: pairs of tiles take every other one of 32, so that a
+  // lane loads two at once, an odd last tile takes 16.  Loads are
+  // unconditional, with indices clamped into the rows (columns past the grid
+  // and samples past n compute values that are never stored): a load under a
+  // branch is waited for before the next one is issued.  A sample whose star
+  // row does not exist reads row 0 and is flagged.
+  constexpr int PAIRS = NPT / 2;
+  constexpr bool ODD = NPT % 2;
+  int col[NPT];
 #pragma unroll
-  for (int s = 0; s < SS; ++s) {
-    ii[s] = min(i0 + s, n - 1);
-    const int brow = base_idx ? base_idx[ii[s]] : 0;
-    row_ok[s] = brow >= 0 && brow < n_base;
-    bs[s] = base + (int64_t)(row_ok[s] ? brow : 0) * n_v;
+  for (int t = 0; t < NPT; ++t) col[t] = 16 * NPT * w + (t < 2 * PAIRS ? 32 * (t / 2) + 2 * c + t % 2 : 16 * t + c);
+  struct Set {
+    f64x2u p[4][PAIRS > 0 ? PAIRS : 1];
+    double b[4];
+  };
+  auto load = [&](Set& o, int k0) {
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const double* bj = basis + (int64_t)min(k0 + 4 * s + g, k - 1) * n_v;
+#pragma unroll
+      for (int q = 0; q < PAIRS; ++q) o.p[s][q] = *reinterpret_cast<const f64x2u*>(bj + min(col[2 * q], n_v - 2));
+      if constexpr (ODD) o.b[s] = bj[min(col[NPT - 1], n_v - 1)];
+    }
+  };
+  auto column = [&](const Set& o, int s, int t) {  // a pair that starts in the last column has it as its second
+    if (t < 2 * PAIRS) return t % 2 || col[t] == n_v - 1 ? o.p[s][t / 2][1] : o.p[s][t / 2][0];
+    return o.b[s];
+  };
+  constexpr int D = NPT <= 4 ? 3 : 2;  // groups in flight
+  Set o[D];
+#pragma unroll
+  for (int d = 0; d + 1 < D; ++d) load(o[d], 16 * d);
+  // the sums start at the samples' base rows; every row index is loaded before
+  // the first is used, and every base value has arrived before the loop (which
+  // would wait for all its loads in each turn otherwise)
+  int brow[4] = {0, 0, 0, 0};
+  if (base_idx) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) brow[r] = base_idx[min(i0 + g + 4 * r, n - 1)];
   }
-  int vc[NPT];
+  f64x4 acc[NPT];
 #pragma unroll
-  for (int t = 0; t < NPT; ++t) vc[t] = min(lane + 64 * t, n_v - 1);
-  double y[SS][NPT];
+  for (int r = 0; r < 4; ++r) {
+    const double* b = base + (int64_t)(brow[r] >= 0 && brow[r] < n_base ? brow[r] : 0) * n_v;
 #pragma unroll
-  for (int s = 0; s < SS; ++s)
+    for (int t = 0; t < NPT; ++t) acc[t][r] = b[min(col[t], n_v - 1)];
+  }
 #pragma unroll
-    for (int t = 0; t < NPT; ++t) y[s][t] = bs[s][vc[t]];
-  for (int k0 = 0; k0 < k; k0 += 64) {
+  for (int t = 0; t < NPT; ++t) asm volatile("" : "+v"(acc[t]));
+  for (int kc = 0; kc < k; kc += SG_KC) {  // the coefficients pass through LDS
+    const int kn = min(SG_KC, k - kc);
+    if (kc) {
+      __syncthreads();
+#pragma unroll
+      for (int d = 0; d + 1 < D; ++d) load(o[d], kc + 16 * d);
+    }
+    constexpr int U = 16 * SG_KC / (64 * SG_W);
+    float x[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int t = threadIdx.x + 64 * SG_W * u;
+      x[u] = coef[min(i0 + t / SG_KC, n - 1) * k + kc + min(t % SG_KC, kn - 1)];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int t = threadIdx.x + 64 * SG_W * u;
+      s_a[t / SG_KC][t % SG_KC] = t % SG_KC < kn ? x[u] : 0.f;  // rows past k add zero
+    }
     __syncthreads();
+    for (int k0 = 0; k0 < kn; k0 += 16 * D) {
 #pragma unroll
-    for (int s = 0; s < SS; ++s) s_c[s][lane] = k0 + lane < k ? (double)coef[ii[s] * k + min(k0 + lane, k - 1)] : 0.0;
-    __syncthreads();
-    const int kn = min(64, k - k0);
-    for (int j0 = 0; j0 < kn; j0 += JU) {
-      double b[JU][NPT];
+      for (int d = 0; d < D; ++d) {
+        load(o[(d + D - 1) % D], kc + k0 + 16 * (d + D - 1));
+        if (k0 + 16 * d >= kn) continue;
 #pragma unroll
-      for (int u = 0; u < JU; ++u) {
-        const double* bj = basis + (int64_t)(k0 + min(j0 + u, kn - 1)) * n_v;
+        for (int s = 0; s < 4; ++s) {
+          const double a = (double)s_a[c][k0 + 16 * d + 4 * s + g];
 #pragma unroll
-        for (int t = 0; t < NPT; ++t) b[u][t] = bj[vc[t]];
-      }
-#pragma unroll
-      for (int u = 0; u < JU; ++u)
-#pragma unroll
-        for (int s = 0; s < SS; ++s) {
-          const double cj = j0 + u < kn ? s_c[s][j0 + u] : 0.0;  // rows past kn add zero
-#pragma unroll
-          for (int t = 0; t < NPT; ++t) y[s][t] = fma(cj, b[u][t], y[s][t]);
+          for (int t = 0; t < NPT; ++t)
+            acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, column(o[d], s, t), acc[t], 0, 0, 0);
         }
+      }
     }
   }
 #pragma unroll
-  for (int s = 0; s < SS; ++s) {
-    if (i0 + s >= n) break;
+  for (int r = 0; r < 4; ++r) {
+    const int64_t i = i0 + g + 4 * r;
+    if (w == 0 && c == 0 && i < n) flag[i] = brow[r] >= 0 && brow[r] < n_base ? 0 : 1;
 #pragma unroll
-    for (int t = 0; t < NPT; ++t) {
-      const int v = lane + 64 * t;
-      if (v < n_v) Y[(i0 + s) * n_v + v] = y[s][t];
-    }
-    if (lane == 0) flag[i0 + s] = row_ok[s] ? 0 : 1;
+    for (int t = 0; t < NPT; ++t)
+      if (i < n && col[t] < n_v) Y[i * n_v + col[t]] = acc[t][r];
   }
 }
 
@@ -1176,98 +1215,144 @@ __global__ void __launch_bounds__(64) k_sg_fit(int64_t n, int n_v, double v0, do
   }
 }
 
-template <int NPT, int EB>
-__global__ void __launch_bounds__(64) k_sg_spread(int64_t n, int k, int E, int n_v, const float* __restrict__ coef,
-                                                  const float* __restrict__ members,
-                                                  const double* __restrict__ basis, const double* __restrict__ G,
-                                                  const int* __restrict__ flag, double calib, double thr,
-                                                  double* __restrict__ err_kms, int* __restrict__ fallback) {
-  constexpr int SS = sg_samples<NPT>();
-  __shared__ double s_g[SS][NPT * 64];
-  const int lane = threadIdx.x;
-  const int64_t i0 = (int64_t)blockIdx.x * SS;
-  int64_t ii[SS];
-  bool bad[SS];
+// EB: members, rounded up; 32 components per wave at a time
+template <int EB>
+__global__ void __launch_bounds__(64 * SG_W) k_sg_spread(int64_t n, int k, int E, int n_v,
+                                                         const float* __restrict__ coef,
+                                                         const float* __restrict__ members,
+                                                         const double* __restrict__ basis,
+                                                         const double* __restrict__ G, const int* __restrict__ flag,
+                                                         double calib, double thr, double* __restrict__ err_kms,
+                                                         int* __restrict__ fallback) {
+  constexpr int NT = 2;
+  __shared__ double s_dr[SG_W][16][EB];
+  __shared__ __align__(16) double s_g[16][SG_VC + 2];
+  const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int c = l & 15, g = l >> 4;
+  const int64_t i0 = (int64_t)blockIdx.x * 16;
+  double dr[4][EB];
 #pragma unroll
-  for (int s = 0; s < SS; ++s) {
-    ii[s] = min(i0 + s, n - 1);
-    bad[s] = flag[ii[s]] != 0;
+  for (int r = 0; r < 4; ++r)
 #pragma unroll
-    for (int t = 0; t < NPT; ++t) {
-      const int v = lane + 64 * t;
-      if (v < n_v) s_g[s][v] = G[ii[s] * n_v + v];
-    }
-  }
-  __syncthreads();
+    for (int e = 0; e < EB; ++e) dr[r][e] = 0.0;
   // h_k = sum_v basis[k][v] g_v, then dRV_e = sum_k h_k (y_e,k - coef_k)
-  double dr[SS][EB];
+  for (int kb = 0; kb < k; kb += 16 * NT * SG_W) {
+    const int k0 = kb + 16 * NT * w;  // waves past k multiply the last row and add nothing
+    const double* bp[NT];
 #pragma unroll
-  for (int s = 0; s < SS; ++s)
+    for (int t = 0; t < NT; ++t) bp[t] = basis + (int64_t)min(k0 + 16 * t + c, k - 1) * n_v;
+    f64x4 h[NT];
 #pragma unroll
-    for (int e = 0; e < EB; ++e) dr[s][e] = 0.0;
-  for (int k0 = 0; k0 < k; k0 += 64) {
-    const int kk = k0 + lane;
-    const int kc = min(kk, k - 1);
-    const double* bk = basis + (int64_t)kc * n_v;
-    // four partial sums over v per sample (16 samples of the row in flight),
-    // added in a fixed order
-    double h4[SS][4];
+    for (int t = 0; t < NT; ++t) h[t] = f64x4{0.0, 0.0, 0.0, 0.0};
+    struct Set {
+      f64x2u b[NT][2];
+    };
+    auto load = [&](Set& o, int v) {  // the lane's four velocities of a group of 16
 #pragma unroll
-    for (int s = 0; s < SS; ++s)
+      for (int q = 0; q < 2; ++q)
 #pragma unroll
-      for (int q = 0; q < 4; ++q) h4[s][q] = 0.0;
-    int v = 0;
-    for (; v + 16 <= n_v; v += 16) {
-      double bv[16];
+        for (int t = 0; t < NT; ++t) o.b[t][q] = *reinterpret_cast<const f64x2u*>(bp[t] + v + 4 * g + 2 * q);
+    };
+    auto multiply = [&](const Set& o, int v) {
 #pragma unroll
-      for (int u = 0; u < 16; ++u) bv[u] = bk[v + u];
+      for (int q = 0; q < 2; ++q) {
+        const f64x2 a = *reinterpret_cast<const f64x2*>(&s_g[c][v + 4 * g + 2 * q]);
 #pragma unroll
-      for (int s = 0; s < SS; ++s)
+        for (int x = 0; x < 2; ++x)
 #pragma unroll
-        for (int u = 0; u < 16; ++u) h4[s][u & 3] = fma(bv[u], s_g[s][v + u], h4[s][u & 3]);
+          for (int t = 0; t < NT; ++t)
+            h[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[x], o.b[t][q][x], h[t], 0, 0, 0);
+      }
+    };
+    for (int vc = 0; vc < n_v; vc += SG_VC) {  // the sensitivities pass through LDS, zeros past the grid
+      const int vn = min(SG_VC, n_v - vc), whole = vn & ~15;
+      constexpr int D = 3;  // groups in flight; past the last whole one it is read again
+      Set o[D];
+      if (whole) {
+#pragma unroll
+        for (int d = 0; d + 1 < D; ++d) load(o[d], vc + min(16 * d, whole - 16));
+      }
+      if ((kb == 0 && vc == 0) || n_v > SG_VC) {
+        if (kb || vc) __syncthreads();
+        constexpr int U = 16 * SG_VC / (64 * SG_W);
+        double x[U];  // all loads before the first is waited for
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int t = threadIdx.x + 64 * SG_W * u;
+          x[u] = G[min(i0 + t / SG_VC, n - 1) * n_v + vc + min(t % SG_VC, vn - 1)];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int t = threadIdx.x + 64 * SG_W * u;
+          s_g[t / SG_VC][t % SG_VC] = t % SG_VC < vn ? x[u] : 0.0;
+        }
+        __syncthreads();
+      }
+      for (int v = 0; v < whole; v += 16 * D) {
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+          load(o[(d + D - 1) % D], vc + min(v + 16 * (d + D - 1), whole - 16));
+          if (v + 16 * d < whole) multiply(o[d], v + 16 * d);
+        }
+      }
+      if (whole < vn) {
+        Set e;
+#pragma unroll
+        for (int x = 0; x < 4; ++x) {
+          const int v = whole + 4 * g + x;
+#pragma unroll
+          for (int t = 0; t < NT; ++t) e.b[t][x >> 1][x & 1] = v < vn ? bp[t][vc + min(v, vn - 1)] : 0.0;
+        }
+        multiply(e, whole);
+      }
     }
-    for (; v < n_v; ++v) {
-      const double bvv = bk[v];
 #pragma unroll
-      for (int s = 0; s < SS; ++s) h4[s][0] = fma(bvv, s_g[s][v], h4[s][0]);
-    }
+    for (int r = 0; r < 4; ++r) {
+      const int64_t i = min(i0 + g + 4 * r, n - 1);
 #pragma unroll
-    for (int s = 0; s < SS; ++s) {
-      const double h = kk < k ? (h4[s][0] + h4[s][1]) + (h4[s][2] + h4[s][3]) : 0.0;
-      const double cm = (double)coef[ii[s] * k + kc];
+      for (int t = 0; t < NT; ++t) {
+        const int kc = min(k0 + 16 * t + c, k - 1);
+        const double hk = k0 + 16 * t + c < k ? h[t][r] : 0.0;
+        const double cm = (double)coef[i * k + kc];
 #pragma unroll
-      for (int e = 0; e < EB; ++e) {
-        if (e < E) {
-          const double ye = (double)members[((int64_t)e * n + ii[s]) * k + kc];
-          dr[s][e] += h * (ye - cm);
+        for (int e = 0; e < EB; ++e) {
+          const double ye = (double)members[((int64_t)min(e, E - 1) * n + i) * k + kc];
+          dr[r][e] += hk * (ye - cm);
         }
       }
     }
   }
+  // sums over the 16 lanes of a sample's components, then over the waves
 #pragma unroll
-  for (int s = 0; s < SS; ++s) {
-    double err = 0.0;
-    if (!bad[s]) {
-      double m = 0.0;
+  for (int r = 0; r < 4; ++r)
 #pragma unroll
-      for (int e = 0; e < EB; ++e) {
-        if (e < E) {  // uniform
-          dr[s][e] = wave_sum_f64(dr[s][e]);
-          m += dr[s][e];
-        }
-      }
-      m /= (double)E;
-      double var = 0.0;
+    for (int e = 0; e < EB; ++e) {
+      double x = dr[r][e];
 #pragma unroll
-      for (int e = 0; e < EB; ++e)
-        if (e < E) var += (dr[s][e] - m) * (dr[s][e] - m);
-      err = calib * sqrt(var / (double)(E - 1));
+      for (int off = 1; off < 16; off *= 2) x += __shfl_xor(x, off, 64);
+      if (c == 0) s_dr[w][g + 4 * r][e] = x;
     }
-    if (lane == 0 && i0 + s < n) {
-      if (err_kms) err_kms[i0 + s] = bad[s] ? INFINITY : err;
-      fallback[i0 + s] = (bad[s] || !(err < thr)) ? 1 : 0;
+  __syncthreads();
+  const int s = threadIdx.x;
+  if (s >= 16 || i0 + s >= n) return;
+  const bool bad = flag[i0 + s] != 0;
+  double err = 0.0;
+  if (!bad) {
+    double d[EB], m = 0.0;
+#pragma unroll
+    for (int e = 0; e < EB; ++e) {
+      d[e] = (s_dr[0][s][e] + s_dr[1][s][e]) + (s_dr[2][s][e] + s_dr[3][s][e]);
+      if (e < E) m += d[e];
     }
+    m /= (double)E;
+    double var = 0.0;
+#pragma unroll
+    for (int e = 0; e < EB; ++e)
+      if (e < E) var += (d[e] - m) * (d[e] - m);
+    err = calib * sqrt(var / (double)(E - 1));
   }
+  if (err_kms) err_kms[i0 + s] = bad ? INFINITY : err;
+  fallback[i0 + s] = (bad || !(err < thr)) ? 1 : 0;
 }
 
 namespace {
@@ -1277,20 +1362,20 @@ void launch_sg_rv_n(soap_ctx* c, const float* d_coef, const float* d_members, in
                     const double* d_base, const int* d_base_idx, int n_base, const double* d_basis, double calib,
                     double thr, soap_rv* d_rv, double* d_rv_kms, double* d_err, int* d_fallback, double* Y,
                     double* G, int* flag) {
-  const dim3 grid_s((unsigned)((n + sg_samples<NPT>() - 1) / sg_samples<NPT>())), block(64);
+  const dim3 grid((unsigned)((n + 15) / 16)), block(64 * SG_W);
   const int nb = d_base_idx ? n_base : 1;
-  hipLaunchKernelGGL((k_sg_lin<NPT>), grid_s, block, 0, c->stream, n, k, c->mask_nv, d_coef, d_base, d_base_idx, nb,
-                     d_basis, Y, flag);
-  hipLaunchKernelGGL((k_sg_fit<NPT>), dim3((unsigned)n), block, 0, c->stream, n, c->mask_nv, c->mask_v0,
+  hipLaunchKernelGGL((k_sg_lin<NPT>), grid, block, 0, c->stream, n, k, c->mask_nv, d_coef, d_base,
+                     d_base_idx, nb, d_basis, Y, flag);
+  hipLaunchKernelGGL((k_sg_fit<NPT>), dim3((unsigned)n), dim3(64), 0, c->stream, n, c->mask_nv, c->mask_v0,
                      c->mask_dv, Y, flag, d_rv, d_rv_kms, G);
   if (E <= 4)
-    hipLaunchKernelGGL((k_sg_spread<NPT, 4>), grid_s, block, 0, c->stream, n, k, E, c->mask_nv, d_coef, d_members,
-                       d_basis, G, flag, calib, thr, d_err, d_fallback);
+    hipLaunchKernelGGL((k_sg_spread<4>), grid, block, 0, c->stream, n, k, E, c->mask_nv, d_coef, d_members, d_basis,
+                       G, flag, calib, thr, d_err, d_fallback);
   else if (E <= 8)
-    hipLaunchKernelGGL((k_sg_spread<NPT, 8>), grid_s, block, 0, c->stream, n, k, E, c->mask_nv, d_coef, d_members,
-                       d_basis, G, flag, calib, thr, d_err, d_fallback);
+    hipLaunchKernelGGL((k_sg_spread<8>), grid, block, 0, c->stream, n, k, E, c->mask_nv, d_coef, d_members, d_basis,
+                       G, flag, calib, thr, d_err, d_fallback);
   else
-    hipLaunchKernelGGL((k_sg_spread<NPT, SG_MAX_ENS>), grid_s, block, 0, c->stream, n, k, E, c->mask_nv, d_coef,
+    hipLaunchKernelGGL((k_sg_spread<SG_MAX_ENS>), grid, block, 0, c->stream, n, k, E, c->mask_nv, d_coef,
                        d_members, d_basis, G, flag, calib, thr, d_err, d_fallback);
 }
 
