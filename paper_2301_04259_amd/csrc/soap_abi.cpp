@@ -197,6 +197,21 @@ hipError_t upload_rows(soap_ctx* c, void* dst, const void* src, int n_rows, bool
   return ce;
 }
 
+// whether `bytes` at p lie in one allocation on the context's device: rows that
+// a kernel may copy (others go through the runtime's copy, which checks them)
+bool on_this_device(const soap_ctx* c, const void* p, size_t bytes) {
+  hipPointerAttribute_t at;
+  hipDeviceptr_t base = nullptr;
+  size_t size = 0;
+  if (hipPointerGetAttributes(&at, p) != hipSuccess || at.type != hipMemoryTypeDevice || at.device != c->device ||
+      hipMemGetAddressRange(&base, &size, const_cast<void*>(p)) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  const size_t off = static_cast<const unsigned char*>(p) - static_cast<const unsigned char*>(base);
+  return off <= size && bytes <= size - off;
+}
+
 // sum over the visible cells of (2/N)^2 |I(mu)|: bounds every tap and
 // column sum of the fixed-point accumulators
 double disk_weight(int N, double u1, double u2) {
@@ -279,13 +294,35 @@ soap_status init_impl(const soap_star_desc* d, soap_ctx* c) {
   c->Pstride = ((soap::PAD_FRONT + tail + 63) / 64) * 64;
   const size_t row_bytes = (size_t)c->Pstride * c->esize;
   const bool on_dev = d->spectra_on_device != 0;
+  // flags of non-finite values: [0] in rows, [1] in the quiet spectrum; read
+  // back with a blocking copy once the stream is idle
+  struct Flags {
+    int* p = nullptr;
+    ~Flags() {
+      if (p) (void)soap::dev_free(p);
+    }
+  } flags;
+  HIP_TRY(soap::dev_malloc((void**)&flags.p, 2 * sizeof(int)));
+  HIP_TRY(hipMemsetAsync(flags.p, 0, 2 * sizeof(int), c->stream));
+  const void* fill_src[3];
+  void* fill_base[3];
+  int n_fill = 0;
+  bool filled[3] = {false, false, false};
   for (int t = 0; t < 3; ++t) {
     if (!d->spectra[t]) continue;
     HIP_TRY(soap::dev_malloc(&c->d_spec_base[t], row_bytes * c->B));
     c->d_spec[t] = static_cast<unsigned char*>(c->d_spec_base[t]) + soap::PAD_FRONT * c->esize;
-    HIP_TRY(upload_rows(c, c->d_spec[t], d->spectra[t], c->B, on_dev));
+    filled[t] = on_dev && on_this_device(c, d->spectra[t], (size_t)c->P * c->esize * c->B);
+    if (filled[t]) {
+      fill_src[n_fill] = d->spectra[t];
+      fill_base[n_fill++] = c->d_spec_base[t];
+    } else {
+      HIP_TRY(upload_rows(c, c->d_spec[t], d->spectra[t], c->B, on_dev));
+      HIP_TRY(soap::launch_pad_rows(c, c->d_spec_base[t], c->B));
+    }
     c->has_type[t] = true;
   }
+  if (n_fill) HIP_TRY(soap::launch_fill_rows(c, fill_src, fill_base, n_fill, c->B, flags.p));
   HIP_TRY(soap::dev_malloc((void**)&c->d_mu, sizeof(double) * c->B));
   HIP_TRY(hipMemcpy(c->d_mu, d->mu_bins, sizeof(double) * c->B, hipMemcpyHostToDevice));
   HIP_TRY(soap::dev_malloc((void**)&c->d_col_c, sizeof(int) * c->N));
@@ -319,7 +356,6 @@ soap_status init_impl(const soap_star_desc* d, soap_ctx* c) {
     }
   }
   HIP_TRY(hipEventCreateWithFlags(&c->pinned_done, hipEventDisableTiming));
-  HIP_TRY(soap::launch_pad(c));
   HIP_TRY(soap::launch_geom(c));
   if (c->cmode == SOAP_CONTRAST_PLANCK) HIP_TRY(soap::launch_contrast(c));
   if (c->cmode == SOAP_CONTRAST_ARRAY) HIP_TRY(soap::launch_pad_rows(c, c->d_con_base, c->con_rows));
@@ -327,24 +363,15 @@ soap_status init_impl(const soap_star_desc* d, soap_ctx* c) {
   // the device copies must be finite: device inputs were not checked on the
   // host, and a host input that was finite there yet is not here means the
   // upload went wrong
-  // d_flag[0]: rows, d_flag[1]: quiet spectrum; read back with a blocking
-  // copy once the stream is idle
-  int* d_flag = nullptr;
-  HIP_TRY(soap::dev_malloc((void**)&d_flag, 2 * sizeof(int)));
   int h_flag[2] = {0, 0};
-  hipError_t fe = hipMemsetAsync(d_flag, 0, 2 * sizeof(int), c->stream);
-  for (int t = 0; t < 3 && fe == hipSuccess; ++t)
-    if (c->d_spec_base[t]) fe = soap::launch_check_finite(c, c->d_spec_base[t], c->B, false, d_flag);
-  if (fe == hipSuccess && c->d_con_base) fe = soap::launch_check_finite(c, c->d_con_base, c->con_rows, false, d_flag);
-  if (fe == hipSuccess) fe = soap::launch_check_finite(c, nullptr, 0, true, d_flag + 1);
+  for (int t = 0; t < 3; ++t)
+    if (c->d_spec_base[t] && !filled[t])
+      HIP_TRY(soap::launch_check_finite(c, c->d_spec_base[t], c->B, false, flags.p));
+  if (c->d_con_base) HIP_TRY(soap::launch_check_finite(c, c->d_con_base, c->con_rows, false, flags.p));
+  HIP_TRY(soap::launch_check_finite(c, nullptr, 0, true, flags.p + 1));
   // host arrays (mu bins, spectra) may be released once the call returns
-  const hipError_t se = hipStreamSynchronize(c->stream);
-  const hipError_t me =
-      (fe == hipSuccess && se == hipSuccess) ? hipMemcpy(h_flag, d_flag, sizeof h_flag, hipMemcpyDeviceToHost) : fe;
-  (void)soap::dev_free(d_flag);
-  HIP_TRY(fe);
-  HIP_TRY(se);
-  HIP_TRY(me);
+  HIP_TRY(hipStreamSynchronize(c->stream));
+  HIP_TRY(hipMemcpy(h_flag, flags.p, sizeof h_flag, hipMemcpyDeviceToHost));
   if (h_flag[0] || h_flag[1]) {
     const char* what = h_flag[0] ? "the device copy of the local spectra or contrast arrays"
                                  : "the quiet integrated spectrum";

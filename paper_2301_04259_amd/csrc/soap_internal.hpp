@@ -277,7 +277,6 @@ struct Plan {
 
 // ---- launchers (each enqueues on ctx->stream; return hipError_t) ----------
 hipError_t launch_geom(soap_ctx* c);
-hipError_t launch_pad(soap_ctx* c);
 hipError_t launch_contrast(soap_ctx* c);
 hipError_t launch_quiet(soap_ctx* c);
 // outputs and scratch of the weight kernel
@@ -396,6 +395,10 @@ hipError_t apply_batch_launch(const ApplyBatchGroup& g, hipStream_t st);
 hipError_t launch_q_convert(soap_ctx* c, void* out);
 // pads of `rows` padded rows starting at base (end samples held)
 hipError_t launch_pad_rows(soap_ctx* c, void* base, int rows);
+// src[t] (rows of P samples, device memory) to the padded rows base[t], with a
+// flag for non-finite values
+hipError_t launch_fill_rows(soap_ctx* c, const void* const* src, void* const* base, int n_sets, int rows,
+                            int* d_flag);
 // sets *d_flag (device int, zeroed by the caller) when any of `rows` padded
 // rows at base (float or double per the context) or, with Q set, the quiet
 // spectrum holds a non-finite value
