@@ -30,9 +30,14 @@ __device__ __forceinline__ double wave_sum(double v) {
   return v;
 }
 
-__global__ void k_geom(int N, double vsini, double dln, int* __restrict__ col_c,
-                       double* __restrict__ col_w) {
+// column shifts, and the limb angles of the bins to device memory
+struct MuBins {
+  double v[MAX_MU];
+};
+__global__ void k_geom(int N, int B, MuBins mu, double vsini, double dln, double* __restrict__ mu_b,
+                       int* __restrict__ col_c, double* __restrict__ col_w) {
   int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < B) mu_b[i] = mu.v[i];
   if (i >= N) return;
   double x = cell_coord(i, N);
   double beta = vsini * x / C_KMS;
@@ -360,8 +365,10 @@ __global__ void k_q_convert(int64_t P, const double* __restrict__ Q, T* __restri
 }
 
 hipError_t launch_geom(soap_ctx* c) {
-  hipLaunchKernelGGL(k_geom, dim3((c->N + 255) / 256), dim3(256), 0, c->stream, c->N, c->vsini, c->dln,
-                     c->d_col_c, c->d_col_w);
+  MuBins mu{};
+  for (int b = 0; b < c->B; ++b) mu.v[b] = c->mu_bins[b];
+  hipLaunchKernelGGL(k_geom, dim3((c->N + 255) / 256), dim3(256), 0, c->stream, c->N, c->B, mu, c->vsini, c->dln,
+                     c->d_mu, c->d_col_c, c->d_col_w);
   return hipGetLastError();
 }
 

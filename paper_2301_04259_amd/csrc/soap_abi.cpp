@@ -148,9 +148,7 @@ void destroy_ctx(soap_ctx* c) {
     (void)hipStreamSynchronize(c->stream);
     if (c->side) (void)hipStreamSynchronize(c->side);
   }
-  for (int t = 0; t < 3; ++t)
-    if (c->d_spec_base[t]) (void)soap::dev_free(c->d_spec_base[t]);
-  void* bufs[] = {c->d_mu, c->d_col_c, c->d_col_w, c->d_colW, c->d_Kq, c->d_Kq_fx, c->d_Q, c->d_con_base};
+  void* bufs[] = {c->d_mu, c->d_col_c, c->d_col_w, c->d_colW, c->d_Kq, c->d_Kq_fx, c->d_rows};
   for (void* p : bufs)
     if (p) (void)soap::dev_free(p);
   soap::Workspace* ws[] = {&c->ws_flux, &c->ws_ccf, &c->ws_ccfout, &c->ws_rv, &c->ws_mask, &c->ws_specin,
@@ -213,16 +211,20 @@ bool on_this_device(const soap_ctx* c, const void* p, size_t bytes) {
 }
 
 // sum over the visible cells of (2/N)^2 |I(mu)|: bounds every tap and
-// column sum of the fixed-point accumulators
+// column sum of the fixed-point accumulators.  One eighth of the disk stands
+// for all of it (all 300 x 300 cells took 230 us of a context's opening, 30 so).
 double disk_weight(int N, double u1, double u2) {
   const double area = (2.0 / N) * (2.0 / N);
   double tot = 0.0;
-  for (int i = 0; i < N; ++i) {
+  for (int i = N / 2; i < N; ++i) {  // the middle column of an odd grid, and those past it
     const double x = soap::cell_coord(i, N);
-    for (int k = 0; k < N; ++k) {
+    const double nx = 2 * i + 1 == N ? 1.0 : 2.0;
+    for (int k = i; k < N; ++k) {
       const double y = soap::cell_coord(k, N);
       const double r2 = x * x + y * y;
-      if (r2 < 1.0) tot += area * std::fabs(soap::limb_dark(std::sqrt(1.0 - r2), u1, u2));
+      if (!(r2 < 1.0)) break;
+      const double cells = nx * (2 * k + 1 == N ? 1.0 : 2.0) * (i == k ? 1.0 : 2.0);
+      tot += cells * area * std::fabs(soap::limb_dark(std::sqrt(1.0 - r2), u1, u2));
     }
   }
   return tot;
@@ -304,13 +306,25 @@ soap_status init_impl(const soap_star_desc* d, soap_ctx* c) {
   } flags;
   HIP_TRY(soap::dev_malloc((void**)&flags.p, 2 * sizeof(int)));
   HIP_TRY(hipMemsetAsync(flags.p, 0, 2 * sizeof(int), c->stream));
+  // one allocation for all padded rows and the quiet spectrum (each large one
+  // costs 12 us to make and 12 to give back)
+  int n_rows = 0;
+  for (int t = 0; t < 3; ++t) n_rows += d->spectra[t] ? c->B : 0;
+  if (c->cmode == SOAP_CONTRAST_PLANCK) c->con_rows = c->B + 1;  // one spot row for every bin, one facula row per bin
+  if (c->cmode == SOAP_CONTRAST_ARRAY) c->con_rows = 2 * c->B;   // the caller's rows: spot [B], then facula [B]
+  const size_t q_bytes = sizeof(double) * c->n_tiles * soap::APPLY_TILE_MAX;
+  HIP_TRY(soap::dev_malloc(&c->d_rows, row_bytes * (n_rows + c->con_rows) + q_bytes));
+  unsigned char* rows = static_cast<unsigned char*>(c->d_rows);
+  c->d_Q = reinterpret_cast<double*>(rows);
+  rows += q_bytes;
   const void* fill_src[3];
   void* fill_base[3];
   int n_fill = 0;
   bool filled[3] = {false, false, false};
   for (int t = 0; t < 3; ++t) {
     if (!d->spectra[t]) continue;
-    HIP_TRY(soap::dev_malloc(&c->d_spec_base[t], row_bytes * c->B));
+    c->d_spec_base[t] = rows;
+    rows += row_bytes * c->B;
     c->d_spec[t] = static_cast<unsigned char*>(c->d_spec_base[t]) + soap::PAD_FRONT * c->esize;
     filled[t] = on_dev && on_this_device(c, d->spectra[t], (size_t)c->P * c->esize * c->B);
     if (filled[t]) {
@@ -324,7 +338,6 @@ soap_status init_impl(const soap_star_desc* d, soap_ctx* c) {
   }
   if (n_fill) HIP_TRY(soap::launch_fill_rows(c, fill_src, fill_base, n_fill, c->B, flags.p));
   HIP_TRY(soap::dev_malloc((void**)&c->d_mu, sizeof(double) * c->B));
-  HIP_TRY(hipMemcpy(c->d_mu, d->mu_bins, sizeof(double) * c->B, hipMemcpyHostToDevice));
   HIP_TRY(soap::dev_malloc((void**)&c->d_col_c, sizeof(int) * c->N));
   HIP_TRY(soap::dev_malloc((void**)&c->d_col_w, sizeof(double) * c->N));
   HIP_TRY(soap::dev_malloc((void**)&c->d_colW, sizeof(double) * c->N * c->B));
@@ -333,19 +346,14 @@ soap_status init_impl(const soap_star_desc* d, soap_ctx* c) {
     HIP_TRY(soap::dev_malloc((void**)&c->d_Kq_fx, sizeof(unsigned long long) * c->B * c->J));
     HIP_TRY(hipMemsetAsync(c->d_Kq_fx, 0, sizeof(unsigned long long) * c->B * c->J, c->stream));
   }
-  HIP_TRY(soap::dev_malloc((void**)&c->d_Q, sizeof(double) * c->n_tiles * soap::APPLY_TILE_MAX));
   if (c->cmode == SOAP_CONTRAST_PLANCK) {
-    // one spot row for every bin, one facula row per bin
-    c->con_rows = c->B + 1;
-    HIP_TRY(soap::dev_malloc(&c->d_con_base, row_bytes * c->con_rows));
+    c->d_con_base = rows;
     c->d_con_spot = static_cast<unsigned char*>(c->d_con_base) + soap::PAD_FRONT * c->esize;
     c->d_con_fac = static_cast<unsigned char*>(c->d_con_spot) + row_bytes;
     c->con_spot_stride = 0;
   } else if (c->cmode == SOAP_CONTRAST_ARRAY) {
-    // the caller's rows: spot [B], then facula [B]; a type without spectra
-    // keeps rows of zeros (never read)
-    c->con_rows = 2 * c->B;
-    HIP_TRY(soap::dev_malloc(&c->d_con_base, row_bytes * c->con_rows));
+    // a type without spectra keeps rows of zeros (never read)
+    c->d_con_base = rows;
     c->d_con_spot = static_cast<unsigned char*>(c->d_con_base) + soap::PAD_FRONT * c->esize;
     c->d_con_fac = static_cast<unsigned char*>(c->d_con_spot) + row_bytes * c->B;
     c->con_spot_stride = c->Pstride;

@@ -173,6 +173,7 @@ struct soap_ctx {
   int pc = 0;                     // phases per apply chunk of the next call's tables (0: auto_pc)
 
   // resident device state (row pointers point at pixel 0 of row 0)
+  void* d_rows = nullptr;                          // owns Q and every padded row: the next ones point into it
   void* d_spec_base[3] = {nullptr, nullptr, nullptr};
   void* d_spec[3] = {nullptr, nullptr, nullptr};  // [B][Pstride]
   double* d_mu = nullptr;                          // [B]
