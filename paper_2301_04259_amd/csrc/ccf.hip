@@ -9,7 +9,7 @@
 // The line positions, the hole edges per velocity and the split of the mask
 // into blocks of lines and batches of nearby lines are built on the host
 // once per mask.  Layout: one block per (block of lines, block of SB
-// spectra), one thread per velocity; each thread keeps SB double
+// spectra), one thread per velocity (two past 512); each thread keeps SB
 // accumulators and reuses its hole geometry for every spectrum of the block.
 // Partial sums per line block are added in a fixed order by the fit kernel,
 // so results repeat bit for bit.
@@ -17,7 +17,7 @@
 // Fit: one wave64 per CCF; damped Newton (Levenberg-Marquardt damping) in
 // double on the unweighted least squares of c0 - a exp(-(v - mu)^2 /
 // (2 sigma^2)); the gradient, J^T J and the second-derivative sums are wave
-// reductions, the 4 x 4 damped system is solved by Cholesky in every lane.
+// reductions, the 4 x 4 damped system is solved by LDL^T in every lane.
 // Start values: c0 = max, a = c0 - min, mu at the vertex of the parabola
 // through the minimum and its neighbours, sigma from the half-depth width
 // with the crossings interpolated between samples.
@@ -1051,9 +1051,10 @@ constexpr int SG_MAX_ENS = 16;
 //     below thr or the fit did not converge.
 // The first and the last are matrix products in double, on the matrix cores
 // (v_mfma_f64_16x16x4_f64: lane l holds A(l % 16, l / 16) and B(l / 16, l % 16)
-// and ends with C(l / 16 + 4 r, l % 16), r < 4; step s of a group of 16 takes
-// the four terms 4 (l / 16) + s, so that a lane's operands of a group are
-// contiguous).  A block of SG_W waves takes 16 samples, each wave its share of
+// and ends with C(l / 16 + 4 r, l % 16), r < 4; the four terms are added in
+// order).  k_sg_lin takes its components in order, so its sums are those of
+// k_ccf_linear; k_sg_spread takes velocities 4 (l / 16) + s of 16 in step s, so
+// that a lane's operands are contiguous.  A block of SG_W waves takes 16 samples, each wave its share of
 // the columns.  Bound by the first-level cache, so the samples' operands pass
 // through LDS and the basis is read 16 bytes a lane.
 // 10000 samples, 128 components, 161 velocities: 19 and 26 us, against
