@@ -96,8 +96,10 @@ constexpr int LSF_KMAX = 32;
 // bounds n_mu x shift range (3 rows per bin in split tables).
 constexpr int DR_TAB_MAX = 1536;
 
-// Column slabs of the per-phase weight kernel (one wave per column).
-constexpr int SLAB_COLS = 4;
+// Disk columns per block of the batched weight kernel's work lists (one wave
+// per column at a time): 24 configurations of 25 to 200 phases 87 us with 4, 70
+// with 8, 64 with 16; 48 small ones 18.8, 18.6 and 20.0.
+constexpr int SLAB_COLS = 8;
 constexpr int WEIGHT_WAVES = 4;
 constexpr int FINISH_THREADS = 512;
 // fixed-point unit of the per-phase tap accumulators

@@ -249,8 +249,8 @@ int params_lanes(int max_reg) {
 // bounding box of the caps that reach the visible hemisphere.  One lane per
 // (phase, region), since a centre's sines and cosines are the kernel's time
 // (100 phases of 3 regions: 9.0 us with one thread per phase walking its
-// regions, 6.5 so; 50 of 6 regions: 14.6 and 8.2).  The regions and phases are read once from the
-// caller's parameter block, so the weight kernel's many blocks read device
+// regions, 6.5 so; 50 of 6 regions: 14.6 and 8.2).  The regions and phases are
+// read once from the caller's parameter block, so the weight kernel's many blocks read device
 // memory.  Block bid of nblk (PARAMS_THREADS each).
 constexpr int PARAMS_THREADS = 128;
 __device__ __forceinline__ void params_block(const ParamsArgs& a, int bid, int nblk) {
@@ -518,12 +518,13 @@ __global__ void __launch_bounds__(WEIGHT_WAVES * 64) k_weights(WeightsArgs a) {
 }
 
 // Blocks per phase of the weight kernels: enough to fill the chip with few
-// phases, few enough that a call over many phases is not spent on launching
-// blocks (500 spots x 8 phases, 75 blocks per phase, most of them without a
-// column: 93 us; 34 with 4).
+// phases (100 phases: 12.9 us with 40 blocks each, 14.4 with 20, 15.6 with 10),
+// few enough that a call over many phases is not spent on launching blocks (500
+// spots x 8 phases, 75 blocks per phase, most of them without a column: 93 us;
+// 34 with 4, 31 with 2, 35 with 1).
 int weight_parts(int N, int n_ph) {
   const int cols = (N + WEIGHT_WAVES - 1) / WEIGHT_WAVES;
-  return std::min(cols, std::max(4, 2048 / std::max(1, n_ph)));
+  return std::min(cols, std::max(2, 4096 / std::max(1, n_ph)));
 }
 
 // Differential rotation: the cells of one column no longer share a shift, so
