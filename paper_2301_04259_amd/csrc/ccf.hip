@@ -32,6 +32,9 @@ namespace soap {
 
 constexpr int CCF_LB = 32;        // mask lines per block (one partial CCF row each)
 constexpr int CCF_SB = 8;         // spectra per block
+constexpr int CCF_FEW = 2;        // and in calls of few blocks,
+constexpr int CCF_AHEAD = 3;      // with this many batches of loads in flight
+constexpr int CCF_FEW_BELOW = 128;
 constexpr int CCF_THREADS = 512;  // most threads of a block: one per velocity, two velocities each past 512
 constexpr int CCF_MIN_THREADS = 192;  // fewest: the block also stages the pixels
 constexpr int CCF_NV_MAX = 768;   // velocities per grid
@@ -45,10 +48,10 @@ int ccf_span_pixels(bool) { return CCF_STG_MAX; }
 
 namespace {
 
-// 16 bytes of elements
-template <typename T>
-struct Quad {
-  static constexpr int N = 16 / (int)sizeof(T);
+// the spectra of a pixel, in pieces of at most 16 bytes
+template <typename T, int SB>
+struct Piece {
+  static constexpr int N = 16 / (int)sizeof(T) < SB ? 16 / (int)sizeof(T) : SB;
   T x[N];
 };
 
@@ -62,7 +65,7 @@ struct Quad {
 // without bank conflicts (rows of all SB values had 2.4 conflict cycles per
 // load: 76 us against 71 for 300 spectra of 150001 pixels, 3000 lines and 401
 // velocities); two stage
-// buffers alternate, the next batch's loads are in flight while one is
+// buffers alternate, the next PF batches' loads are in flight while one is
 // used, and one barrier per batch separates them.  Pixels outside the
 // spectrum are staged as zeros.  Each thread computes its holes' pixel
 // overlaps once per line (in double: the hole edges come from differences of
@@ -71,22 +74,24 @@ struct Quad {
 // a few pixels in FP32 for float spectra, and the partials of the line blocks
 // are added in double by the fit kernel.
 // Line block lb, spectrum block sb.
-template <typename T, int A, int NPX, int STG>
+template <typename T, int A, int NPX, int STG, int SB, int PF>
 __device__ __forceinline__ void ccf_block(int P, int64_t n_spec, const T* __restrict__ F,
                                           const double2* __restrict__ lines, const double2* __restrict__ edges,
                                           const int4* __restrict__ batches, const int* __restrict__ bfirst,
                                           int n_v, T* __restrict__ part, int lb, int sb) {
-  constexpr int SB = CCF_SB;
   constexpr int R = (STG + CCF_MIN_THREADS - 1) / CCF_MIN_THREADS;  // staged pixels per thread
-  constexpr int QN = Quad<T>::N, NQ = SB / QN;
-  static_assert(SB % QN == 0, "whole 16-byte pieces");
-  __shared__ __align__(16) Quad<T> st[2][NQ][STG];
+  using Quad = Piece<T, SB>;
+  constexpr int QN = Quad::N, NQ = SB / QN;
+  static_assert(SB % QN == 0, "whole pieces");
+  __shared__ __align__(16) Quad st[2][NQ][STG];
   __shared__ double2 s_line[CCF_LB];
   // the edges on their way to registers: past the first stage buffer, which
   // is filled meanwhile, or over both
-  constexpr bool OVER = sizeof(st[1]) < sizeof(double2) * A * CCF_THREADS;
-  static_assert(sizeof(st) >= sizeof(double2) * (A == 1 ? CCF_THREADS : CCF_NV_MAX), "edges fit");
-  double2* s_ed = reinterpret_cast<double2*>(&st[OVER ? 0 : 1][0][0]);
+  constexpr size_t ED = sizeof(double2) * (A == 1 ? CCF_THREADS : CCF_NV_MAX);
+  constexpr bool OWN = sizeof(st) < ED, OVER = !OWN && sizeof(st[1]) < ED;
+  __shared__ double2 s_own[OWN ? ED / sizeof(double2) : 1];
+  double2* s_ed = OWN ? s_own : reinterpret_cast<double2*>(&st[OVER ? 0 : 1][0][0]);
+  __shared__ int4 s_bat[PF == 1 ? 1 : CCF_LB];  // the block's batches, one line each or more: read ahead
   const int tid = threadIdx.x, nt = blockDim.x;
   const int64_t s0 = (int64_t)sb * SB;
   const int ns = (int)min<int64_t>(SB, n_spec - s0);
@@ -94,6 +99,7 @@ __device__ __forceinline__ void ccf_block(int P, int64_t n_spec, const T* __rest
   const int l0 = batches[b0].y;
   const int nl = batches[b1 - 1].z - l0;
   if (tid < nl) s_line[tid] = lines[l0 + tid];
+  if (PF > 1 && tid < b1 - b0) s_bat[tid] = batches[b0 + tid];
   // lanes past the velocity grid repeat its last velocity (results dropped);
   // the edges go through LDS so that no global load is pending in the loop
 #pragma unroll
@@ -110,87 +116,100 @@ __device__ __forceinline__ void ccf_block(int P, int64_t n_spec, const T* __rest
     for (int s = 0; s < SB; ++s) acc[a][s] = T(0);
   }
   if constexpr (OVER) __syncthreads();
-  T vals[R][SB];
+  T vals[PF][R][SB];
   // only the batch's read span (batches[bi].w <= STG pixels) is loaded and
   // staged: no hole of the batch reads past it
-  auto load = [&](int bi) {
-    if (bi >= b1) return;
-    const int lo = batches[bi].x, span = batches[bi].w;
+  const int nb = b1 - b0;
+  auto bat = [&](int i) {  // batch i of the block (uniform)
+    if constexpr (PF == 1) return batches[b0 + i];
+    const int4 v = s_bat[i];
+    return make_int4(__builtin_amdgcn_readfirstlane(v.x), __builtin_amdgcn_readfirstlane(v.y),
+                     __builtin_amdgcn_readfirstlane(v.z), __builtin_amdgcn_readfirstlane(v.w));
+  };
+  auto load = [&](int i, T (&v)[R][SB]) {
+    if (i >= nb) return;
+    const int4 B = bat(i);
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-      if (tid + r * nt < span) {
-        const int m = min(max(lo + tid + r * nt, 0), P - 1);
+      if (tid + r * nt < B.w) {
+        const int m = min(max(B.x + tid + r * nt, 0), P - 1);
 #pragma unroll
-        for (int s = 0; s < SB; ++s) vals[r][s] = F[(s0 + min(s, ns - 1)) * (int64_t)P + m];
+        for (int s = 0; s < SB; ++s) v[r][s] = F[(s0 + min(s, ns - 1)) * (int64_t)P + m];
       }
     }
   };
-  auto put = [&](int bi) {
-    if (bi >= b1) return;
-    const int lo = batches[bi].x, span = batches[bi].w;
-    Quad<T>(*sb)[STG] = st[(bi - b0) & 1];
+  auto put = [&](int i, const T (&v)[R][SB]) {
+    if (i >= nb) return;
+    const int4 B = bat(i);
+    Quad(*sb)[STG] = st[i & 1];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-      const int i = tid + r * nt;
-      if (i < span) {
-        const int m = lo + i;
+      const int p = tid + r * nt;
+      if (p < B.w) {
+        const int m = B.x + p;
         const bool ok = m >= 0 && m < P;
 #pragma unroll
         for (int q = 0; q < NQ; ++q) {
-          Quad<T> v;
+          Quad x;
 #pragma unroll
-          for (int s = 0; s < QN; ++s) v.x[s] = ok ? vals[r][q * QN + s] : T(0);
-          sb[q][i] = v;
+          for (int s = 0; s < QN; ++s) x.x[s] = ok ? v[r][q * QN + s] : T(0);
+          sb[q][p] = x;
         }
       }
     }
   };
-  load(b0);
-  put(b0);
-  load(b0 + 1);
-  __syncthreads();
-  for (int bi = b0; bi < b1; ++bi) {
-    const int4 B = batches[bi];
-    const Quad<T>(*sb)[STG] = st[(bi - b0) & 1];
-    for (int l = B.y; l < B.z; ++l) {
-      const double2 mw = s_line[l - l0];
+  load(0, vals[0]);
+  put(0, vals[0]);
 #pragma unroll
-      for (int a = 0; a < A; ++a) {
-        const double qlo = mw.x + alo[a];
-        const double qhi = mw.x + ahi[a];
-        const double fa = floor(qlo);
-        const int i0 = (int)fa - B.x;
-        double w[NPX];
-        if constexpr (NPX == 2) {
-          // a hole narrower than a pixel: the first pixel takes the part of
-          // the hole below fa + 1, the second the rest
-          const double e1 = fa + 1.0;
-          w[0] = mw.y * (fmin(qhi, e1) - qlo);
-          w[1] = mw.y * fmax(qhi - e1, 0.0);
-        } else {
-          // pixel px covers [fa + px, fa + px + 1); the first pixel's lower
-          // edge is the hole's, pixels past the hole get weight zero
+  for (int d = 0; d < PF; ++d) load(1 + d, vals[d]);
+  __syncthreads();
+  for (int n0 = 0; n0 < nb; n0 += PF) {
+#pragma unroll
+    for (int d = 0; d < PF; ++d) {
+      const int i = n0 + d;
+      if (PF > 1 && i >= nb) break;
+      const int4 B = bat(i);
+      const Quad(*sb)[STG] = st[i & 1];
+      for (int l = B.y; l < B.z; ++l) {
+        const double2 mw = s_line[l - l0];
+#pragma unroll
+        for (int a = 0; a < A; ++a) {
+          const double qlo = mw.x + alo[a];
+          const double qhi = mw.x + ahi[a];
+          const double fa = floor(qlo);
+          const int i0 = (int)fa - B.x;
+          double w[NPX];
+          if constexpr (NPX == 2) {
+            // a hole narrower than a pixel: the first pixel takes the part of
+            // the hole below fa + 1, the second the rest
+            const double e1 = fa + 1.0;
+            w[0] = mw.y * (fmin(qhi, e1) - qlo);
+            w[1] = mw.y * fmax(qhi - e1, 0.0);
+          } else {
+            // pixel px covers [fa + px, fa + px + 1); the first pixel's lower
+            // edge is the hole's, pixels past the hole get weight zero
+#pragma unroll
+            for (int px = 0; px < NPX; ++px) {
+              const double mlo = fa + (double)px;
+              w[px] = mw.y * fmax(fmin(qhi, mlo + 1.0) - (px == 0 ? qlo : mlo), 0.0);
+            }
+          }
 #pragma unroll
           for (int px = 0; px < NPX; ++px) {
-            const double mlo = fa + (double)px;
-            w[px] = mw.y * fmax(fmin(qhi, mlo + 1.0) - (px == 0 ? qlo : mlo), 0.0);
-          }
-        }
+            const T wp = (T)w[px];
 #pragma unroll
-        for (int px = 0; px < NPX; ++px) {
-          const T wp = (T)w[px];
+            for (int q = 0; q < NQ; ++q) {
+              const Quad f = sb[q][i0 + px];
 #pragma unroll
-          for (int q = 0; q < NQ; ++q) {
-            const Quad<T> f = sb[q][i0 + px];
-#pragma unroll
-            for (int s = 0; s < QN; ++s) acc[a][q * QN + s] = fma(wp, f.x[s], acc[a][q * QN + s]);
+              for (int s = 0; s < QN; ++s) acc[a][q * QN + s] = fma(wp, f.x[s], acc[a][q * QN + s]);
+            }
           }
         }
       }
+      put(i + 1, vals[d]);
+      load(i + 1 + PF, vals[d]);
+      __syncthreads();
     }
-    put(bi + 1);
-    load(bi + 2);
-    __syncthreads();
   }
 #pragma unroll
   for (int a = 0; a < A; ++a) {
@@ -202,14 +221,14 @@ __device__ __forceinline__ void ccf_block(int P, int64_t n_spec, const T* __rest
   }
 }
 
-template <typename T, int A, int NPX, int STG>
+template <typename T, int A, int NPX, int STG, int SB, int PF>
 __global__ void __launch_bounds__(CCF_THREADS) k_ccf(int P, int64_t n_spec, const T* __restrict__ F,
                                                      const double2* __restrict__ lines,
                                                      const double2* __restrict__ edges,
                                                      const int4* __restrict__ batches,
                                                      const int* __restrict__ bfirst, int n_v,
                                                      T* __restrict__ part) {
-  ccf_block<T, A, NPX, STG>(P, n_spec, F, lines, edges, batches, bfirst, n_v, part, blockIdx.x, blockIdx.y);
+  ccf_block<T, A, NPX, STG, SB, PF>(P, n_spec, F, lines, edges, batches, bfirst, n_v, part, blockIdx.x, blockIdx.y);
 }
 
 // Work-list form over many spectra sets with one mask layout: blk[b] =
@@ -220,7 +239,7 @@ __global__ void __launch_bounds__(CCF_THREADS) k_ccf_batch(const CcfBatchSet* __
   const int4 t = blk[blockIdx.x];
   const CcfBatchSet c = sets[t.x];
   const unsigned char* tb = c.tables;
-  ccf_block<T, A, NPX, STG>(c.P, c.n_spec, static_cast<const T*>(c.flux), reinterpret_cast<const double2*>(tb),
+  ccf_block<T, A, NPX, STG, CCF_SB, 1>(c.P, c.n_spec, static_cast<const T*>(c.flux), reinterpret_cast<const double2*>(tb),
                             reinterpret_cast<const double2*>(tb + c.off_edges),
                             reinterpret_cast<const int4*>(tb + c.off_batch),
                             reinterpret_cast<const int*>(tb + c.off_bfirst), n_v, static_cast<T*>(c.part), t.y, t.z);
@@ -791,10 +810,20 @@ static unsigned ccf_threads(int n_v) {
 }
 
 template <typename T, int A, int NPX, int STG>
-static void launch_ccf_a(const CcfPlan& q, hipStream_t st, dim3 grid, const void* d_flux, int64_t n_spec,
+static void launch_ccf_a(const CcfPlan& q, hipStream_t st, const void* d_flux, int64_t n_spec,
                          void* d_part) {
   const unsigned char* base = q.tables;
-  hipLaunchKernelGGL((k_ccf<T, A, NPX, STG>), grid, dim3(ccf_threads<A>(q.nv)), 0, st, (int)q.P, n_spec,
+  const int nlb = ccf_line_blocks(q.n_lines);
+  auto blocks = [&](int sb) { return dim3((unsigned)nlb, (unsigned)((n_spec + sb - 1) / sb)); };
+  // Few blocks of CCF_SB spectra leave the chip idle, and each is a chain of
+  // batches that wait for their loads: then blocks of CCF_FEW spectra with
+  // CCF_AHEAD batches of loads in flight (one spectrum of 400 lines, 13 blocks:
+  // 13.9 us and 10.9 so; 25 FP64 spectra of 100 lines, 16 blocks: 14.1 and 10.4;
+  // 50 of 1200 lines, 266 blocks: 13.9 and 13.5; 60 FP64 of 2000 lines, 504
+  // blocks: 17.3 and 19.4).
+  const bool few = (int64_t)nlb * blocks(CCF_SB).y < CCF_FEW_BELOW;
+  auto* kernel = few ? &k_ccf<T, A, NPX, STG, CCF_FEW, CCF_AHEAD> : &k_ccf<T, A, NPX, STG, CCF_SB, 1>;
+  hipLaunchKernelGGL(kernel, blocks(few ? CCF_FEW : CCF_SB), dim3(ccf_threads<A>(q.nv)), 0, st, (int)q.P, n_spec,
                      static_cast<const T*>(d_flux), reinterpret_cast<const double2*>(base),
                      reinterpret_cast<const double2*>(base + q.off_edges),
                      reinterpret_cast<const int4*>(base + q.off_batch),
@@ -802,28 +831,28 @@ static void launch_ccf_a(const CcfPlan& q, hipStream_t st, dim3 grid, const void
 }
 
 template <typename T, int NPX, int STG>
-static void launch_ccf_n(const CcfPlan& q, hipStream_t st, dim3 grid, const void* d_flux, int64_t n_spec,
+static void launch_ccf_n(const CcfPlan& q, hipStream_t st, const void* d_flux, int64_t n_spec,
                          void* d_part) {
-  if (q.nv <= CCF_THREADS) launch_ccf_a<T, 1, NPX, STG>(q, st, grid, d_flux, n_spec, d_part);
-  else launch_ccf_a<T, 2, NPX, STG>(q, st, grid, d_flux, n_spec, d_part);
+  if (q.nv <= CCF_THREADS) launch_ccf_a<T, 1, NPX, STG>(q, st, d_flux, n_spec, d_part);
+  else launch_ccf_a<T, 2, NPX, STG>(q, st, d_flux, n_spec, d_part);
 }
 
 template <typename T, int STG>
-static void launch_ccf_s(const CcfPlan& q, hipStream_t st, dim3 grid, const void* d_flux, int64_t n_spec,
+static void launch_ccf_s(const CcfPlan& q, hipStream_t st, const void* d_flux, int64_t n_spec,
                          void* d_part) {
   switch (q.npx) {
-    case 2: launch_ccf_n<T, 2, STG>(q, st, grid, d_flux, n_spec, d_part); break;
-    case 3: launch_ccf_n<T, 3, STG>(q, st, grid, d_flux, n_spec, d_part); break;
-    case 5: launch_ccf_n<T, 5, STG>(q, st, grid, d_flux, n_spec, d_part); break;
-    default: launch_ccf_n<T, 10, STG>(q, st, grid, d_flux, n_spec, d_part); break;
+    case 2: launch_ccf_n<T, 2, STG>(q, st, d_flux, n_spec, d_part); break;
+    case 3: launch_ccf_n<T, 3, STG>(q, st, d_flux, n_spec, d_part); break;
+    case 5: launch_ccf_n<T, 5, STG>(q, st, d_flux, n_spec, d_part); break;
+    default: launch_ccf_n<T, 10, STG>(q, st, d_flux, n_spec, d_part); break;
   }
 }
 
 template <typename T>
-static void launch_ccf_t(const CcfPlan& q, hipStream_t st, dim3 grid, const void* d_flux, int64_t n_spec,
+static void launch_ccf_t(const CcfPlan& q, hipStream_t st, const void* d_flux, int64_t n_spec,
                          void* d_part) {
-  if (q.stg <= 256) launch_ccf_s<T, 256>(q, st, grid, d_flux, n_spec, d_part);
-  else launch_ccf_s<T, CCF_STG_MAX>(q, st, grid, d_flux, n_spec, d_part);
+  if (q.stg <= 256) launch_ccf_s<T, 256>(q, st, d_flux, n_spec, d_part);
+  else launch_ccf_s<T, CCF_STG_MAX>(q, st, d_flux, n_spec, d_part);
 }
 
 CcfPlan ccf_plan(const soap_ctx* c, int n_lines, const void* tables) {
@@ -844,10 +873,8 @@ CcfPlan ccf_plan(const soap_ctx* c, int n_lines, const void* tables) {
 }
 
 hipError_t launch_ccf_p(const CcfPlan& q, hipStream_t st, const void* d_flux, int64_t n_spec, void* d_part) {
-  const int nlb = ccf_line_blocks(q.n_lines);
-  dim3 grid(nlb, (unsigned)((n_spec + CCF_SB - 1) / CCF_SB));
-  if (q.fp32) launch_ccf_t<float>(q, st, grid, d_flux, n_spec, d_part);
-  else launch_ccf_t<double>(q, st, grid, d_flux, n_spec, d_part);
+  if (q.fp32) launch_ccf_t<float>(q, st, d_flux, n_spec, d_part);
+  else launch_ccf_t<double>(q, st, d_flux, n_spec, d_part);
   return hipGetLastError();
 }
 

@@ -57,3 +57,31 @@ def test_velocity_counts_match_oracle(prec, n_v, hole_px, span_px, n_spec):
     rel = np.max(np.abs(got[:-1] - ref) / np.abs(ref))
     assert rel < (1e-9 if prec == W.PREC_FP64 else 2e-5), rel
     L.soap_destroy(ctx)
+
+
+@pytest.mark.parametrize("prec,hole_px,n_lines", [(W.PREC_FP32, 0.9, 70), (W.PREC_FP32, 3.0, 33),
+                                                  (W.PREC_FP64, 0.9, 1), (W.PREC_FP64, 1.4, 64)])
+def test_few_spectra_equal_many(prec, hole_px, n_lines):
+    """Calls of few blocks take two spectra a block with more loads in flight;
+    every spectrum's CCF and fit is bit for bit that of a large call."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    print(f"[ccf-lanes] few: prec {prec} hole {hole_px} px lines {n_lines}", flush=True)
+    n_pix, n_v, n_many = 3000, 161, 1100  # at least 138 blocks of eight spectra
+    star = W.make_tiny(52, n_grid=8, n_pix=n_pix, n_mu=2, precision=prec, n_phases=1)
+    ctx = L.soap_grid_init(star)
+    rng = np.random.default_rng(n_lines)
+    px_kms = C_KMS * star.dln_lambda
+    dv = 46.0 * px_kms / (n_v - 1)
+    q = np.sort(rng.uniform(-5.0, n_pix + 5.0, n_lines))
+    mask = W.Mask(star.ln_lambda0 + (q - 0.5) * star.dln_lambda, rng.uniform(0.5, 1.5, n_lines),
+                  0.5 * hole_px * px_kms, -0.5 * dv * (n_v - 1), dv, n_v)
+    dt = torch.float64 if prec == W.PREC_FP64 else torch.float32
+    flux = torch.from_numpy(rng.uniform(0.2, 1.0, (n_many, n_pix))).to(dt).cuda()
+    many = torch.empty(n_many, n_v, dtype=torch.float64, device="cuda")
+    L.soap_ccf_rv(ctx, flux, mask, ccf_out=many)
+    for n in (1, 2, 7):
+        few = torch.empty(n, n_v, dtype=torch.float64, device="cuda")
+        L.soap_ccf_rv(ctx, flux[:n], mask, ccf_out=few)
+        assert torch.equal(few, many[:n]), n
+    L.soap_destroy(ctx)
