@@ -7,13 +7,14 @@
 // Network per ensemble member: x[n_in] -> SiLU(x W1 + b1)[H] ->
 // SiLU(. W2 + b2)[H] -> . W3 + b3 [n_out].  Parameters are FP32 masters;
 // the matrix products run on BF16 copies with MFMA (v_mfma_f32_16x16x32_bf16,
-// FP32 accumulate), one 16 x 16 output tile per wave.  Training minimises the
+// FP32 accumulate): the whole network per block of rows where its activations
+// fit in LDS, else a kernel per layer.  Training minimises the
 // mean squared error over the batch and outputs with Adam (bias-corrected
 // moments, FP32).  Every kernel has a fixed order of operations, so results
 // repeat bit for bit.
 //
 // The PCA projection coef = (d - mean) V of spectra differences onto a basis
-// is an FP32 tiled product (K = pixels, large).
+// is an FP32 product on the matrix cores (K = pixels, large).
 #include <cmath>
 
 #include "surrogate_internal.hpp"
