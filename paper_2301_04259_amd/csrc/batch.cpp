@@ -298,6 +298,11 @@ static soap_status create_impl(soap_ctx* const* ctxs, int32_t n_cfg, const soap_
     return (e == hipErrorOutOfMemory) ? SOAP_ERR_OOM : SOAP_ERR_HIP;
   };
   hipError_t e;
+  auto alloc = [&](void** p) {
+    std::vector<soap_ctx*> cs;
+    for (const CfgPlan& q : cp) cs.push_back(q.c);
+    return soap::dev_malloc_for(cs.data(), n_cfg, p, arena);
+  };
   std::unique_lock<std::mutex> direct_lock;
   unsigned char* A = nullptr;
   if (direct) {
@@ -306,13 +311,13 @@ static soap_status create_impl(soap_ctx* const* ctxs, int32_t n_cfg, const soap_
       if (g_direct.ptr) (void)soap::dev_free(g_direct.ptr);
       g_direct.ptr = nullptr;
       g_direct.bytes = 0;
-      if ((e = soap::dev_malloc(&g_direct.ptr, arena)) != hipSuccess) return fail("hipMalloc", e);
+      if ((e = alloc(&g_direct.ptr)) != hipSuccess) return fail("hipMalloc", e);
       g_direct.bytes = arena;
       g_direct.dev = dev;
     }
     A = static_cast<unsigned char*>(g_direct.ptr);
   } else {
-    if ((e = soap::dev_malloc(&b->arena, arena)) != hipSuccess) return fail("hipMalloc", e);
+    if ((e = alloc(&b->arena)) != hipSuccess) return fail("hipMalloc", e);
     A = static_cast<unsigned char*>(b->arena);
   }
   // tap accumulators start at zero (each run's tap-list kernel clears them

@@ -122,7 +122,45 @@ soap_status validate_desc(const soap_star_desc* d, std::string& err) {
   return SOAP_OK;
 }
 
-hipError_t grow(soap::Workspace& w, size_t bytes) {
+bool is_oom(hipError_t e) { return e == hipErrorOutOfMemory || e == hipErrorMemoryAllocation; }
+
+void free_ws(soap::Workspace& w) {
+  if (w.ptr) (void)soap::dev_free(w.ptr);
+  w.ptr = nullptr;
+  w.bytes = 0;
+}
+
+void free_tables(soap_ctx::Prep& S) {
+  free_ws(S.mem);
+  std::fill(std::begin(S.at), std::end(S.at), 0);
+  S.used = S.built = false;
+}
+
+// frees every table set but the last call's, which soap_profile_read reads;
+// whether there was one to free
+bool free_spare_tables(soap_ctx* c) {
+  bool any = false;
+  for (int i = 0; i < soap_ctx::NPREP; ++i) any = any || (i != c->last_prep && c->prep[i].mem.ptr);
+  if (!any || hipStreamSynchronize(c->stream) != hipSuccess) return false;
+  for (int i = 0; i < soap_ctx::NPREP; ++i)
+    if (i != c->last_prep) free_tables(c->prep[i]);
+  return true;
+}
+
+}  // namespace
+
+hipError_t soap::dev_malloc_for(soap_ctx* const* ctxs, int n, void** p, size_t bytes) {
+  hipError_t e = soap::dev_malloc(p, bytes);
+  if (!is_oom(e)) return e;
+  (void)hipGetLastError();
+  bool freed = false;
+  for (int i = 0; i < n; ++i) freed = free_spare_tables(ctxs[i]) || freed;
+  return freed ? soap::dev_malloc(p, bytes) : e;
+}
+
+namespace {
+
+hipError_t grow(soap_ctx* c, soap::Workspace& w, size_t bytes) {
   if (w.bytes >= bytes) return hipSuccess;
   if (w.ptr) {
     hipError_t e = soap::dev_free(w.ptr);
@@ -131,15 +169,9 @@ hipError_t grow(soap::Workspace& w, size_t bytes) {
     w.bytes = 0;
   }
   size_t want = std::max<size_t>(bytes, 256);
-  hipError_t e = soap::dev_malloc(&w.ptr, want);
+  hipError_t e = soap::dev_malloc_for(&c, 1, &w.ptr, want);
   if (e == hipSuccess) w.bytes = want;
   return e;
-}
-
-void free_ws(soap::Workspace& w) {
-  if (w.ptr) (void)soap::dev_free(w.ptr);
-  w.ptr = nullptr;
-  w.bytes = 0;
 }
 
 void destroy_ctx(soap_ctx* c) {
@@ -155,8 +187,7 @@ void destroy_ctx(soap_ctx* c) {
                            &c->ws_lsf, &c->ws_sg};
   for (auto* w : ws) free_ws(*w);
   for (auto& S : c->prep) {
-    soap::Workspace* pw[] = {&S.par, &S.Kfx, &S.K, &S.mask64, &S.vg, &S.nvg};
-    for (auto* w : pw) free_ws(*w);
+    free_tables(S);
     if (S.done) (void)hipEventDestroy(S.done);
   }
   if (c->side) (void)hipStreamDestroy(c->side);
@@ -509,7 +540,7 @@ SOAP_API soap_status soap_quiet_spectrum(soap_ctx* c, void* out, int32_t out_on_
   const size_t bytes = (size_t)c->P * c->esize;
   void* dst = out;
   if (!out_on_device) {
-    HIP_TRY(grow(c->ws_flux, bytes));
+    HIP_TRY(grow(c, c->ws_flux, bytes));
     dst = c->ws_flux.ptr;
   }
   if (c->prec == SOAP_PREC_FP64)
@@ -544,37 +575,89 @@ hipError_t wait_started(soap_ctx* c, unsigned seq) {
   }
 }
 
-// The table set of the next call.  Set 0 runs on the context stream.  When the
-// caller is ahead of the device (the last call's apply has not begun) the
-// table kernels, short and far from filling the chip, run beside what is
-// pending instead: a 100-phase series enqueued over and over takes 76 us a
-// call so, 100 on one stream.
+// Sizes of the parts of a call's tables
+struct TableSizes {
+  size_t bytes[soap::TAB_N];
+};
+
+bool tables_fit(const soap_ctx::Prep& S, const TableSizes& z) {
+  for (int i = 0; i < soap::TAB_N; ++i)
+    if (S.at[i + 1] - S.at[i] < z.bytes[i]) return false;
+  return S.mem.ptr != nullptr;
+}
+
+// Makes the tables of an idle set hold z, and every part what it held unless
+// `least`; a set that cannot keeps none of them.  One allocation: 15 us for a
+// new context's 100-phase set, six of its parts' sizes up to 80 (a new chunk
+// of the runtime's pool).
+hipError_t grow_tables(soap_ctx::Prep& S, const TableSizes& z, bool least) {
+  size_t at[soap::TAB_N + 1] = {0};
+  for (int i = 0; i < soap::TAB_N; ++i) {
+    const size_t part = std::max(z.bytes[i], least ? 0 : S.at[i + 1] - S.at[i]);
+    at[i + 1] = at[i] + 256 * std::max<size_t>(1, (part + 255) / 256);
+  }
+  free_tables(S);
+  const hipError_t e = soap::dev_malloc(&S.mem.ptr, at[soap::TAB_N]);
+  if (e != hipSuccess) return e;
+  S.mem.bytes = at[soap::TAB_N];
+  std::copy(std::begin(at), std::end(at), std::begin(S.at));
+  S.kfx_dirty = true;
+  return hipSuccess;
+}
+
+// The table set of the next call, and the stream of its table kernels.  On the
+// context stream any set will do: the stream keeps the order.  When the caller
+// is ahead of the device (the last call's apply has not begun) the table
+// kernels, short and far from filling the chip, run beside what is pending
+// instead: a 100-phase series enqueued over and over takes 76 us a call so, 100
+// on one stream.  They take the set that was used longest ago, whose apply is
+// over once a later one has begun.
 // Otherwise the second queue only adds its hand-over and host time: the same
 // series with a wait after each call, 133 us with the second queue, 112 us on
 // one stream.
-hipError_t choose_prep(soap_ctx* c, int* sidx) {
+// Memory for the side stream's sets is spare: a call that cannot have it runs
+// on the context stream.
+hipError_t choose_prep(soap_ctx* c, const TableSizes& z, int* sidx, hipStream_t* st) {
   hipError_t e;
-  if (c->tables_open) {  // the last call stopped half-way: nothing of it may run on
-    if ((e = hipStreamSynchronize(c->stream)) != hipSuccess) return e;
-    if (c->side && (e = hipStreamSynchronize(c->side)) != hipSuccess) return e;
-    c->tables_open = false;
-  }
   if (!c->started) {
     if ((e = hipHostMalloc(reinterpret_cast<void**>(&c->started), 64, hipHostMallocMapped | hipHostMallocCoherent)) !=
         hipSuccess)
       return e;
     *c->started = c->call_seq;
   }
-  *sidx = 0;
-  if (__atomic_load_n(c->started, __ATOMIC_ACQUIRE) == c->call_seq) return hipSuccess;
-  if (!c->side && (e = hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking)) != hipSuccess) return e;
-  soap_ctx::Prep& S = c->prep[c->prep_next];
-  if (!S.done && (e = hipEventCreateWithFlags(&S.done, hipEventDisableTiming)) != hipSuccess) return e;
-  // the set's last apply is over once a later one has begun
-  if (S.used && (e = wait_started(c, S.seq + 1)) != hipSuccess) return e;
-  *sidx = c->prep_next;
-  c->prep_next = c->prep_next % (soap_ctx::NPREP - 1) + 1;
-  return hipSuccess;
+  *st = c->stream;
+  if (__atomic_load_n(c->started, __ATOMIC_ACQUIRE) != c->call_seq) {
+    if (!c->side && (e = hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking)) != hipSuccess) return e;
+    size_t all = 0;
+    for (size_t b : z.bytes) all += b;
+    const int n = all <= soap::PREP_SMALL ? soap_ctx::NPREP : 2;
+    int k = 0;  // the first unused set, else the one used longest ago
+    for (int i = 1; i < n && c->prep[k].used; ++i)
+      if (!c->prep[i].used || (int)(c->prep[k].seq - c->prep[i].seq) > 0) k = i;
+    soap_ctx::Prep& S = c->prep[k];
+    if (S.used && (e = wait_started(c, S.seq + 1)) != hipSuccess) return e;
+    if (!S.done && (e = hipEventCreateWithFlags(&S.done, hipEventDisableTiming)) != hipSuccess) return e;
+    if (tables_fit(S, z) || (e = grow_tables(S, z, false)) == hipSuccess) {
+      *sidx = k;
+      *st = c->side;
+      return hipSuccess;
+    }
+    if (!is_oom(e)) return e;
+    (void)hipGetLastError();
+  }
+  for (int i = 0; i < soap_ctx::NPREP; ++i)
+    if (tables_fit(c->prep[i], z)) {
+      *sidx = i;
+      return hipSuccess;
+    }
+  soap_ctx::Prep& S = c->prep[c->last_prep];
+  *sidx = c->last_prep;
+  // buffers in use are replaced only with the stream idle
+  if (S.used && (e = hipStreamSynchronize(c->stream)) != hipSuccess) return e;
+  if ((e = grow_tables(S, z, false)) == hipSuccess || !is_oom(e)) return e;
+  (void)hipGetLastError();
+  (void)free_spare_tables(c);
+  return grow_tables(S, z, true);
 }
 
 // Shared body of soap_active_spectra and soap_active_spectra_jobs.  With
@@ -622,11 +705,6 @@ soap_status active_impl(soap_ctx* c, const soap_region* regions, int32_t n_regio
   const size_t reg_bytes = 256 * ((sizeof(soap::Region) * n_reg_slots + 255) / 256);
   const size_t ph_bytes = 256 * ((sizeof(double) * n_phases + 255) / 256);
   const size_t par_bytes = reg_bytes + ph_bytes + (pj_host ? sizeof(int2) * n_phases : 0);
-  const unsigned seq = c->call_seq + 1;
-  int sidx = 0;
-  HIP_TRY(choose_prep(c, &sidx));
-  soap_ctx::Prep& S = c->prep[sidx];
-  const hipStream_t st = sidx ? c->side : c->stream;
   const size_t reg_dev = reg_bytes;
   const size_t pj_dev = 256 * ((sizeof(int2) * (size_t)n_phases + 255) / 256);
   const size_t cen_dev = 256 * ((sizeof(double4) * (size_t)n_phases * std::max(1, max_reg) + 255) / 256);
@@ -636,30 +714,11 @@ soap_status active_impl(soap_ctx* c, const soap_region* regions, int32_t n_regio
   const size_t m_bytes = sizeof(unsigned long long) * (size_t)n_phases * pl.G;
   const size_t vg_bytes = (size_t)soap::win_bytes(pl.pc, (int)c->esize) * pl.n_chunks * pl.vg_cap;
   const size_t nvg_bytes = sizeof(int) * (size_t)pl.n_chunks;
-  const bool regrow = S.par.bytes < par_dev || S.Kfx.bytes < kfx_bytes || S.K.bytes < k_bytes ||
-                      S.mask64.bytes < m_bytes || S.vg.bytes < vg_bytes || S.nvg.bytes < nvg_bytes;
-  if (regrow) {
-    // buffers are replaced only with both streams idle
-    HIP_TRY(hipStreamSynchronize(c->stream));
-    if (c->side) HIP_TRY(hipStreamSynchronize(c->side));
-    HIP_TRY(grow(S.par, par_dev));
-    HIP_TRY(grow(S.K, k_bytes));
-    HIP_TRY(grow(S.mask64, m_bytes));
-    HIP_TRY(grow(S.vg, vg_bytes));
-    HIP_TRY(grow(S.nvg, nvg_bytes));
-  }
-  if (S.Kfx.bytes < kfx_bytes || S.kfx_dirty) {
-    // fixed-point tap accumulators: zero when allocated; every call that
-    // accumulates also clears them, so they are zeroed again only after an
-    // interrupted call
-    HIP_TRY(grow(S.Kfx, kfx_bytes));
-    HIP_TRY(hipMemsetAsync(S.Kfx.ptr, 0, S.Kfx.bytes, st));
-    S.kfx_dirty = false;
-  }
+  // the outputs' workspaces first: making room for them may take table sets
   const size_t out_bytes = (size_t)n_phases * c->P * c->esize;
   void* dflux = flux;
   if (!flux_on_device) {
-    HIP_TRY(grow(c->ws_flux, out_bytes));
+    HIP_TRY(grow(c, c->ws_flux, out_bytes));
     dflux = c->ws_flux.ptr;
   }
   // with resolution lowering the synthesis goes to a workspace first
@@ -672,9 +731,20 @@ soap_status active_impl(soap_ctx* c, const soap_region* regions, int32_t n_regio
   if (lower) {
     if (c->ws_lsf.bytes < out_bytes) {
       HIP_TRY(hipStreamSynchronize(c->stream));
-      HIP_TRY(grow(c->ws_lsf, out_bytes));
+      HIP_TRY(grow(c, c->ws_lsf, out_bytes));
     }
     dsyn = c->ws_lsf.ptr;
+  }
+  const unsigned seq = c->call_seq + 1;
+  int sidx = 0;
+  hipStream_t st = nullptr;
+  HIP_TRY(choose_prep(c, TableSizes{{par_dev, kfx_bytes, k_bytes, m_bytes, vg_bytes, nvg_bytes}}, &sidx, &st));
+  soap_ctx::Prep& S = c->prep[sidx];
+  if (S.kfx_dirty) {
+    // every call that accumulates also clears the accumulators, so they are
+    // zeroed only when new and after an interrupted call
+    HIP_TRY(hipMemsetAsync(S.part(soap::TAB_KFX), 0, S.at[soap::TAB_KFX + 1] - S.at[soap::TAB_KFX], st));
+    S.kfx_dirty = false;
   }
   const int k = (int)(seq % soap_ctx::NSLOT);
   HIP_TRY(wait_started(c, seq - soap_ctx::NSLOT));
@@ -706,17 +776,28 @@ soap_status active_impl(soap_ctx* c, const soap_region* regions, int32_t n_regio
   const int2* d_pj = pj_host ? reinterpret_cast<const int2*>(dev_par + reg_bytes + ph_bytes) : nullptr;
 
   soap::WeightsOut wo;
-  wo.reg = static_cast<soap::Region*>(S.par.ptr);
-  wo.pj = reinterpret_cast<int2*>(static_cast<unsigned char*>(S.par.ptr) + reg_dev);
-  wo.cen = reinterpret_cast<double4*>(static_cast<unsigned char*>(S.par.ptr) + reg_dev + pj_dev);
-  wo.box = reinterpret_cast<int4*>(static_cast<unsigned char*>(S.par.ptr) + reg_dev + pj_dev + cen_dev);
-  wo.Kfx = static_cast<unsigned long long*>(S.Kfx.ptr);
-  wo.K = static_cast<double*>(S.K.ptr);
-  wo.mask = static_cast<unsigned long long*>(S.mask64.ptr);
-  wo.wins = static_cast<unsigned char*>(S.vg.ptr);
-  wo.nvg = static_cast<int*>(S.nvg.ptr);
-  c->tables_open = true;
-  c->call_seq = seq;
+  unsigned char* par = S.part<unsigned char>(soap::TAB_PAR);
+  wo.reg = reinterpret_cast<soap::Region*>(par);
+  wo.pj = reinterpret_cast<int2*>(par + reg_dev);
+  wo.cen = reinterpret_cast<double4*>(par + reg_dev + pj_dev);
+  wo.box = reinterpret_cast<int4*>(par + reg_dev + pj_dev + cen_dev);
+  wo.Kfx = S.part<unsigned long long>(soap::TAB_KFX);
+  wo.K = S.part<double>(soap::TAB_K);
+  wo.mask = S.part<unsigned long long>(soap::TAB_MASK);
+  wo.wins = S.part<unsigned char>(soap::TAB_WIN);
+  wo.nvg = S.part<int>(soap::TAB_NWIN);
+  // a call that stops between its table kernels and its apply leaves nothing
+  // running, so that its set, its slot and its number can be used again
+  struct Idle {
+    hipStream_t a, b;
+    bool open = true;
+    ~Idle() {
+      if (!open) return;
+      (void)hipStreamSynchronize(a);
+      (void)hipStreamSynchronize(b);
+    }
+  } idle{st, c->stream};
+  S.built = false;
   S.kfx_dirty = true;
   {
     StageTimer t(c, ST_WEIGHTS, st);
@@ -729,18 +810,19 @@ soap_status active_impl(soap_ctx* c, const soap_region* regions, int32_t n_regio
     t.done();
   }
   S.kfx_dirty = false;
-  if (sidx) {
+  if (st != c->stream) {
     HIP_TRY(hipEventRecord(S.done, st));
     HIP_TRY(hipStreamWaitEvent(c->stream, S.done, 0));
   }
   {
     StageTimer t(c, ST_APPLY);
-    HIP_TRY(soap::launch_apply(c, pl, S.vg.ptr, static_cast<const int*>(S.nvg.ptr), dsyn, seq));
+    HIP_TRY(soap::launch_apply(c, pl, wo.wins, wo.nvg, dsyn, seq));
     t.done();
   }
-  c->tables_open = false;
+  idle.open = false;
+  c->call_seq = seq;
   S.seq = seq;
-  S.used = true;
+  S.used = S.built = true;
   c->last_prep = sidx;
   if (lower) {
     StageTimer t(c, ST_LSF);
@@ -948,11 +1030,11 @@ SOAP_API soap_status soap_instrument_lsf(soap_ctx* c, const void* in, void* out,
   const void* din = in;
   void* dout = out;
   if (!on_device) {
-    HIP_TRY(grow(c->ws_specin, bytes));
+    HIP_TRY(grow(c, c->ws_specin, bytes));
     soap_status st = stage_to_device(c, in, bytes, c->ws_specin.ptr);
     if (st != SOAP_OK) return st;
     din = c->ws_specin.ptr;
-    HIP_TRY(grow(c->ws_lsf, bytes));
+    HIP_TRY(grow(c, c->ws_lsf, bytes));
     dout = c->ws_lsf.ptr;
   }
   {
@@ -1012,7 +1094,7 @@ soap_status ctx_set_mask(soap_ctx* c, const soap_mask* mask) {
       c->err = terr;
       return SOAP_ERR_UNSUPPORTED;
     }
-    HIP_TRY(grow(c->ws_mask, blob.size()));
+    HIP_TRY(grow(c, c->ws_mask, blob.size()));
     c->mask_blob_bytes = blob.size();
     soap_status st = stage_to_device(c, blob.data(), blob.size(), c->ws_mask.ptr);
     if (st != SOAP_OK) return st;
@@ -1042,7 +1124,7 @@ SOAP_API soap_status soap_ccf_rv(soap_ctx* c, const void* flux, int32_t flux_on_
   const void* dflux = flux;
   const size_t in_bytes = (size_t)n_spec * c->P * c->esize;
   if (!flux_on_device) {
-    HIP_TRY(grow(c->ws_specin, in_bytes));
+    HIP_TRY(grow(c, c->ws_specin, in_bytes));
     // through the context's pinned staging, not an asynchronous copy from
     // pageable memory
     soap_status st = stage_to_device(c, flux, in_bytes, c->ws_specin.ptr);
@@ -1051,10 +1133,10 @@ SOAP_API soap_status soap_ccf_rv(soap_ctx* c, const void* flux, int32_t flux_on_
   }
   const int nlb = soap::ccf_line_blocks(nl);
   const size_t ccf_elems = (size_t)n_spec * c->mask_nv;
-  HIP_TRY(grow(c->ws_ccf, c->esize * ccf_elems * nlb));
+  HIP_TRY(grow(c, c->ws_ccf, c->esize * ccf_elems * nlb));
   double* dccf = (ccf_out && ccf_on_device) ? ccf_out : nullptr;
   if (!dccf) {
-    HIP_TRY(grow(c->ws_ccfout, sizeof(double) * ccf_elems));
+    HIP_TRY(grow(c, c->ws_ccfout, sizeof(double) * ccf_elems));
     dccf = static_cast<double*>(c->ws_ccfout.ptr);
   }
   {
@@ -1067,7 +1149,7 @@ SOAP_API soap_status soap_ccf_rv(soap_ctx* c, const void* flux, int32_t flux_on_
   if (rv_out) {
     drv = rv_on_device ? rv_out : nullptr;
     if (!drv) {
-      HIP_TRY(grow(c->ws_rv, sizeof(soap_rv) * (size_t)n_spec));
+      HIP_TRY(grow(c, c->ws_rv, sizeof(soap_rv) * (size_t)n_spec));
       drv = static_cast<soap_rv*>(c->ws_rv.ptr);
     }
   }
@@ -1097,7 +1179,7 @@ SOAP_API soap_status soap_ccf_linear_rv(soap_ctx* c, const float* coef, int64_t 
   }
   double* lin = ccf_out;
   if (!lin) {
-    HIP_TRY(grow(c->ws_ccfout, sizeof(double) * (size_t)n * c->mask_nv));
+    HIP_TRY(grow(c, c->ws_ccfout, sizeof(double) * (size_t)n * c->mask_nv));
     lin = static_cast<double*>(c->ws_ccfout.ptr);
   }
   // the fit reads each row into registers before writing it back, so the
@@ -1126,7 +1208,7 @@ SOAP_API soap_status soap_surrogate_rv(soap_ctx* c, const float* coef, const flo
   if (c->ws_sg.bytes < wb) {
     // the workspace is replaced only with the stream idle
     HIP_TRY(hipStreamSynchronize(c->stream));
-    HIP_TRY(grow(c->ws_sg, wb));
+    HIP_TRY(grow(c, c->ws_sg, wb));
   }
   HIP_TRY(soap::launch_sg_rv(c, coef, members, n, n_ens, k, base, base_index, n_base, basis, calib, threshold_kms,
                              rv_out, rv_kms, err_kms, fallback, c->ws_sg.ptr));
@@ -1173,15 +1255,15 @@ SOAP_API soap_status soap_profile_read(soap_ctx* c, soap_profile* out) {
   out->src_arrays = out->con_arrays = 0;
   out->taps_nonzero = out->taps_offsets = out->fma_issued = 0;
   out->last_phases = c->last_phases;
-  if (c->last_phases > 0) {
+  if (c->last_phases > 0 && c->prep[c->last_prep].built) {
     // distinct inputs the last apply walked, from its virtual-group lists
     const int n_chunks = (c->last_phases + c->last_pc - 1) / c->last_pc;
     const size_t wb = (size_t)soap::win_bytes(c->last_pc, (int)c->esize);
     std::vector<int> nvg(n_chunks);
     std::vector<unsigned char> vg((size_t)n_chunks * c->last_vg_cap * wb);
     const soap_ctx::Prep& S = c->prep[c->last_prep];
-    HIP_TRY(hipMemcpy(nvg.data(), S.nvg.ptr, sizeof(int) * n_chunks, hipMemcpyDeviceToHost));
-    HIP_TRY(hipMemcpy(vg.data(), S.vg.ptr, vg.size(), hipMemcpyDeviceToHost));
+    HIP_TRY(hipMemcpy(nvg.data(), S.part(soap::TAB_NWIN), sizeof(int) * n_chunks, hipMemcpyDeviceToHost));
+    HIP_TRY(hipMemcpy(vg.data(), S.part(soap::TAB_WIN), vg.size(), hipMemcpyDeviceToHost));
     std::vector<char> src(3 * c->B, 0), con(3 * c->B, 0);
     const bool per_pixel = c->cmode != SOAP_CONTRAST_SCALAR;
     const bool spot_rows = c->con_spot_stride != 0;  // one spot contrast row per bin

@@ -150,6 +150,25 @@ struct LsfPlan {
 
 }  // namespace soap
 
+namespace soap {
+
+// Parts of a call's tables
+enum {
+  TAB_PAR,   // regions, per-phase region centres and bounding boxes
+  TAB_KFX,   // [n_phases][G][J] fixed-point tap accumulators (kept zero)
+  TAB_K,     // [n_phases][G][J] double
+  TAB_MASK,  // [n_phases][G] bitmask of nonzero offsets
+  TAB_WIN,   // [n_chunks][vg_cap] window records (win_bytes(pc) each)
+  TAB_NWIN,  // [n_chunks] int
+  TAB_N
+};
+// Table sets a caller who is ahead may rotate through: with three, two calls
+// can be pending when the third's tables are built (their kernels are short,
+// so the host must not be held up); larger tables keep to two sets.
+constexpr size_t PREP_SMALL = 8 << 20;
+
+}  // namespace soap
+
 struct soap_ctx {
   int device = 0;
   bool hip_used = false;
@@ -194,27 +213,26 @@ struct soap_ctx {
 
   // per-call workspace (grown on demand, freed by soap_destroy)
   // Per-call tables (region parameters, tap accumulators and taps, window
-  // records).  Table kernels run on the context stream, in set 0, or, when
-  // the caller is ahead of the device, on the side stream, in the next of the
-  // other sets, beside what is running; the context stream then waits for
-  // them before the apply.
+  // records).  Table kernels run on the context stream, or, when the caller is
+  // ahead of the device, on the side stream beside what is running; the context
+  // stream then waits for them before the apply.
   struct Prep {
-    soap::Workspace par;     // regions, per-phase region centres and bounding boxes
-    soap::Workspace Kfx;     // [n_phases][G][J] fixed-point tap accumulators (kept zero)
-    soap::Workspace K;       // [n_phases][G][J] double
-    soap::Workspace mask64;  // [n_phases][G] bitmask of nonzero offsets
-    soap::Workspace vg;      // [n_chunks][vg_cap] window records (win_bytes(pc) each)
-    soap::Workspace nvg;     // [n_chunks] int
-    hipEvent_t done = nullptr;  // side sets: recorded on the side stream after the tables
+    soap::Workspace mem;  // every part (one allocation: see grow_tables)
+    size_t at[soap::TAB_N + 1] = {};  // place of each part, then the end
+    hipEvent_t done = nullptr;  // recorded on the side stream after the tables
     unsigned seq = 0;           // call that last used the set
     bool used = false;          // by any call
-    bool kfx_dirty = false;     // a call stopped between accumulation and clearing
+    bool built = false;         // the tables of call seq are whole
+    bool kfx_dirty = false;     // the accumulators are not zero: new memory, or a call stopped before clearing them
+    template <typename T = void>
+    T* part(int i) const {
+      return reinterpret_cast<T*>(static_cast<unsigned char*>(mem.ptr) + at[i]);
+    }
   };
-  static constexpr int NPREP = 4;  // set 0, and three for the side stream
+  static constexpr int NPREP = 3;  // two for tables past PREP_SMALL bytes
   Prep prep[NPREP];
-  int prep_next = 1, last_prep = 0;
+  int last_prep = 0;
   hipStream_t side = nullptr;  // created by the first call that uses it
-  bool tables_open = false;    // a call stopped between its table kernels and its apply
   soap::Workspace ws_flux;     // host-output staging for fluxes
   soap::Workspace ws_ccf;      // partial CCFs
   soap::Workspace ws_ccfout;   // [n_spec][n_v] double
@@ -277,6 +295,9 @@ struct Plan {
   int vg_cap = 0;   // virtual groups per chunk
   int pc = 0;       // phases per chunk of the tables
 };
+
+// dev_malloc; when there is no room, the contexts' spare table sets make some
+hipError_t dev_malloc_for(soap_ctx* const* ctxs, int n, void** p, size_t bytes);
 
 // ---- launchers (each enqueues on ctx->stream; return hipError_t) ----------
 hipError_t launch_geom(soap_ctx* c);

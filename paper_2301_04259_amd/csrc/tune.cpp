@@ -104,7 +104,7 @@ SOAP_API soap_status soap_autotune(soap_ctx* c, const soap_region* regions, int3
   }
   std::memset(out, 0, sizeof *out);
   void* tmp = nullptr;
-  if (soap::dev_malloc(&tmp, (size_t)std::max(1, n_phases) * c->P * c->esize) != hipSuccess) {
+  if (soap::dev_malloc_for(&c, 1, &tmp, (size_t)std::max(1, n_phases) * c->P * c->esize) != hipSuccess) {
     c->err = std::string("autotune: no device memory for a trial output") + soap::dev_cap_note();
     return SOAP_ERR_OOM;
   }
@@ -145,7 +145,7 @@ SOAP_API soap_status soap_autotune(soap_ctx* c, const soap_region* regions, int3
   {
     soap_ctx::Prep& S = c->prep[c->last_prep];
     std::vector<int> nvg(pl.n_chunks);
-    if (hipMemcpy(nvg.data(), S.nvg.ptr, sizeof(int) * pl.n_chunks, hipMemcpyDeviceToHost) != hipSuccess)
+    if (hipMemcpy(nvg.data(), S.part(soap::TAB_NWIN), sizeof(int) * pl.n_chunks, hipMemcpyDeviceToHost) != hipSuccess)
       return fail(SOAP_ERR_HIP, "autotune: reading window counts failed");
     for (int v : nvg) tot += v;
   }
@@ -188,10 +188,10 @@ SOAP_API soap_status soap_autotune(soap_ctx* c, const soap_region* regions, int3
     for (int d : kDepths) {
       for (int o : kOrders) {
         for (int r = 0; r < 2; ++r)
-          (void)soap::launch_apply_shape(c, pl, S.vg.ptr, static_cast<const int*>(S.nvg.ptr), tmp, d, o, c->stream);
+          (void)soap::launch_apply_shape(c, pl, S.part(soap::TAB_WIN), S.part<int>(soap::TAB_NWIN), tmp, d, o, c->stream);
         (void)hipEventRecord(e0, c->stream);
         for (int r = 0; r < kReps; ++r)
-          (void)soap::launch_apply_shape(c, pl, S.vg.ptr, static_cast<const int*>(S.nvg.ptr), tmp, d, o, c->stream);
+          (void)soap::launch_apply_shape(c, pl, S.part(soap::TAB_WIN), S.part<int>(soap::TAB_NWIN), tmp, d, o, c->stream);
         (void)hipEventRecord(e1, c->stream);
         if (hipEventSynchronize(e1) != hipSuccess || hipGetLastError() != hipSuccess) {
           done_events();
