@@ -174,6 +174,33 @@ hipError_t grow(soap_ctx* c, soap::Workspace& w, size_t bytes) {
   return e;
 }
 
+constexpr size_t PIN_BYTES = soap_ctx::PIN_WORD + soap_ctx::NSLOT * soap_ctx::PIN_SLOT + soap_ctx::PIN_STAGE;
+
+// the context's block of pinned memory
+hipError_t ensure_pin(soap_ctx* c) {
+  if (c->pin) return hipSuccess;
+  const hipError_t e =
+      hipHostMalloc(reinterpret_cast<void**>(&c->pin), PIN_BYTES, hipHostMallocMapped | hipHostMallocCoherent);
+  if (e != hipSuccess) return e;
+  c->started = reinterpret_cast<unsigned*>(c->pin);
+  *c->started = c->call_seq;
+  for (int k = 0; k < soap_ctx::NSLOT; ++k) {
+    c->slot[k] = c->pin + soap_ctx::PIN_WORD + k * soap_ctx::PIN_SLOT;
+    c->slot_bytes[k] = soap_ctx::PIN_SLOT;
+  }
+  c->pinned = c->pin + soap_ctx::PIN_WORD + soap_ctx::NSLOT * soap_ctx::PIN_SLOT;
+  c->pinned_bytes = soap_ctx::PIN_STAGE;
+  return hipSuccess;
+}
+
+bool in_pin(const soap_ctx* c, const void* p) {
+  const uintptr_t q = reinterpret_cast<uintptr_t>(p), b = reinterpret_cast<uintptr_t>(c->pin);
+  return b && q >= b && q < b + PIN_BYTES;
+}
+
+// gives back an allocation of its own, not a part of the block
+hipError_t free_pinned(const soap_ctx* c, void* p) { return !p || in_pin(c, p) ? hipSuccess : hipHostFree(p); }
+
 void destroy_ctx(soap_ctx* c) {
   if (!c) return;
   if (c->hip_used) {
@@ -195,10 +222,9 @@ void destroy_ctx(soap_ctx* c) {
     (void)hipEventDestroy(p.a);
     (void)hipEventDestroy(p.b);
   }
-  for (void* p : c->slot)
-    if (p) (void)hipHostFree(p);
-  if (c->started) (void)hipHostFree(c->started);
-  if (c->pinned) (void)hipHostFree(c->pinned);
+  for (void* p : c->slot) (void)free_pinned(c, p);
+  (void)free_pinned(c, c->pinned);
+  if (c->pin) (void)hipHostFree(c->pin);
   if (c->pinned_done) (void)hipEventDestroy(c->pinned_done);
   delete c;
 }
@@ -427,16 +453,14 @@ soap_status init_impl(const soap_star_desc* d, soap_ctx* c) {
 // copy a small host block to device memory through pinned staging; the host
 // waits for the previous staging copy before overwriting the buffer
 soap_status stage_to_device(soap_ctx* c, const void* src, size_t bytes, void* dst) {
+  HIP_TRY(ensure_pin(c));
+  HIP_TRY(hipEventSynchronize(c->pinned_done));
   if (c->pinned_bytes < bytes) {
-    HIP_TRY(hipEventSynchronize(c->pinned_done));
-    if (c->pinned) HIP_TRY(hipHostFree(c->pinned));
+    HIP_TRY(free_pinned(c, c->pinned));
     c->pinned = nullptr;
     c->pinned_bytes = 0;
-    size_t want = std::max<size_t>(bytes, 64 * 1024);
-    HIP_TRY(hipHostMalloc(&c->pinned, want, hipHostMallocDefault));
-    c->pinned_bytes = want;
-  } else {
-    HIP_TRY(hipEventSynchronize(c->pinned_done));
+    HIP_TRY(hipHostMalloc(&c->pinned, bytes, hipHostMallocDefault));
+    c->pinned_bytes = bytes;
   }
   std::memcpy(c->pinned, src, bytes);
   HIP_TRY(hipMemcpyAsync(dst, c->pinned, bytes, hipMemcpyHostToDevice, c->stream));
@@ -619,12 +643,7 @@ hipError_t grow_tables(soap_ctx::Prep& S, const TableSizes& z, bool least) {
 // on the context stream.
 hipError_t choose_prep(soap_ctx* c, const TableSizes& z, int* sidx, hipStream_t* st) {
   hipError_t e;
-  if (!c->started) {
-    if ((e = hipHostMalloc(reinterpret_cast<void**>(&c->started), 64, hipHostMallocMapped | hipHostMallocCoherent)) !=
-        hipSuccess)
-      return e;
-    *c->started = c->call_seq;
-  }
+  if ((e = ensure_pin(c)) != hipSuccess) return e;
   *st = c->stream;
   if (__atomic_load_n(c->started, __ATOMIC_ACQUIRE) != c->call_seq) {
     if (!c->side && (e = hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking)) != hipSuccess) return e;
@@ -749,12 +768,11 @@ soap_status active_impl(soap_ctx* c, const soap_region* regions, int32_t n_regio
   const int k = (int)(seq % soap_ctx::NSLOT);
   HIP_TRY(wait_started(c, seq - soap_ctx::NSLOT));
   if (c->slot_bytes[k] < par_bytes) {
-    if (c->slot[k]) HIP_TRY(hipHostFree(c->slot[k]));
+    HIP_TRY(free_pinned(c, c->slot[k]));
     c->slot[k] = nullptr;
     c->slot_bytes[k] = 0;
-    const size_t want = std::max<size_t>(par_bytes, 16 * 1024);
-    HIP_TRY(hipHostMalloc(&c->slot[k], want, hipHostMallocMapped | hipHostMallocCoherent));
-    c->slot_bytes[k] = want;
+    HIP_TRY(hipHostMalloc(&c->slot[k], par_bytes, hipHostMallocMapped | hipHostMallocCoherent));
+    c->slot_bytes[k] = par_bytes;
   }
   unsigned char* host = static_cast<unsigned char*>(c->slot[k]);
   soap::Region* hr = reinterpret_cast<soap::Region*>(host);
@@ -769,7 +787,12 @@ soap_status active_impl(soap_ctx* c, const soap_region* regions, int32_t n_regio
   std::memcpy(host + reg_bytes, phases, sizeof(double) * n_phases);
   if (pj_host) std::memcpy(host + reg_bytes + ph_bytes, pj_host, sizeof(int2) * n_phases);
   void* dev_view = nullptr;
-  HIP_TRY(hipHostGetDevicePointer(&dev_view, c->slot[k], 0));
+  if (in_pin(c, c->slot[k])) {
+    HIP_TRY(hipHostGetDevicePointer(&dev_view, c->pin, 0));
+    dev_view = static_cast<unsigned char*>(dev_view) + (host - c->pin);
+  } else {
+    HIP_TRY(hipHostGetDevicePointer(&dev_view, c->slot[k], 0));
+  }
   const unsigned char* dev_par = static_cast<const unsigned char*>(dev_view);
   const soap::Region* d_reg = reinterpret_cast<const soap::Region*>(dev_par);
   const double* d_ph = reinterpret_cast<const double*>(dev_par + reg_bytes);

@@ -239,6 +239,11 @@ struct soap_ctx {
   soap::Workspace ws_rv;       // [n_spec] soap_rv
   soap::Workspace ws_mask;     // [n_lines] double2 (u, w)
   soap::Workspace ws_specin;   // host-input staging for ccf
+  // pinned memory, one block (each costs 25 to 30 us, whatever its size): the
+  // word `started`, the parameter slots and the staging buffer; a slot or buffer
+  // that has to be larger is an allocation of its own
+  static constexpr size_t PIN_WORD = 64, PIN_SLOT = 16 << 10, PIN_STAGE = 128 << 10;
+  unsigned char* pin = nullptr;
   void* pinned = nullptr;      // host staging for the mask upload
   size_t pinned_bytes = 0;
   hipEvent_t pinned_done = nullptr;
