@@ -405,7 +405,6 @@ static soap_status create_impl(soap_ctx* const* ctxs, int32_t n_cfg, const soap_
       if (std::find(seen.begin(), seen.end(), c) != seen.end()) continue;
       seen.push_back(c);
       if ((e = hipStreamSynchronize(c->stream)) != hipSuccess) return fail("context stream", e);
-      if (c->side && (e = hipStreamSynchronize(c->side)) != hipSuccess) return fail("context stream", e);
     }
   }
   // Every launch of one run: with fork_join, work per configuration spreads

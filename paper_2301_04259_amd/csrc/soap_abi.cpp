@@ -13,6 +13,8 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <memory>
+#include <mutex>
 #include <new>
 #include <string>
 #include <vector>
@@ -149,6 +151,10 @@ bool free_spare_tables(soap_ctx* c) {
 
 }  // namespace
 
+soap::StreamShare::~StreamShare() {
+  if (side) (void)hipStreamDestroy(side);
+}
+
 hipError_t soap::dev_malloc_for(soap_ctx* const* ctxs, int n, void** p, size_t bytes) {
   hipError_t e = soap::dev_malloc(p, bytes);
   if (!is_oom(e)) return e;
@@ -172,6 +178,29 @@ hipError_t grow(soap_ctx* c, soap::Workspace& w, size_t bytes) {
   hipError_t e = soap::dev_malloc_for(&c, 1, &w.ptr, want);
   if (e == hipSuccess) w.bytes = want;
   return e;
+}
+
+// the record of a stream, made by its first context
+std::shared_ptr<soap::StreamShare> share_of(int device, hipStream_t stream) {
+  static std::mutex mu;
+  static auto* all = new std::vector<std::weak_ptr<soap::StreamShare>>;
+  std::lock_guard<std::mutex> lk(mu);
+  std::shared_ptr<soap::StreamShare> found;
+  size_t n = 0;
+  for (auto& w : *all) {
+    auto s = w.lock();
+    if (!s) continue;
+    if (s->device == device && s->stream == stream) found = s;
+    (*all)[n++] = w;
+  }
+  all->resize(n);
+  if (!found) {
+    found = std::make_shared<soap::StreamShare>();
+    found->device = device;
+    found->stream = stream;
+    all->push_back(found);
+  }
+  return found;
 }
 
 constexpr size_t PIN_BYTES = soap_ctx::PIN_WORD + soap_ctx::NSLOT * soap_ctx::PIN_SLOT + soap_ctx::PIN_STAGE;
@@ -204,8 +233,12 @@ hipError_t free_pinned(const soap_ctx* c, void* p) { return !p || in_pin(c, p) ?
 void destroy_ctx(soap_ctx* c) {
   if (!c) return;
   if (c->hip_used) {
+    // (table kernels of the side stream are waited for on this stream)
     (void)hipStreamSynchronize(c->stream);
-    if (c->side) (void)hipStreamSynchronize(c->side);
+  }
+  if (c->share) {
+    std::lock_guard<std::mutex> lk(c->share->mu);
+    if (c->share->started == c->started) c->share->started = nullptr;
   }
   void* bufs[] = {c->d_mu, c->d_col_c, c->d_col_w, c->d_colW, c->d_Kq, c->d_Kq_fx, c->d_rows};
   for (void* p : bufs)
@@ -217,7 +250,6 @@ void destroy_ctx(soap_ctx* c) {
     free_tables(S);
     if (S.done) (void)hipEventDestroy(S.done);
   }
-  if (c->side) (void)hipStreamDestroy(c->side);
   for (auto& p : c->pending) {
     (void)hipEventDestroy(p.a);
     (void)hipEventDestroy(p.b);
@@ -343,6 +375,7 @@ soap_status init_impl(const soap_star_desc* d, soap_ctx* c) {
 
   c->hip_used = true;
   HIP_TRY(hipGetDevice(&c->device));
+  c->share = share_of(c->device, c->stream);
   // the allocation-free entry point's scratch on this device (its status is
   // kept and reported by that entry point)
   (void)soap::scratch_setup(c->device);
@@ -629,9 +662,31 @@ hipError_t grow_tables(soap_ctx::Prep& S, const TableSizes& z, bool least) {
   return hipSuccess;
 }
 
+// the side stream when the caller is ahead of the device, else null
+hipError_t side_if_ahead(soap_ctx* c, hipStream_t* side) {
+  soap::StreamShare& sh = *c->share;
+  std::lock_guard<std::mutex> lk(sh.mu);
+  bool ahead;
+  if (sh.started) {
+    ahead = __atomic_load_n(sh.started, __ATOMIC_ACQUIRE) != sh.seq;
+  } else {
+    const hipError_t e = hipStreamQuery(c->stream);
+    ahead = e == hipErrorNotReady;
+    if (e != hipSuccess) (void)hipGetLastError();
+  }
+  if (!ahead) return hipSuccess;
+  if (!sh.side) {
+    const hipError_t e = hipStreamCreateWithFlags(&sh.side, hipStreamNonBlocking);
+    if (e != hipSuccess) return e;
+  }
+  *side = sh.side;
+  return hipSuccess;
+}
+
 // The table set of the next call, and the stream of its table kernels.  On the
 // context stream any set will do: the stream keeps the order.  When the caller
-// is ahead of the device (the last call's apply has not begun) the table
+// is ahead of the device (the apply of the stream's last call, by any context,
+// has not begun; before the first such call, the stream is busy) the table
 // kernels, short and far from filling the chip, run beside what is pending
 // instead: a 100-phase series enqueued over and over takes 76 us a call so, 100
 // on one stream.  They take the set that was used longest ago, whose apply is
@@ -645,8 +700,9 @@ hipError_t choose_prep(soap_ctx* c, const TableSizes& z, int* sidx, hipStream_t*
   hipError_t e;
   if ((e = ensure_pin(c)) != hipSuccess) return e;
   *st = c->stream;
-  if (__atomic_load_n(c->started, __ATOMIC_ACQUIRE) != c->call_seq) {
-    if (!c->side && (e = hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking)) != hipSuccess) return e;
+  hipStream_t side = nullptr;
+  if ((e = side_if_ahead(c, &side)) != hipSuccess) return e;
+  if (side) {
     size_t all = 0;
     for (size_t b : z.bytes) all += b;
     const int n = all <= soap::PREP_SMALL ? soap_ctx::NPREP : 2;
@@ -658,7 +714,7 @@ hipError_t choose_prep(soap_ctx* c, const TableSizes& z, int* sidx, hipStream_t*
     if (!S.done && (e = hipEventCreateWithFlags(&S.done, hipEventDisableTiming)) != hipSuccess) return e;
     if (tables_fit(S, z) || (e = grow_tables(S, z, false)) == hipSuccess) {
       *sidx = k;
-      *st = c->side;
+      *st = side;
       return hipSuccess;
     }
     if (!is_oom(e)) return e;
@@ -844,6 +900,11 @@ soap_status active_impl(soap_ctx* c, const soap_region* regions, int32_t n_regio
   }
   idle.open = false;
   c->call_seq = seq;
+  {
+    std::lock_guard<std::mutex> lk(c->share->mu);
+    c->share->started = c->started;
+    c->share->seq = seq;
+  }
   S.seq = seq;
   S.used = S.built = true;
   c->last_prep = sidx;
@@ -1240,7 +1301,6 @@ SOAP_API soap_status soap_surrogate_rv(soap_ctx* c, const float* coef, const flo
 
 SOAP_API soap_status soap_profile_enable(soap_ctx* c, int32_t on) {
   if (!c) return SOAP_ERR_ARG;
-  if (c->side) HIP_TRY(hipStreamSynchronize(c->side));
   HIP_TRY(hipStreamSynchronize(c->stream));
   for (auto& p : c->pending) {
     (void)hipEventDestroy(p.a);
@@ -1257,7 +1317,6 @@ SOAP_API soap_status soap_profile_read(soap_ctx* c, soap_profile* out) {
   if (!c) return SOAP_ERR_ARG;
   std::string& err = c->err;
   ARG_CHECK(out != nullptr, "out is NULL");
-  if (c->side) HIP_TRY(hipStreamSynchronize(c->side));
   HIP_TRY(hipStreamSynchronize(c->stream));
   for (auto& p : c->pending) {
     float ms = 0.f;
@@ -1344,7 +1403,6 @@ SOAP_API soap_status soap_profile_read(soap_ctx* c, soap_profile* out) {
 
 SOAP_API soap_status soap_sync(soap_ctx* c) {
   if (!c) return SOAP_ERR_ARG;
-  if (c->side) HIP_TRY(hipStreamSynchronize(c->side));
   HIP_TRY(hipStreamSynchronize(c->stream));
   return SOAP_OK;
 }

@@ -7,6 +7,8 @@
 #include <cstdint>
 #include <cstdio>
 #include <cstring>
+#include <memory>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -162,6 +164,20 @@ enum {
   TAB_NWIN,  // [n_chunks] int
   TAB_N
 };
+// What the contexts on one stream share: the last synthesis call that any of
+// them enqueued (a word that takes `seq` when the call's apply begins), which
+// tells whether the caller is ahead of the device, and the side stream of the
+// table kernels.  Freed with the last of the contexts.
+struct StreamShare {
+  int device = 0;
+  hipStream_t stream = nullptr;
+  std::mutex mu;                     // guards what follows
+  const unsigned* started = nullptr;  // a word of that call's context (null: no call, or its context is gone)
+  unsigned seq = 0;
+  hipStream_t side = nullptr;  // created by the first call that is ahead
+  ~StreamShare();
+};
+
 // Table sets a caller who is ahead may rotate through: with three, two calls
 // can be pending when the third's tables are built (their kernels are short,
 // so the host must not be held up); larger tables keep to two sets.
@@ -232,7 +248,7 @@ struct soap_ctx {
   static constexpr int NPREP = 3;  // two for tables past PREP_SMALL bytes
   Prep prep[NPREP];
   int last_prep = 0;
-  hipStream_t side = nullptr;  // created by the first call that uses it
+  std::shared_ptr<soap::StreamShare> share;  // with the other contexts on this stream
   soap::Workspace ws_flux;     // host-output staging for fluxes
   soap::Workspace ws_ccf;      // partial CCFs
   soap::Workspace ws_ccfout;   // [n_spec][n_v] double

@@ -152,3 +152,43 @@ def test_byte_cap_that_holds_the_sets(busy, monkeypatch, n_phases, sets):
     q = np.empty(star.n_pix, dtype=np.float32)
     L.soap_quiet_spectrum(ctx, q)
     L.soap_destroy(ctx)
+
+
+def test_threads_with_contexts_on_one_stream():
+    import threading
+
+    stars = [_star(61 + i, W.PREC_FP32, 1200 + 500 * i, 11 + 40 * i, 2 + i) for i in range(2)]
+    calls = [_calls(s, 40, 9 + i) for i, s in enumerate(stars)]
+    want, outs, ctxs = [], [], []
+    for s, c in zip(stars, calls):
+        ref = L.soap_grid_init(s)
+        want.append(_single(ref, s, c))
+        L.soap_destroy(ref)
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        for s, c in zip(stars, calls):
+            ctxs.append(L.soap_grid_init(s))
+            outs.append([_out(s, len(p)) for _, p in c])
+    torch.cuda.synchronize()
+    print("[sets] two threads, one stream", flush=True)
+    errors = []
+
+    def work(i):
+        try:
+            for k, (regions, phases) in enumerate(calls[i]):
+                L.soap_active_spectra(ctxs[i], regions, phases, W.EFFECT_TOT, outs[i][k])
+            if i == 0:  # this context goes while the other one's calls are pending
+                L.soap_destroy(ctxs[0])
+        except Exception as e:  # noqa: BLE001
+            errors.append(e)
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    torch.cuda.synchronize()
+    assert not errors, errors
+    for i in range(2):
+        for k in range(len(calls[i])):
+            assert torch.equal(outs[i][k], want[i][k]), (i, k)
