@@ -249,9 +249,12 @@ int params_lanes(int max_reg) {
 // bounding box of the caps that reach the visible hemisphere.  One lane per
 // (phase, region), since a centre's sines and cosines are the kernel's time
 // (100 phases of 3 regions: 9.0 us with one thread per phase walking its
-// regions, 6.5 so; 50 of 6 regions: 14.6 and 8.2).  The regions and phases are
-// read once from the caller's parameter block, so the weight kernel's many blocks read device
-// memory.  Block bid of nblk (PARAMS_THREADS each).
+// regions, 6.5 so; 50 of 6 regions: 14.6 and 8.2).  Every lane reads its
+// region from the caller's parameter block in host memory, which costs less
+// than a pass through LDS would save (64 regions over 1000 and 4000 phases: 9.3
+// and 17.0 us; the list read once per block of several phases and staged, 13.2
+// and 26.9); the weight kernel's many blocks read the copy in device memory.
+// Block bid of nblk (PARAMS_THREADS each).
 constexpr int PARAMS_THREADS = 128;
 __device__ __forceinline__ void params_block(const ParamsArgs& a, int bid, int nblk) {
   const int N = a.N, n_reg = a.n_reg, max_reg = a.max_reg, n_ph = a.n_ph, lanes = a.lanes;
@@ -521,9 +524,16 @@ __global__ void __launch_bounds__(WEIGHT_WAVES * 64) k_weights(WeightsArgs a) {
 // phases (100 phases: 12.9 us with 40 blocks each, 14.4 with 20, 15.6 with 10),
 // few enough that a call over many phases is not spent on launching blocks (500
 // spots x 8 phases, 75 blocks per phase, most of them without a column: 93 us;
-// 34 with 4, 31 with 2, 35 with 1).
-int weight_parts(int N, int n_ph) {
+// 34 with 4, 31 with 2, 35 with 1).  With long region lists a set of columns is
+// work enough for a block, and long blocks leave the chip idle at the end: the
+// stage of 64 regions takes 131 and 934 us over 100 and 1000 phases with a block
+// per set (75), 162 and 1024 with 32 and 4; over 4000 phases 3677 with 4, 3750
+// with 2.  32 regions: 59 and 346 against 71 and 365, over 4000 phases 1121
+// against 1141, over 20000 5990 against 5822; 24 regions, a block per set: 47 and
+// 219 against 54 and 219.
+int weight_parts(int N, int n_ph, int max_reg) {
   const int cols = (N + WEIGHT_WAVES - 1) / WEIGHT_WAVES;
+  if (max_reg >= 32) return n_ph <= 2048 ? cols : std::min(cols, std::max(2, std::min(4, 32768 / n_ph)));
   return std::min(cols, std::max(2, 4096 / std::max(1, n_ph)));
 }
 
@@ -652,7 +662,7 @@ ParamsArgs params_args(const soap_ctx* c, const Plan& pl, const Region* d_reg, i
 
 WeightsArgs weights_args(const soap_ctx* c, const Plan& pl, int n_reg, int max_reg, const int2* pj,
                          const WeightsOut& o) {
-  return WeightsArgs{c->N,     c->B,  c->J,       c->jmin,    pl.G,      pl.paired, weight_parts(c->N, pl.n_ph),
+  return WeightsArgs{c->N,     c->B,  c->J,       c->jmin,    pl.G,      pl.paired, weight_parts(c->N, pl.n_ph, max_reg),
                      pl.effect, n_reg, max_reg,   c->u1,      c->u2,     c->d_mu,   c->d_col_c,
                      c->d_col_w, o.reg, pj,       o.cen,      o.box,     o.Kfx};
 }
@@ -734,7 +744,7 @@ hipError_t launch_weights(soap_ctx* c, const Plan& pl, const Region* d_reg, int 
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const int2* pj = d_pj ? o.pj : nullptr;
-  const int parts = weight_parts(c->N, pl.n_ph);
+  const int parts = weight_parts(c->N, pl.n_ph, max_reg);
   dim3 grid((unsigned)parts * (unsigned)pl.n_ph);
   if (c->diff_rot != 0.0) {
     const size_t lds = (size_t)WEIGHT_WAVES * pl.G * c->J * sizeof(unsigned long long);
