@@ -483,9 +483,11 @@ typedef struct {
   int64_t last_phases;       /* last apply: number of phases                */
   /* last apply's arithmetic per output pixel, summed over its phases and
    * windows: non-zero taps (one FMA each per pixel), window offsets with any
-   * non-zero tap (one FMA each to form the difference), and the FMAs of the
-   * phase groups (four phases in FP32, two in FP64) that have a non-zero tap
-   * at an offset, plus one difference per such offset                      */
+   * non-zero tap (one FMA each to form the difference), and the operations
+   * the kernel issues: it walks a window's offsets up to the last one with a
+   * tap, forms a difference at each (not for split tables) and adds whole
+   * groups of phases: FP32 eight at a time (of 8 always, of 16 those with a
+   * tap), FP64 the pairs that have a tap                                     */
   int64_t taps_nonzero;
   int64_t taps_offsets;
   int64_t fma_issued;

@@ -478,6 +478,21 @@ int apply_table_mode(const soap_ctx* c, const Plan& pl) {
   return (c->cmode != SOAP_CONTRAST_SCALAR && pl.effect != SOAP_EFFECT_BCONV) ? MODE_CONTRAST : MODE_PAIRED;
 }
 
+// as consume() walks a window: the offsets up to the mask's last one, empty ones
+// too; per offset a difference unless the table is split, and FP32 phases in
+// pairs of groups (of the only pair always), FP64 phases in the groups with a tap
+int window_fmas(unsigned gmask, int pc, int esize, int mode) {
+  const int gp = win_group(esize), ng = pc / gp, step = esize == 4 ? 2 : 1;
+  int n = 0;
+  for (int q = 0; q < APPLY_JW && (q == 0 || (gmask >> (q * ng))); ++q) {
+    const unsigned bits = gmask >> (q * ng);
+    if (mode != MODE_SPLIT) ++n;
+    for (int g = 0; g < ng; g += step)
+      if ((esize == 4 && ng == 2) || ((bits >> g) & ((1u << step) - 1u))) n += step * gp;
+  }
+  return n;
+}
+
 namespace {
 
 template <typename T, int PC, int MODE>

@@ -919,6 +919,7 @@ soap_status active_impl(soap_ctx* c, const soap_region* regions, int32_t n_regio
   c->last_vg_cap = pl.vg_cap;
   c->last_pc = pl.pc;
   c->last_paired = pl.paired;
+  c->last_mode = soap::apply_table_mode(c, pl);
   if (dflux != flux) {
     HIP_TRY(hipStreamSynchronize(c->stream));
     HIP_TRY(hipMemcpy(flux, dflux, out_bytes, hipMemcpyDeviceToHost));
@@ -1355,15 +1356,7 @@ SOAP_API soap_status soap_profile_read(soap_ctx* c, soap_profile* out) {
         const unsigned char* rec = vg.data() + ((size_t)ch * c->last_vg_cap + v) * wb;
         std::memcpy(&h, rec, sizeof(h));
         {
-          // one mask bit per (offset, group of phases) with a non-zero tap:
-          // each bit costs one FMA per phase of the group and pixel, each
-          // offset with a bit one difference formation
-          const int gp = soap::win_group((int)c->esize), ng = c->last_pc / gp;
-          int bits = 0, offs = 0;
-          for (unsigned m = h.gmask; m; m &= m - 1) ++bits;
-          for (int q = 0; q < soap::APPLY_JW; ++q)
-            if ((h.gmask >> (q * ng)) & ((1u << ng) - 1u)) ++offs;
-          out->fma_issued += (int64_t)bits * gp + offs;
+          out->fma_issued += soap::window_fmas(h.gmask, c->last_pc, (int)c->esize, c->last_mode);
           for (int q = 0; q < soap::APPLY_JW; ++q) {
             bool any = false;
             for (int pp = 0; pp < c->last_pc; ++pp) {

@@ -287,7 +287,7 @@ struct soap_ctx {
   soap::LsfPlan lsf;
   soap::Workspace ws_lsf;  // synthesis output before the lowering
   soap::Workspace ws_sg;   // surrogate RVs: mean-prediction CCFs, sensitivities, flags
-  int last_phases = 0, last_effect = 0, last_vg_cap = 0, last_paired = 0, last_pc = 0;
+  int last_phases = 0, last_effect = 0, last_vg_cap = 0, last_paired = 0, last_pc = 0, last_mode = 0;
 
   // cached mask
   std::vector<double> mask_lnl, mask_w;
@@ -413,6 +413,8 @@ hipError_t table_batch_launch(const TableBatch& tb, hipStream_t st);
 // paired tables without a contrast (D = A - S_q), and with one (D = C A - S_q)
 enum { MODE_SPLIT = 0, MODE_PAIRED = 1, MODE_CONTRAST = 2 };
 int apply_table_mode(const soap_ctx* c, const Plan& pl);
+// operations per pixel that the apply kernel issues for one window
+int window_fmas(unsigned gmask, int pc, int esize, int mode);
 hipError_t launch_apply(soap_ctx* c, const Plan& pl, const void* d_win, const int* d_nvg, void* d_flux, unsigned seq);
 // apply with an explicit shape (threads per block, windows staged per LDS
 // pass) on stream st
