@@ -152,7 +152,12 @@ static soap_status create_impl(soap_ctx* const* ctxs, int32_t n_cfg, const soap_
     }
     pl.G = (pl.paired ? 2 : 3) * c->B;
     pl.n_slabs = (c->N + soap::SLAB_COLS - 1) / soap::SLAB_COLS;
-    // the narrow layout where none is set: the configurations fill the chip together
+    // The narrow layout where none is set: the configurations fill the chip
+    // together, with few windows in common between a configuration's phases.
+    // 24 configurations of 25 to 200 phases and up to 205800 px 880 us narrow,
+    // 886 wide, 8 of them 365 and 391, 3 of them 172 and 181; 12 of up to 60
+    // phases and 20000 px 107 and 142; 48 stars' spots at 2 to 8 phases 537 and
+    // 578.
     pl.pc = c->pc ? c->pc : (c->prec == SOAP_PREC_FP32 ? soap::PC_F32 : soap::PC_F64);
     pl.n_chunks = (np + pl.pc - 1) / pl.pc;
     pl.vg_cap = pl.G * ((c->J + soap::APPLY_JW - 1) / soap::APPLY_JW);

@@ -416,8 +416,8 @@ int apply_table_mode(const soap_ctx* c, const Plan& pl);
 // operations per pixel that the apply kernel issues for one window
 int window_fmas(unsigned gmask, int pc, int esize, int mode);
 hipError_t launch_apply(soap_ctx* c, const Plan& pl, const void* d_win, const int* d_nvg, void* d_flux, unsigned seq);
-// apply with an explicit shape (threads per block, windows staged per LDS
-// pass) on stream st
+// apply with an explicit shape (windows in flight per wave, item order) on
+// stream st
 hipError_t launch_apply_shape(soap_ctx* c, const Plan& pl, const void* d_win, const int* d_nvg, void* d_flux,
                               int depth, int order, hipStream_t st);
 
