@@ -34,7 +34,7 @@ constexpr int CCF_LB = 32;        // mask lines per block (one partial CCF row e
 constexpr int CCF_SB = 8;         // spectra per block
 constexpr int CCF_FEW = 2;        // and in calls of few blocks,
 constexpr int CCF_AHEAD = 3;      // with this many batches of loads in flight
-constexpr int CCF_FEW_BELOW = 128;
+constexpr int CCF_FEW_WAVES = 640;  // few: blocks of CCF_SB with fewer waves than this in all
 constexpr int CCF_THREADS = 512;  // most threads of a block: one per velocity, two velocities each past 512
 constexpr int CCF_MIN_THREADS = 192;  // fewest: the block also stages the pixels
 constexpr int CCF_NV_MAX = 768;   // velocities per grid
@@ -817,13 +817,16 @@ static void launch_ccf_a(const CcfPlan& q, hipStream_t st, const void* d_flux, i
   auto blocks = [&](int sb) { return dim3((unsigned)nlb, (unsigned)((n_spec + sb - 1) / sb)); };
   // Few blocks of CCF_SB spectra leave the chip idle, and each is a chain of
   // batches that wait for their loads: then blocks of CCF_FEW spectra with
-  // CCF_AHEAD batches of loads in flight (one spectrum of 400 lines, 13 blocks:
-  // 13.9 us and 10.9 so; 25 FP64 spectra of 100 lines, 16 blocks: 14.1 and 10.4;
-  // 50 of 1200 lines, 266 blocks: 13.9 and 13.5; 60 FP64 of 2000 lines, 504
-  // blocks: 17.3 and 19.4).
-  const bool few = (int64_t)nlb * blocks(CCF_SB).y < CCF_FEW_BELOW;
+  // CCF_AHEAD batches of loads in flight.  The line lies where the blocks' waves
+  // would fill it (stage times with CCF_SB and so, FP32): 161 velocities, 3 waves
+  // a block, 13 blocks 12.1 and 10.7 us, 125 12.4 and 11.6, 190 13.2 and 12.8, 250
+  // 12.8 and 12.8, 375 13.9 and 15.1; 401 velocities, 7 waves, 13 blocks 12.6 and
+  // 11.2, 75 13.8 and 12.4, 94 14.4 and 14.3, 125 13.3 and 13.7, 190 14.2 and 16.7.
+  // FP64 gains more below it (125 blocks: 12.7 and 11.1, 14.6 and 13.9).
+  const unsigned threads = ccf_threads<A>(q.nv);
+  const bool few = (int64_t)nlb * blocks(CCF_SB).y * (threads / 64) < CCF_FEW_WAVES;
   auto* kernel = few ? &k_ccf<T, A, NPX, STG, CCF_FEW, CCF_AHEAD> : &k_ccf<T, A, NPX, STG, CCF_SB, 1>;
-  hipLaunchKernelGGL(kernel, blocks(few ? CCF_FEW : CCF_SB), dim3(ccf_threads<A>(q.nv)), 0, st, (int)q.P, n_spec,
+  hipLaunchKernelGGL(kernel, blocks(few ? CCF_FEW : CCF_SB), dim3(threads), 0, st, (int)q.P, n_spec,
                      static_cast<const T*>(d_flux), reinterpret_cast<const double2*>(base),
                      reinterpret_cast<const double2*>(base + q.off_edges),
                      reinterpret_cast<const int4*>(base + q.off_batch),
