@@ -110,6 +110,11 @@ void free_all(soap_surrogate* s) {
     if (p) (void)soap::dev_free(p);
 }
 
+bool overlap(const void* a, size_t na, const void* b, size_t nb) {
+  const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+  return x < y + nb && y < x + na;
+}
+
 soap_status ensure_y(soap_surrogate* s, int B) {
   if (B <= s->cap_y) return SOAP_OK;
   SG_HIP(hipStreamSynchronize(s->stream));
@@ -259,24 +264,29 @@ SOAP_API soap_status soap_surrogate_predict(soap_surrogate* s, const float* x_de
   if (!s) return SOAP_ERR_ARG;
   SG_ARG(x_dev && coef_dev, "x and coef must be device arrays");
   SG_ARG(batch >= 16 && batch % 16 == 0 && batch <= (1 << 20), "batch must be a multiple of 16 in [16, 2^20]");
+  const size_t n_mem = sizeof(float) * (size_t)s->n_ens * batch * s->n_out;
+  bool copied = members_dev != nullptr;  // the members come from the library's buffer
   if (soap::sg_rows_fit(s->hidden, s->n_out, false)) {
+    // The row kernel writes members while other rows' inputs are still to be
+    // read: straight to the caller's array unless that is over the inputs (or
+    // the means, which are written before the members then).
+    copied = members_dev && (overlap(members_dev, n_mem, x_dev, sizeof(float) * (size_t)batch * s->n_in) ||
+                             overlap(members_dev, n_mem, coef_dev, sizeof(float) * (size_t)batch * s->n_out));
     float* Y = members_dev;
-    if (!Y) {
+    if (!members_dev || copied) {
       soap_status st = ensure_y(s, batch);
       if (st != SOAP_OK) return st;
       Y = s->Y;
     }
     SG_HIP(soap::sg_rows_forward(s, x_dev, batch, Y));
     SG_HIP(soap::sg_ens_mean(s, batch, Y, coef_dev));
-    return SOAP_OK;
+  } else {
+    soap_status st = ensure_batch(s, batch);
+    if (st != SOAP_OK) return st;
+    SG_HIP(soap::sg_forward(s, x_dev, batch));
+    SG_HIP(soap::sg_ens_mean(s, batch, s->Y, coef_dev));
   }
-  soap_status st = ensure_batch(s, batch);
-  if (st != SOAP_OK) return st;
-  SG_HIP(soap::sg_forward(s, x_dev, batch));
-  SG_HIP(soap::sg_ens_mean(s, batch, s->Y, coef_dev));
-  if (members_dev)
-    SG_HIP(hipMemcpyAsync(members_dev, s->Y, sizeof(float) * (size_t)s->n_ens * batch * s->n_out,
-                          hipMemcpyDeviceToDevice, s->stream));
+  if (copied) SG_HIP(hipMemcpyAsync(members_dev, s->Y, n_mem, hipMemcpyDeviceToDevice, s->stream));
   return SOAP_OK;
 }
 
