@@ -291,8 +291,8 @@ __global__ void k_f32_to_bf16(int64_t n, SgLayout L, int H, int O, int bfrag, co
 // What the weight gradients need goes out transposed in the same order, so that
 // k_sg_grads reads both operands straight into registers; it also updates the
 // parameters.
-// Every output is one MFMA chain over k in steps of 32, and the column sums
-// keep their order, so a step gives bit for bit what the general kernels give.
+// Every output is one MFMA chain over k in steps of 32, as in the general
+// kernels, and the column sums keep their order.
 // Bound by launches and latency at the usual sizes: a step of batch 512, hidden
 // 256, 128 outputs and 4 members takes 17 us of rows (about 3.5 of them before the
 // first product, 2 a layer, of those 1.5 of VALU work on two waves' SiLUs) and 12
