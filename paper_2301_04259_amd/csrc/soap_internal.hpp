@@ -164,16 +164,18 @@ enum {
   TAB_NWIN,  // [n_chunks] int
   TAB_N
 };
-// What the contexts on one stream share: the last synthesis call that any of
-// them enqueued (a word that takes `seq` when the call's apply begins), which
-// tells whether the caller is ahead of the device, and the side stream of the
+// What the contexts on one stream share: the last two synthesis calls that any
+// of them enqueued (a word that takes `seq` when the call's apply begins), which
+// tell whether the caller is ahead of the device, and the side stream of the
 // table kernels.  Freed with the last of the contexts.
 struct StreamShare {
   int device = 0;
   hipStream_t stream = nullptr;
   std::mutex mu;                     // guards what follows
-  const unsigned* started = nullptr;  // a word of that call's context (null: no call, or its context is gone)
-  unsigned seq = 0;
+  struct Call {
+    const unsigned* started = nullptr;  // a word of its context (null: no call, or its context is gone)
+    unsigned seq = 0;
+  } last, before;
   hipStream_t side = nullptr;  // created by the first call that is ahead
   ~StreamShare();
 };
