@@ -24,6 +24,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <type_traits>
 
 #include "soap_internal.hpp"
 #include "wave.hpp"
@@ -1092,7 +1093,9 @@ constexpr int SG_MAX_ENS = 16;
 // one fixed order.
 constexpr int SG_W = 4;
 constexpr int SG_KC = 128;  // components per LDS pass of k_sg_lin
-constexpr int SG_VC = 192;  // velocities per LDS pass of k_sg_spread
+constexpr int SG_VC = 192;  // velocities per LDS pass of k_sg_spread, at most
+// row length of its LDS: whole groups of 16 velocities, and two against bank conflicts
+__host__ __device__ constexpr int sg_spread_ld(int n_v) { return (n_v < SG_VC ? (n_v + 15) & ~15 : SG_VC) + 2; }
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 typedef double f64x2 __attribute__((ext_vector_type(2)));
 typedef double f64x2u __attribute__((ext_vector_type(2), aligned(8)));
@@ -1246,9 +1249,12 @@ __global__ void __launch_bounds__(64) k_sg_fit(int64_t n, int n_v, double v0, do
   }
 }
 
-// EB: members, rounded up; 32 components per wave at a time
-template <int EB>
-__global__ void __launch_bounds__(64 * SG_W) k_sg_spread(int64_t n, int k, int E, int n_v,
+// EB: members, rounded up; W waves per block, 32 components each at a time.  With
+// few components fewer waves per block, and LDS for the velocities there are, so
+// that more blocks are in flight: 8 members, 32 components, 41 velocities, 20000
+// samples 99 us with four waves and room for 192 velocities, 41 so.
+template <int EB, int W>
+__global__ void __launch_bounds__(64 * W) k_sg_spread(int64_t n, int k, int E, int n_v,
                                                          const float* __restrict__ coef,
                                                          const float* __restrict__ members,
                                                          const double* __restrict__ basis,
@@ -1256,9 +1262,10 @@ __global__ void __launch_bounds__(64 * SG_W) k_sg_spread(int64_t n, int k, int E
                                                          double calib, double thr, double* __restrict__ err_kms,
                                                          int* __restrict__ fallback) {
   constexpr int NT = 2;
-  __shared__ double s_dr[SG_W][16][EB];
-  __shared__ __align__(16) double s_g[16][SG_VC + 2];
-  const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
+  __shared__ double s_dr[W][16][EB];
+  extern __shared__ __align__(16) double s_g[];  // [16][ld]
+  const int ld = sg_spread_ld(n_v);
+  const int l = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int c = l & 15, g = l >> 4;
   const int64_t i0 = (int64_t)blockIdx.x * 16;
   double dr[4][EB];
@@ -1267,8 +1274,10 @@ __global__ void __launch_bounds__(64 * SG_W) k_sg_spread(int64_t n, int k, int E
 #pragma unroll
     for (int e = 0; e < EB; ++e) dr[r][e] = 0.0;
   // h_k = sum_v basis[k][v] g_v, then dRV_e = sum_k h_k (y_e,k - coef_k)
-  for (int kb = 0; kb < k; kb += 16 * NT * SG_W) {
-    const int k0 = kb + 16 * NT * w;  // waves past k multiply the last row and add nothing
+  for (int kb = 0; kb < k; kb += 16 * NT * W) {
+    const int k0 = kb + 16 * NT * w;
+    // waves past k only stage
+    const bool mine = k0 < k;
     const double* bp[NT];
 #pragma unroll
     for (int t = 0; t < NT; ++t) bp[t] = basis + (int64_t)min(k0 + 16 * t + c, k - 1) * n_v;
@@ -1287,7 +1296,7 @@ __global__ void __launch_bounds__(64 * SG_W) k_sg_spread(int64_t n, int k, int E
     auto multiply = [&](const Set& o, int v) {
 #pragma unroll
       for (int q = 0; q < 2; ++q) {
-        const f64x2 a = *reinterpret_cast<const f64x2*>(&s_g[c][v + 4 * g + 2 * q]);
+        const f64x2 a = *reinterpret_cast<const f64x2*>(&s_g[c * ld + v + 4 * g + 2 * q]);
 #pragma unroll
         for (int x = 0; x < 2; ++x)
 #pragma unroll
@@ -1299,26 +1308,30 @@ __global__ void __launch_bounds__(64 * SG_W) k_sg_spread(int64_t n, int k, int E
       const int vn = min(SG_VC, n_v - vc), whole = vn & ~15;
       constexpr int D = 3;  // groups in flight; past the last whole one it is read again
       Set o[D];
-      if (whole) {
+      if (mine && whole) {
 #pragma unroll
         for (int d = 0; d + 1 < D; ++d) load(o[d], vc + min(16 * d, whole - 16));
       }
       if ((kb == 0 && vc == 0) || n_v > SG_VC) {
         if (kb || vc) __syncthreads();
-        constexpr int U = 16 * SG_VC / (64 * SG_W);
-        double x[U];  // all loads before the first is waited for
+        constexpr int TR = 4 * W, U = SG_VC / TR;  // threads per sample's row
+        const int row = threadIdx.x / TR, col = threadIdx.x % TR, wide = (vn + 15) & ~15;
+        const double* gr = G + min(i0 + row, n - 1) * n_v + vc;
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-          const int t = threadIdx.x + 64 * SG_W * u;
-          x[u] = G[min(i0 + t / SG_VC, n - 1) * n_v + vc + min(t % SG_VC, vn - 1)];
-        }
+        for (int u0 = 0; u0 < U; u0 += 12) {
+          double x[12];  // all loads before the first is waited for
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-          const int t = threadIdx.x + 64 * SG_W * u;
-          s_g[t / SG_VC][t % SG_VC] = t % SG_VC < vn ? x[u] : 0.0;
+          for (int u = 0; u < 12; ++u)
+            if (TR * (u0 + u) < vn) x[u] = gr[min(col + TR * (u0 + u), vn - 1)];
+#pragma unroll
+          for (int u = 0; u < 12; ++u) {
+            const int v = col + TR * (u0 + u);
+            if (v < wide) s_g[row * ld + v] = v < vn ? x[u] : 0.0;
+          }
         }
         __syncthreads();
       }
+      if (!mine) continue;
       for (int v = 0; v < whole; v += 16 * D) {
 #pragma unroll
         for (int d = 0; d < D; ++d) {
@@ -1337,6 +1350,7 @@ __global__ void __launch_bounds__(64 * SG_W) k_sg_spread(int64_t n, int k, int E
         multiply(e, whole);
       }
     }
+    if (!mine) continue;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int64_t i = min(i0 + g + 4 * r, n - 1);
@@ -1359,8 +1373,10 @@ __global__ void __launch_bounds__(64 * SG_W) k_sg_spread(int64_t n, int k, int E
 #pragma unroll
     for (int e = 0; e < EB; ++e) {
       double x = dr[r][e];
-#pragma unroll
-      for (int off = 1; off < 16; off *= 2) x += __shfl_xor(x, off, 64);
+      x += dpp_f64<DPP_PAIR>(x);
+      x += dpp_f64<DPP_QUAD>(x);
+      x += dpp_f64<DPP_HALF_MIRROR>(x);
+      x += dpp_f64<DPP_MIRROR>(x);
       if (c == 0) s_dr[w][g + 4 * r][e] = x;
     }
   __syncthreads();
@@ -1372,7 +1388,9 @@ __global__ void __launch_bounds__(64 * SG_W) k_sg_spread(int64_t n, int k, int E
     double d[EB], m = 0.0;
 #pragma unroll
     for (int e = 0; e < EB; ++e) {
-      d[e] = (s_dr[0][s][e] + s_dr[1][s][e]) + (s_dr[2][s][e] + s_dr[3][s][e]);
+      if constexpr (W == 4) d[e] = (s_dr[0][s][e] + s_dr[1][s][e]) + (s_dr[2][s][e] + s_dr[3][s][e]);
+      else if constexpr (W == 2) d[e] = s_dr[0][s][e] + s_dr[1][s][e];
+      else d[e] = s_dr[0][s][e];
       if (e < E) m += d[e];
     }
     m /= (double)E;
@@ -1399,15 +1417,17 @@ void launch_sg_rv_n(soap_ctx* c, const float* d_coef, const float* d_members, in
                      d_base_idx, nb, d_basis, Y, flag);
   hipLaunchKernelGGL((k_sg_fit<NPT>), dim3((unsigned)n), dim3(64), 0, c->stream, n, c->mask_nv, c->mask_v0,
                      c->mask_dv, Y, flag, d_rv, d_rv_kms, G);
-  if (E <= 4)
-    hipLaunchKernelGGL((k_sg_spread<4>), grid, block, 0, c->stream, n, k, E, c->mask_nv, d_coef, d_members, d_basis,
-                       G, flag, calib, thr, d_err, d_fallback);
-  else if (E <= 8)
-    hipLaunchKernelGGL((k_sg_spread<8>), grid, block, 0, c->stream, n, k, E, c->mask_nv, d_coef, d_members, d_basis,
-                       G, flag, calib, thr, d_err, d_fallback);
-  else
-    hipLaunchKernelGGL((k_sg_spread<SG_MAX_ENS>), grid, block, 0, c->stream, n, k, E, c->mask_nv, d_coef,
-                       d_members, d_basis, G, flag, calib, thr, d_err, d_fallback);
+  const size_t lds = sizeof(double) * 16 * sg_spread_ld(c->mask_nv);
+  auto spread = [&](auto eb) {
+    constexpr int EB = decltype(eb)::value;
+    const int w = k <= 32 ? 1 : (k <= 64 ? 2 : 4);
+    auto* kernel = w == 1 ? &k_sg_spread<EB, 1> : (w == 2 ? &k_sg_spread<EB, 2> : &k_sg_spread<EB, 4>);
+    hipLaunchKernelGGL(kernel, grid, dim3(64 * w), lds, c->stream, n, k, E, c->mask_nv, d_coef, d_members, d_basis, G,
+                       flag, calib, thr, d_err, d_fallback);
+  };
+  if (E <= 4) spread(std::integral_constant<int, 4>());
+  else if (E <= 8) spread(std::integral_constant<int, 8>());
+  else spread(std::integral_constant<int, SG_MAX_ENS>());
 }
 
 }  // namespace

@@ -49,11 +49,14 @@ constexpr int WIN_HEAD = 32;  // bytes of a window record's header
 // Phases per chunk of a call whose context sets none.  The wide layout halves
 // the copies and differences per phase but also the blocks, and its waves walk
 // the union of more phases' windows: it is taken from four wide blocks per CU
-// on (at about 1000 blocks: 150000 px x 100 phases 35.4 us narrow, 31.8 wide;
-// 206k px x 100 phases, 1407 blocks, 42.9 and 38.7; 60000 px x 60 phases, 236
-// blocks, 20.6 and 27.4; FP64 100003 px x 60 phases, 1568 blocks, 45.4 and
-// 40.2).  Phases with region lists of their own share few windows (500 spots
-// x 8 phases: 107 and 110 us) and stay narrow.
+// on.  Stage times in a series, narrow and wide, FP32, three regions: 205800 px x
+// 100 phases, 1407 blocks, 50.7 and 43.4 us; x 200, 2613 blocks, 82.3 and 71.1;
+// 150000 px x 100, 1029 blocks, 38.2 and 36.9; 205800 px x 72, 1005 blocks, 39.1
+// and 38.5; x 50, 804 blocks, 33.1 and 34.6; 100000 px x 100, 686 blocks, 23.0 and
+// 29.1; 60000 px x 60, 236 blocks, 22.5 and 29.8; FP64 100003 px x 60 phases, 1568
+// blocks, 40.1 and 35.0; x 40, 980 blocks, 30.2 and 32.2.  (20000 px x 1000, 1260
+// blocks: 38.4 and 39.9.)  Phases with region lists of their own share few
+// windows (500 spots x 8 phases: 107 and 110 us) and stay narrow.
 inline int auto_pc(bool fp32, int64_t n_pix, int64_t n_ph, bool own_lists) {
   const int wide = fp32 ? PC_F32_WIDE : PC_F64_WIDE, tile = fp32 ? 1024 : 512;
   const int64_t blocks = ((n_pix + tile - 1) / tile) * ((n_ph + wide - 1) / wide);
