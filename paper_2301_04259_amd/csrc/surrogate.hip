@@ -356,7 +356,14 @@ __global__ void k_f32_to_bf16(int64_t n, SgLayout L, int H, int O, int bfrag, co
 // of gradients, 31 us in all against 139 as 20 launches; batch 4096, 96 against
 // 460.  Row-major weights (64-byte pieces at power-of-two strides) took 26 and
 // 27 us, eight waves a block 19.
-constexpr int sr_waves(bool train) { return train ? 16 : 8; }  // waves per block
+// Waves per block: 16 in training, 8 in inference; 2 in inference of many rows
+// where every layer's columns fit in two waves' tiles (the others would idle: 8
+// networks of 32 hidden units, 20000 rows, 43 us with 8 waves, 25 so).  Of
+// few rows the waves past the columns still help to stage them: below
+// SR_NARROW_ROWS rows of all networks 8 waves (2048 rows of 8 networks 12.4 us
+// by 13.4 with 2).
+constexpr int SR_TRAIN = 16, SR_INFER = 8, SR_NARROW = 2;
+constexpr int SR_NARROW_COLS = SR_NARROW * 2 * 16, SR_NARROW_ROWS = 49152;
 constexpr int SR_MT = 2;  // row tiles per block of large inference batches
 
 namespace {
@@ -459,11 +466,11 @@ __device__ __forceinline__ void rows_mm(RowsB<NT>& first, const __bf16* As, int 
 
 }  // namespace
 
-template <int MT, bool TRAIN>
-__global__ void __launch_bounds__(64 * sr_waves(TRAIN), MT == 1 ? 1 : 4) k_sg_rows(SgRows a) {
+template <int MT, bool TRAIN, int W>
+__global__ void __launch_bounds__(64 * W, MT == 1 ? 1 : 4) k_sg_rows(SgRows a) {
   extern __shared__ __align__(16) unsigned char lds[];
   constexpr int R = 16 * MT;
-  constexpr int W = sr_waves(TRAIN), NT = 16 / W;
+  constexpr int NT = TRAIN ? 1 : 2;  // column tiles at a time per wave
   constexpr bool PRE = MT == 1;
   const int H = a.H, O = a.O, B = a.B, e = blockIdx.y;
   const int ldx = SG_K0 + 8, ldh = H + 8, ldo = O + 8, ldz = H + 4, ldd = O + 4;
@@ -1057,16 +1064,16 @@ AdamArgs next_adam(soap_surrogate* s, float lr) {
   return AdamArgs{lr, b1, b2, eps, 1.0f - powf(b1, (float)s->step), 1.0f - powf(b2, (float)s->step)};
 }
 
-template <int MT, bool TRAIN>
+template <int MT, bool TRAIN, int W>
 hipError_t launch_rows(soap_surrogate* s, const SgRows& a) {
   const size_t lds = sg_rows_lds(16 * MT, a.H, a.O, TRAIN);
   if (lds > 64 * 1024) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_sg_rows<MT, TRAIN>),
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_sg_rows<MT, TRAIN, W>),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL((k_sg_rows<MT, TRAIN>), dim3((unsigned)((a.B + 16 * MT - 1) / (16 * MT)), s->n_ens),
-                     dim3(64 * sr_waves(TRAIN)), lds, s->stream, a);
+  hipLaunchKernelGGL((k_sg_rows<MT, TRAIN, W>), dim3((unsigned)((a.B + 16 * MT - 1) / (16 * MT)), s->n_ens),
+                     dim3(64 * W), lds, s->stream, a);
   return hipGetLastError();
 }
 
@@ -1101,7 +1108,9 @@ hipError_t sg_rows_forward(soap_surrogate* s, const float* x, int B, float* Y) {
   SgRows a = rows_args(s, x, B);
   a.Y = Y;
   const bool wide = (int64_t)B * s->n_ens >= 16 * SR_MT * 512 && 2 * sg_rows_lds(16 * SR_MT, a.H, a.O, false) <= SR_LDS;
-  return wide ? launch_rows<SR_MT, false>(s, a) : launch_rows<1, false>(s, a);
+  if (a.H <= SR_NARROW_COLS && a.O <= SR_NARROW_COLS && (int64_t)B * s->n_ens >= SR_NARROW_ROWS)
+    return launch_rows<SR_MT, false, SR_NARROW>(s, a);
+  return wide ? launch_rows<SR_MT, false, SR_INFER>(s, a) : launch_rows<1, false, SR_INFER>(s, a);
 }
 
 hipError_t sg_rows_step(soap_surrogate* s, const float* x, const float* target, int B, float lr) {
@@ -1117,7 +1126,7 @@ hipError_t sg_rows_step(soap_surrogate* s, const float* x, const float* target, 
   a.dZ2f = s->dZf;
   a.dZ1f = s->dZf2;
   a.row_se = s->row_se;
-  SG_TRY((launch_rows<1, true>(s, a)));
+  SG_TRY((launch_rows<1, true, SR_TRAIN>(s, a)));
   const int H = a.H, O = a.O;
   SgGrads g{};
   g.B = B;

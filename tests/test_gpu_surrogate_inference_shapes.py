@@ -1,0 +1,41 @@
+"""Predictions of many rows, or of very wide networks, take other launch shapes
+than those of a few rows of ordinary ones: what a row's prediction is must not
+depend on how many rows are with it.  Every output is compared bit for bit with
+the same rows' in calls of at most 32 rows; the values themselves are tested
+against the oracle in test_gpu_surrogate_rows.py.
+"""
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+L = pytest.importorskip("paper_2301_04259_amd", reason="libsoap.so not built")
+
+
+@pytest.mark.parametrize(
+    "n_in,H,O,E,B",
+    [
+        (12, 32, 32, 16, 3072),  # narrow, the fewest rows of the two-wave blocks
+        (32, 64, 64, 8, 6160),   # narrow, every column tile used; the last block half full
+        (1, 64, 32, 5, 9872),    # a single input
+    ],
+)
+def test_rows_do_not_depend_on_the_batch(n_in, H, O, E, B):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    print(f"[sg-shapes] n_in {n_in} H {H} O {O} E {E} B {B}", flush=True)
+    rng = np.random.default_rng(B)
+    s = L.soap_surrogate_create(n_in, H, O, E, seed=5)
+    x = torch.as_tensor(rng.normal(size=(B, n_in)).astype(np.float32), device="cuda")
+    coef = torch.empty((B, O), dtype=torch.float32, device="cuda")
+    mem = torch.full((E + 1, B, O), 7.0, dtype=torch.float32, device="cuda")
+    L.soap_surrogate_predict(s, x, coef, mem[:E])
+    assert torch.all(mem[E] == 7.0)
+    for r in sorted({*range(0, B, max(32, B // 5 // 16 * 16)), B - 16}):
+        n = min(32, B - r)
+        c = torch.empty((n, O), dtype=torch.float32, device="cuda")
+        m = torch.empty((E, n, O), dtype=torch.float32, device="cuda")
+        L.soap_surrogate_predict(s, x[r:r + n].contiguous(), c, m)
+        assert torch.equal(m, mem[:E, r:r + n]) and torch.equal(c, coef[r:r + n]), r
