@@ -266,7 +266,7 @@ SOAP_API soap_status soap_surrogate_predict(soap_surrogate* s, const float* x_de
   SG_ARG(batch >= 16 && batch % 16 == 0 && batch <= (1 << 20), "batch must be a multiple of 16 in [16, 2^20]");
   const size_t n_mem = sizeof(float) * (size_t)s->n_ens * batch * s->n_out;
   bool copied = members_dev != nullptr;  // the members come from the library's buffer
-  if (soap::sg_rows_fit(s->hidden, s->n_out, false)) {
+  if (soap::sg_rows_predict(s, batch)) {
     // The row kernel writes members while other rows' inputs are still to be
     // read: straight to the caller's array unless that is over the inputs (or
     // the means, which are written before the members then).

@@ -69,6 +69,7 @@ hipError_t sg_backward(soap_surrogate* s, const float* target, int B);
 hipError_t sg_adam(soap_surrogate* s, float lr);
 // whether the rows of a block and their activations fit in LDS
 bool sg_rows_fit(int hidden, int n_out, bool train);
+bool sg_rows_predict(const soap_surrogate* s, int B);  // whether a prediction of B rows takes the row kernels
 // outputs of every member to Y[n_ens][B][n_out] (row kernel)
 hipError_t sg_rows_forward(soap_surrogate* s, const float* x, int B, float* Y);
 // one Adam step (row kernel, then weight gradients and update)

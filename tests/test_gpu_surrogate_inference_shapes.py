@@ -20,6 +20,8 @@ L = pytest.importorskip("paper_2301_04259_amd", reason="libsoap.so not built")
         (12, 32, 32, 16, 3072),  # narrow, the fewest rows of the two-wave blocks
         (32, 64, 64, 8, 6160),   # narrow, every column tile used; the last block half full
         (1, 64, 32, 5, 9872),    # a single input
+        (12, 1792, 32, 1, 240),  # wide, the fewest rows of the row kernel; of fewer the general kernels
+        (12, 2048, 96, 3, 352),  # wider, more columns and members
     ],
 )
 def test_rows_do_not_depend_on_the_batch(n_in, H, O, E, B):
