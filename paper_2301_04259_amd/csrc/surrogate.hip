@@ -15,7 +15,9 @@
 //
 // The PCA projection coef = (d - mean) V of spectra differences onto a basis
 // is an FP32 product on the matrix cores (K = pixels, large).
+#include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 #include "surrogate_internal.hpp"
 #include "wave.hpp"
@@ -842,18 +844,29 @@ constexpr int PCA_D = 3;   // steps of 16 pixels in flight per wave
 
 typedef float pca_f4 __attribute__((ext_vector_type(4), aligned(4)));  // any element alignment
 
-// C4: 16-byte loads from the rows of V (k a multiple of 4; lanes past k repeat
-// the last four components, which are not stored)
-template <int MT, bool C4>
+// C4 (k at least 4): 16-byte loads from the rows of V; a lane that would pass k
+// takes the last four components, and keeps those that are its own.
+// SPLIT: the waves of a block split the pixels of one row tile; else (many rows of
+// few pixels, where a wave had two or three steps and the block its sums to add:
+// 100000 rows, 161 pixels, 256 components 286 us) each takes a tile of its own,
+// and all pixels of it, 124 us.  There 16-row tiles are as fast as 32 or faster
+// (135 us) while D fits in the 256 MiB cache.
+template <int MT, bool C4, bool SPLIT>
 __global__ void __launch_bounds__(64 * PCA_W) k_pca_project(int n, int P, int k, const float* __restrict__ D,
                                                             int64_t ldd, const float* __restrict__ mean,
                                                             const int* __restrict__ mean_idx, int n_mean,
                                                             const float* __restrict__ V, float* __restrict__ coef) {
   __shared__ float s_part[PCA_W / 2][16 * MT][PCA_N + 4];
   const int l = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-  const int64_t r0 = (int64_t)blockIdx.x * 16 * MT;  // rows on x: up to 2^25 / 16 blocks
+  // rows on x: up to 2^25 / 16 blocks
+  const int64_t r0 = (SPLIT ? (int64_t)blockIdx.x : (int64_t)blockIdx.x * PCA_W + w) * 16 * MT;
   const int c0 = blockIdx.y * PCA_N;
+  constexpr int NW = SPLIT ? PCA_W : 1;  // waves of a row tile
+  const int first = SPLIT ? w : 0;
+  if (r0 >= n) return;  // never when SPLIT
   const int lk = 4 * (l >> 4), lc = c0 + 4 * (l & 15);
+  const int cl = C4 ? min(lc, k - 4) : lc;  // the lane's first component
+  const bool own = !C4 || cl == lc;         // all four are its own
   const float* drow[MT];
   const float* mrow[MT];
 #pragma unroll
@@ -865,7 +878,7 @@ __global__ void __launch_bounds__(64 * PCA_W) k_pca_project(int n, int P, int k,
   }
   unsigned vo[4];  // the lane's part of its offsets in V
 #pragma unroll
-  for (int c = 0; c < 4; ++c) vo[c] = (unsigned)lk * k + (C4 ? min(lc, k - 4) + c : min(lc + c, k - 1));
+  for (int c = 0; c < 4; ++c) vo[c] = (unsigned)lk * k + min(cl + c, k - 1);
   f32x4 acc[MT][4];
 #pragma unroll
   for (int a = 0; a < MT; ++a)
@@ -903,12 +916,17 @@ __global__ void __launch_bounds__(64 * PCA_W) k_pca_project(int n, int P, int k,
         for (int c = 0; c < 4; ++c)
           acc[a][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(o.d[a][s] - o.m[a][s], o.v[s][c], acc[a][c], 0, 0, 0);
   };
-  // whole steps of 16 pixels: step i of the wave starts at pixel 16 (w + PCA_W i)
+  // whole steps of 16 pixels: step i of the wave starts at pixel 16 (first + NW i)
   const int steps = P / 16;
-  const int mine = (steps - w + PCA_W - 1) / PCA_W;
+  const int mine = (steps - first + NW - 1) / NW;
+  // past them, a tile's only wave takes the last 16 pixels, if there are as many,
+  // and leaves out those that it has had: loads without a branch or a wait
+  const bool rest16 = !SPLIT && P % 16 && P > 16;
+  Step tail;
+  if (rest16) load(tail, P - 16);
   if (mine > 0) {
     Step o[PCA_D];
-    auto at = [&](int i) { return 16 * (w + PCA_W * min(i, mine - 1)); };
+    auto at = [&](int i) { return 16 * (first + NW * min(i, mine - 1)); };
 #pragma unroll
     for (int d = 0; d + 1 < PCA_D; ++d) load(o[d], at(d));
     for (int i0 = 0; i0 < mine; i0 += PCA_D) {
@@ -919,7 +937,20 @@ __global__ void __launch_bounds__(64 * PCA_W) k_pca_project(int n, int P, int k,
       }
     }
   }
-  if (P % 16 && w == steps % PCA_W) {  // the rest, by the wave whose turn it is: pixels past P are zeros
+  if (rest16) {
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const bool in = lk + s >= 16 - P % 16;
+#pragma unroll
+      for (int a = 0; a < MT; ++a) {
+        tail.d[a][s] = in ? tail.d[a][s] : 0.f;
+        tail.m[a][s] = in ? tail.m[a][s] : 0.f;
+      }
+#pragma unroll
+      for (int c = 0; c < 4; ++c) tail.v[s][c] = in ? tail.v[s][c] : 0.f;
+    }
+    multiply(tail);
+  } else if (P % 16 && first == steps % NW) {  // the rest, by the wave whose turn it is: pixels past P are zeros
     Step o;
     const int p = 16 * steps;
 #pragma unroll
@@ -936,6 +967,29 @@ __global__ void __launch_bounds__(64 * PCA_W) k_pca_project(int n, int P, int k,
     multiply(o);
   }
   // partial tiles: lane l ends with row 4 (l / 16) + r, component 4 (l % 16) + c.
+  if constexpr (!SPLIT) {
+#pragma unroll
+    for (int a = 0; a < MT; ++a)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int64_t row = r0 + 16 * a + 4 * (l >> 4) + r;
+        if (row >= n) continue;
+        const int mi = mean_idx ? mean_idx[row] : 0;
+        const bool bad = mi < 0 || mi >= n_mean;
+        pca_f4 v;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) v[c] = bad ? __builtin_nanf("") : acc[a][c][r];
+        float* o = coef + row * k + cl;
+        if (C4 && own) {
+          *reinterpret_cast<pca_f4*>(o) = v;
+        } else {
+#pragma unroll
+          for (int c = 0; c < 4; ++c)
+            if (cl + c >= lc && cl + c < k) o[c] = v[c];
+        }
+      }
+    return;
+  }
   // The upper half of the waves hands its tiles to the lower half, which adds
   // them to its own; then every output adds the PCA_W / 2 sums in order.
   auto put = [&](int slot) {
@@ -960,9 +1014,11 @@ __global__ void __launch_bounds__(64 * PCA_W) k_pca_project(int n, int P, int k,
   __syncthreads();
   for (int t = threadIdx.x; t < 16 * MT * PCA_N; t += 64 * PCA_W) {
     const int i = t / PCA_N, j = t - i * PCA_N;
+    const int past = C4 ? max(c0 + (j & ~3) + 4 - k, 0) : 0;  // components of the lane's four that lie before its own
+    const int at = min(j + past, PCA_N - 1);                  // (past k: not stored)
     float v = 0.f;
 #pragma unroll
-    for (int q = 0; q < PCA_W / 2; ++q) v += s_part[q][i][j];
+    for (int q = 0; q < PCA_W / 2; ++q) v += s_part[q][i][at];
     const int64_t row = r0 + i;
     if (row >= n || c0 + j >= k) continue;
     const int mi = mean_idx ? mean_idx[row] : 0;
@@ -1210,14 +1266,22 @@ hipError_t sg_pca_project(hipStream_t st, int n, int P, int k, const float* D, i
   // 32-row tiles read V half as often, once they still give every CU two blocks
   // (8192 x 128: 482 us against 676; 2048 x 128, 128 blocks of them: 297 against 209)
   const bool wide = (int64_t)((n + 31) / 32) * nb >= 512;
-  const dim3 grid((unsigned)(wide ? (n + 31) / 32 : (n + 15) / 16), nb), block(64 * PCA_W);
+  // a row tile to each wave once the tiles fill the chip, the sooner the fewer the
+  // pixels (split and not, us: 8000 rows x 128 components, 1000 tiles, 192 pixels 14
+  // and 11.5, 512 pixels 20 and 24; 20000 x 256, 5000 tiles, 800 pixels 108 and 97,
+  // 2000 pixels 217 and 230)
+  const bool split = P > std::min((int64_t)1024, (int64_t)((n + 15) / 16) * nb / 5);
+  const int tiles = split && wide ? (n + 31) / 32 : (n + 15) / 16;
+  const dim3 grid((unsigned)(split ? tiles : (tiles + PCA_W - 1) / PCA_W), nb), block(64 * PCA_W);
   auto go = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, grid, block, 0, st, n, P, k, D, ldd, mean, mean_idx, mean_idx ? n_mean : 1, V, coef);
   };
-  if (k % 4 == 0)
-    wide ? go(k_pca_project<2, true>) : go(k_pca_project<1, true>);
-  else
-    wide ? go(k_pca_project<2, false>) : go(k_pca_project<1, false>);
+  auto by_rows = [&](auto c4) {
+    constexpr bool C4 = decltype(c4)::value;
+    if (!split) go(k_pca_project<1, C4, false>);
+    else wide ? go(k_pca_project<2, C4, true>) : go(k_pca_project<1, C4, true>);
+  };
+  k >= 4 ? by_rows(std::true_type()) : by_rows(std::false_type());
   return hipGetLastError();
 }
 
