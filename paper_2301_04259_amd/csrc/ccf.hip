@@ -9,7 +9,7 @@
 // The line positions, the hole edges per velocity and the split of the mask
 // into blocks of lines and batches of nearby lines are built on the host
 // once per mask.  Layout: one block per (block of lines, block of SB
-// spectra), one thread per velocity (two past 512); each thread keeps SB
+// spectra), one thread per velocity (two or three past 512); each thread keeps SB
 // accumulators and reuses its hole geometry for every spectrum of the block.
 // Partial sums per line block are added in a fixed order by the fit kernel,
 // so results repeat bit for bit.
@@ -36,7 +36,7 @@ constexpr int CCF_SB = 8;         // spectra per block
 constexpr int CCF_FEW = 2;        // and in calls of few blocks,
 constexpr int CCF_AHEAD = 3;      // with this many batches of loads in flight
 constexpr int CCF_FEW_WAVES = 640;  // few: blocks of CCF_SB with fewer waves than this in all
-constexpr int CCF_THREADS = 512;  // most threads of a block: one per velocity, two velocities each past 512
+constexpr int CCF_THREADS = 512;  // most threads of a block: one per velocity, more velocities each past 512
 constexpr int CCF_MIN_THREADS = 192;  // fewest: the block also stages the pixels
 constexpr int CCF_NV_MAX = 768;   // velocities per grid
 constexpr int CCF_STG_MAX = 512;  // widest staged span of a batch, in pixels
@@ -48,6 +48,16 @@ int ccf_line_blocks(int n_lines) { return (n_lines + CCF_LB - 1) / CCF_LB; }
 int ccf_span_pixels(bool) { return CCF_STG_MAX; }
 
 namespace {
+
+// Velocities of a thread past CCF_THREADS: two, and of float spectra three, whose
+// weights in double cost as much as their products (768 velocities, FP32, 100
+// spectra of 100003 pixels, 4000 lines and holes of 1.6 km/s: 163 us with two, 126
+// with three, 154 with four; FP64, 700 spectra of 20000 pixels, 400 lines: 155, 177
+// and 222).
+template <typename T>
+constexpr int CCF_MORE = sizeof(T) == 4 ? 3 : 2;
+// most threads of a block of A velocities each
+constexpr int ccf_max_threads(int a) { return a == 1 ? CCF_THREADS : 64 * ((CCF_NV_MAX + 64 * a - 1) / (64 * a)); }
 
 // the spectra of a pixel, in pieces of at most 16 bytes
 template <typename T, int SB>
@@ -223,7 +233,7 @@ __device__ __forceinline__ void ccf_block(int P, int64_t n_spec, const T* __rest
 }
 
 template <typename T, int A, int NPX, int STG, int SB, int PF>
-__global__ void __launch_bounds__(CCF_THREADS) k_ccf(int P, int64_t n_spec, const T* __restrict__ F,
+__global__ void __launch_bounds__(ccf_max_threads(A)) k_ccf(int P, int64_t n_spec, const T* __restrict__ F,
                                                      const double2* __restrict__ lines,
                                                      const double2* __restrict__ edges,
                                                      const int4* __restrict__ batches,
@@ -235,7 +245,7 @@ __global__ void __launch_bounds__(CCF_THREADS) k_ccf(int P, int64_t n_spec, cons
 // Work-list form over many spectra sets with one mask layout: blk[b] =
 // (set, line block, spectrum block).
 template <typename T, int A, int NPX, int STG>
-__global__ void __launch_bounds__(CCF_THREADS) k_ccf_batch(const CcfBatchSet* __restrict__ sets,
+__global__ void __launch_bounds__(ccf_max_threads(A)) k_ccf_batch(const CcfBatchSet* __restrict__ sets,
                                                            const int4* __restrict__ blk, int n_v) {
   const int4 t = blk[blockIdx.x];
   const CcfBatchSet c = sets[t.x];
@@ -838,7 +848,7 @@ template <typename T, int NPX, int STG>
 static void launch_ccf_n(const CcfPlan& q, hipStream_t st, const void* d_flux, int64_t n_spec,
                          void* d_part) {
   if (q.nv <= CCF_THREADS) launch_ccf_a<T, 1, NPX, STG>(q, st, d_flux, n_spec, d_part);
-  else launch_ccf_a<T, 2, NPX, STG>(q, st, d_flux, n_spec, d_part);
+  else launch_ccf_a<T, CCF_MORE<T>, NPX, STG>(q, st, d_flux, n_spec, d_part);
 }
 
 template <typename T, int STG>
@@ -948,7 +958,7 @@ void launch_ccf_batch_a(const CcfBatch& cb, hipStream_t st) {
 template <typename T, int NPX, int STG>
 void launch_ccf_batch_n(const CcfBatch& cb, hipStream_t st) {
   if (cb.shape.nv <= CCF_THREADS) launch_ccf_batch_a<T, 1, NPX, STG>(cb, st);
-  else launch_ccf_batch_a<T, 2, NPX, STG>(cb, st);
+  else launch_ccf_batch_a<T, CCF_MORE<T>, NPX, STG>(cb, st);
 }
 
 template <typename T, int STG>
