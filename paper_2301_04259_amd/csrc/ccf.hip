@@ -1259,10 +1259,11 @@ __global__ void __launch_bounds__(64) k_sg_fit(int64_t n, int n_v, double v0, do
   }
 }
 
-// EB: members, rounded up; W waves per block, 32 components each at a time.  With
-// few components fewer waves per block, and LDS for the velocities there are, so
-// that more blocks are in flight: 8 members, 32 components, 41 velocities, 20000
-// samples 99 us with four waves and room for 192 velocities, 41 so.
+// EB: members, rounded up; W waves per block, 32 components each at a time.  In
+// calls of many blocks with few components fewer waves per block, and LDS for the
+// velocities there are, so that more blocks are in flight: 8 members, 32
+// components, 41 velocities, 20000 samples 99 us with four waves and room for 192
+// velocities, 41 so.
 template <int EB, int W>
 __global__ void __launch_bounds__(64 * W) k_sg_spread(int64_t n, int k, int E, int n_v,
                                                          const float* __restrict__ coef,
@@ -1430,7 +1431,12 @@ void launch_sg_rv_n(soap_ctx* c, const float* d_coef, const float* d_members, in
   const size_t lds = sizeof(double) * 16 * sg_spread_ld(c->mask_nv);
   auto spread = [&](auto eb) {
     constexpr int EB = decltype(eb)::value;
-    const int w = k <= 32 ? 1 : (k <= 64 ? 2 : 4);
+    // Up to a block per CU the waves past the components still stage (call times
+    // with one, two and four waves, 32 components, 401 velocities, us: 960 samples
+    // of 2 members 53, 52 and 48; 6000 of 2 100, 96 and 98; 6000 of 8 123, 119 and
+    // 139).  One wave pays past two blocks per CU of more than four members: 12000
+    // of 8 170, 192 and 206; 20000 of 2 231, 226 and 230.
+    const int w = k > 64 || grid.x <= 256 ? 4 : (k > 32 || EB <= 4 || grid.x <= 512 ? 2 : 1);
     auto* kernel = w == 1 ? &k_sg_spread<EB, 1> : (w == 2 ? &k_sg_spread<EB, 2> : &k_sg_spread<EB, 4>);
     hipLaunchKernelGGL(kernel, grid, dim3(64 * w), lds, c->stream, n, k, E, c->mask_nv, d_coef, d_members, d_basis, G,
                        flag, calib, thr, d_err, d_fallback);
