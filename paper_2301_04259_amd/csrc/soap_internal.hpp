@@ -184,9 +184,11 @@ struct StreamShare {
 };
 
 // Table sets a caller who is ahead may rotate through: with three, two calls
-// can be pending when the third's tables are built (their kernels are short,
-// so the host must not be held up); larger tables keep to two sets.
-constexpr size_t PREP_SMALL = 8 << 20;
+// can be pending when the third's tables are built.  With two the host waits for
+// the apply of the call before, and then the device for the host: 1200 phases of
+// 4096 pixels, 86 us a call with two sets of 9 MB, 76 with three.  Tables past
+// PREP_SMALL bytes take long enough to build and keep to two.
+constexpr size_t PREP_SMALL = 64 << 20;
 
 }  // namespace soap
 

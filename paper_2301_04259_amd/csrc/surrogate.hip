@@ -1159,10 +1159,10 @@ bool sg_rows_fit(int hidden, int n_out, bool train) { return sg_rows_lds(16, hid
 // very wide networks takes longer than the general kernels, whose blocks spread
 // the columns over the chip.  By the rows of all networks, row kernel and general
 // kernels in us: 1792 hidden units, 64 rows 81 and 77, 256 rows of 4 networks 82
-// and 90; 2048 units, 64 rows 102 and 84, 512 rows 98 and 92, 1024 rows
-// 89 and 110.  (1696 units: 80 and 84 at 64 rows, 79 and 76 at 16.)
+// and 90; 2048 units, 64 rows 102 and 84, 512 rows 98 and 92, 960 rows of 4
+// 109 and 105; 2176 units, 960 rows of 4 123 and 135.  (1696 units: 80 and 84 at 64 rows, 79 and 76 at 16.)
 bool sg_rows_predict(const soap_surrogate* s, int B) {
-  const int few = s->hidden < 1792 ? 0 : s->hidden < 2048 ? 240 : 1024;
+  const int few = s->hidden < 1792 ? 0 : s->hidden < 2048 ? 240 : 960;
   return sg_rows_fit(s->hidden, s->n_out, false) && (int64_t)B * s->n_ens >= few;
 }
 
