@@ -824,12 +824,6 @@ soap_status active_impl(soap_ctx* c, const soap_region* regions, int32_t n_regio
   hipStream_t st = nullptr;
   HIP_TRY(choose_prep(c, TableSizes{{par_dev, kfx_bytes, k_bytes, m_bytes, vg_bytes, nvg_bytes}}, &sidx, &st));
   soap_ctx::Prep& S = c->prep[sidx];
-  if (S.kfx_dirty) {
-    // every call that accumulates also clears the accumulators, so they are
-    // zeroed only when new and after an interrupted call
-    HIP_TRY(hipMemsetAsync(S.part(soap::TAB_KFX), 0, S.at[soap::TAB_KFX + 1] - S.at[soap::TAB_KFX], st));
-    S.kfx_dirty = false;
-  }
   const int k = (int)(seq % soap_ctx::NSLOT);
   HIP_TRY(wait_started(c, seq - soap_ctx::NSLOT));
   if (c->slot_bytes[k] < par_bytes) {
@@ -886,6 +880,10 @@ soap_status active_impl(soap_ctx* c, const soap_region* regions, int32_t n_regio
     }
   } idle{st, c->stream};
   S.built = false;
+  // every call that accumulates also clears the accumulators, so they are
+  // zeroed only when new and after an interrupted call
+  if (S.kfx_dirty)
+    HIP_TRY(hipMemsetAsync(S.part(soap::TAB_KFX), 0, S.at[soap::TAB_KFX + 1] - S.at[soap::TAB_KFX], st));
   S.kfx_dirty = true;
   {
     StageTimer t(c, ST_WEIGHTS, st);
