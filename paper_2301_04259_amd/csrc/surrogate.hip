@@ -849,8 +849,8 @@ typedef float pca_f4 __attribute__((ext_vector_type(4), aligned(4)));  // any el
 // SPLIT: the waves of a block split the pixels of one row tile; else (many rows of
 // few pixels, where a wave had two or three steps and the block its sums to add:
 // 100000 rows, 161 pixels, 256 components 286 us) each takes a tile of its own,
-// and all pixels of it, 124 us.  There 16-row tiles are as fast as 32 or faster
-// (135 us) while D fits in the 256 MiB cache.
+// and all pixels of it, 129 us.  There 16-row tiles are as fast as 32 or faster
+// while D fits in the 256 MiB cache.
 template <int MT, bool C4, bool SPLIT>
 __global__ void __launch_bounds__(64 * PCA_W) k_pca_project(int n, int P, int k, const float* __restrict__ D,
                                                             int64_t ldd, const float* __restrict__ mean,
@@ -907,14 +907,34 @@ __global__ void __launch_bounds__(64 * PCA_W) k_pca_project(int n, int P, int k,
       }
     }
   };
-  auto multiply = [&](const Step& o) {
+  auto multiply = [&](const Step& o, f32x4 (&to)[MT][4]) {
 #pragma unroll
     for (int s = 0; s < 4; ++s)
 #pragma unroll
       for (int a = 0; a < MT; ++a)
 #pragma unroll
         for (int c = 0; c < 4; ++c)
-          acc[a][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(o.d[a][s] - o.m[a][s], o.v[s][c], acc[a][c], 0, 0, 0);
+          to[a][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(o.d[a][s] - o.m[a][s], o.v[s][c], to[a][c], 0, 0, 0);
+  };
+  auto add = [&](f32x4 (&to)[MT][4], const f32x4 (&x)[MT][4]) {
+#pragma unroll
+    for (int a = 0; a < MT; ++a)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) to[a][c] += x[a][c];
+  };
+  // A wave that has all pixels of its tile would round more in one chain than
+  // the split's eight do (2.3e-8 against 1.0e-8 of outputs of 0.1 for 161 pixels,
+  // 5.1e-8 against 1.9e-8 for 800): each step's products are a sum of their own
+  // there, and PCA_D of those are added before they go to the tile's
+  // (0.94e-8 and 1.1e-8).
+  auto take = [&](const Step& o, f32x4 (&to)[MT][4]) {
+    if constexpr (SPLIT) {
+      multiply(o, acc);
+    } else {
+      f32x4 x[MT][4] = {};
+      multiply(o, x);
+      add(to, x);
+    }
   };
   // whole steps of 16 pixels: step i of the wave starts at pixel 16 (first + NW i)
   const int steps = P / 16;
@@ -930,11 +950,13 @@ __global__ void __launch_bounds__(64 * PCA_W) k_pca_project(int n, int P, int k,
 #pragma unroll
     for (int d = 0; d + 1 < PCA_D; ++d) load(o[d], at(d));
     for (int i0 = 0; i0 < mine; i0 += PCA_D) {
+      f32x4 group[MT][4] = {};
 #pragma unroll
       for (int d = 0; d < PCA_D; ++d) {
         load(o[(d + PCA_D - 1) % PCA_D], at(i0 + d + PCA_D - 1));
-        if (i0 + d < mine) multiply(o[d]);
+        if (i0 + d < mine) take(o[d], group);
       }
+      if constexpr (!SPLIT) add(acc, group);
     }
   }
   if (rest16) {
@@ -949,7 +971,7 @@ __global__ void __launch_bounds__(64 * PCA_W) k_pca_project(int n, int P, int k,
 #pragma unroll
       for (int c = 0; c < 4; ++c) tail.v[s][c] = in ? tail.v[s][c] : 0.f;
     }
-    multiply(tail);
+    take(tail, acc);
   } else if (P % 16 && first == steps % NW) {  // the rest, by the wave whose turn it is: pixels past P are zeros
     Step o;
     const int p = 16 * steps;
@@ -964,7 +986,7 @@ __global__ void __launch_bounds__(64 * PCA_W) k_pca_project(int n, int P, int k,
 #pragma unroll
       for (int c = 0; c < 4; ++c) o.v[s][c] = in ? V[(int64_t)(p + s) * k + vo[c]] : 0.f;
     }
-    multiply(o);
+    take(o, acc);
   }
   // partial tiles: lane l ends with row 4 (l / 16) + r, component 4 (l % 16) + c.
   if constexpr (!SPLIT) {
@@ -1267,10 +1289,11 @@ hipError_t sg_pca_project(hipStream_t st, int n, int P, int k, const float* D, i
   // (8192 x 128: 482 us against 676; 2048 x 128, 128 blocks of them: 297 against 209)
   const bool wide = (int64_t)((n + 31) / 32) * nb >= 512;
   // a row tile to each wave once the tiles fill the chip, the sooner the fewer the
-  // pixels (split and not, us: 8000 rows x 128 components, 1000 tiles, 192 pixels 14
-  // and 11.5, 512 pixels 20 and 24; 20000 x 256, 5000 tiles, 800 pixels 108 and 97,
-  // 2000 pixels 217 and 230)
-  const bool split = P > std::min((int64_t)1024, (int64_t)((n + 15) / 16) * nb / 5);
+  // pixels (split and not, us: 8000 rows x 128 components, 1000 tiles, 128 pixels
+  // 13.6 and 10.4, 512 pixels 20 and 24; 20000 x 128, 2500 tiles, 256 pixels 32 and
+  // 27, 401 pixels 38 and 41; 20000 x 256, 5000 tiles, 512 pixels 87 and 68, 800
+  // pixels 108 and 105)
+  const bool split = P > std::min((int64_t)1024, (int64_t)((n + 15) / 16) * nb / 7);
   const int tiles = split && wide ? (n + 31) / 32 : (n + 15) / 16;
   const dim3 grid((unsigned)(split ? tiles : (tiles + PCA_W - 1) / PCA_W), nb), block(64 * PCA_W);
   auto go = [&](auto kernel) {

@@ -22,10 +22,10 @@ def _dev(a):
     "n,P,k",
     [
         (160, 1, 1),         # one pixel of one component, the last block with two tiles
-        (1281, 15, 3),       # no whole step; one row past the tiles
+        (1681, 15, 3),       # no whole step; one row past the tiles
         (1601, 16, 66),      # one whole step, four components that begin before the second tile
         (2047, 17, 4),       # one pixel past it
-        (4109, 47, 63),
+        (5309, 47, 63),
         (16385, 161, 130),   # ten steps, three component tiles
     ],
 )
