@@ -168,6 +168,24 @@ soap_status ensure_batch(soap_surrogate* s, int B) {
   return SOAP_OK;
 }
 
+// whether the buffers of the general kernels are there for B rows, or could be
+// had: not while the stream is being captured, nor past the memory there is
+bool have_batch(soap_surrogate* s, int B) {
+  if (B <= s->cap) return true;
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s->stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) return false;
+  if (ensure_batch(s, B) == SOAP_OK) return true;
+  (void)hipGetLastError();
+  s->cap = 0;
+  auto drop = [](auto*& p) {
+    if (p) (void)soap::dev_free(p);
+    p = nullptr;
+  };
+  for (__bf16** p : {&s->X, &s->H1, &s->H2, &s->dY, &s->dZb, &s->dZb2}) drop(*p);
+  for (float** p : {&s->Z1, &s->Z2, &s->dYf, &s->dZf, &s->dZf2, &s->row_se, &s->colpart}) drop(*p);
+  return false;
+}
+
 constexpr uint32_t SG_MAGIC = 0x53475231u;  // file tag
 
 }  // namespace
@@ -266,7 +284,10 @@ SOAP_API soap_status soap_surrogate_predict(soap_surrogate* s, const float* x_de
   SG_ARG(batch >= 16 && batch % 16 == 0 && batch <= (1 << 20), "batch must be a multiple of 16 in [16, 2^20]");
   const size_t n_mem = sizeof(float) * (size_t)s->n_ens * batch * s->n_out;
   bool copied = members_dev != nullptr;  // the members come from the library's buffer
-  if (soap::sg_rows_predict(s, batch)) {
+  // (few rows of a very wide network that the row kernels hold: the general ones
+  // are faster, where their buffers can be had)
+  if (soap::sg_rows_predict(s, batch) ||
+      (soap::sg_rows_fit(s->hidden, s->n_out, false) && !have_batch(s, batch))) {
     // The row kernel writes members while other rows' inputs are still to be
     // read: straight to the caller's array unless that is over the inputs (or
     // the means, which are written before the members then).

@@ -41,3 +41,44 @@ def test_rows_do_not_depend_on_the_batch(n_in, H, O, E, B):
         m = torch.empty((E, n, O), dtype=torch.float32, device="cuda")
         L.soap_surrogate_predict(s, x[r:r + n].contiguous(), c, m)
         assert torch.equal(m, mem[:E, r:r + n]) and torch.equal(c, coef[r:r + n]), r
+
+
+@pytest.mark.parametrize("members", [False, True])
+def test_few_rows_of_a_wide_network_without_memory(monkeypatch, members):
+    """After a call of many rows, one of few is refused neither under a byte cap
+    nor in a captured graph; its outputs are the same."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    H, O, E, B = 1792, 64, 2, 512
+    rng = np.random.default_rng(7)
+    x = torch.as_tensor(rng.normal(size=(B, 12)).astype(np.float32), device="cuda")
+    few = x[:32].contiguous()
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        s = L.soap_surrogate_create(12, H, O, E, seed=5)
+
+        def call(x):
+            coef = torch.zeros((len(x), O), dtype=torch.float32, device="cuda")
+            mem = torch.zeros((E, len(x), O), dtype=torch.float32, device="cuda") if members else None
+            L.soap_surrogate_predict(s, x, coef, mem)
+            return coef, mem
+
+        want, mem = call(x)
+        monkeypatch.setenv("SOAP_MAX_DEVICE_BYTES", str(L.device_bytes() + 4096))
+        held = L.device_bytes()
+        got, m = call(few)
+        assert torch.equal(got, want[:32]) and (not members or torch.equal(m, mem[:, :32]))
+        assert L.device_bytes() == held
+        monkeypatch.delenv("SOAP_MAX_DEVICE_BYTES")
+        coef = torch.zeros((32, O), dtype=torch.float32, device="cuda")
+        m = torch.zeros((E, 32, O), dtype=torch.float32, device="cuda") if members else None
+        stream.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=stream):
+            L.soap_surrogate_predict(s, few, coef, m)
+        for _ in range(3):
+            coef.zero_()
+            g.replay()
+            assert torch.equal(coef, want[:32])
+        got, m = call(few)  # (the general kernels)
+        assert torch.equal(got, want[:32]) and (not members or torch.equal(m, mem[:, :32]))
