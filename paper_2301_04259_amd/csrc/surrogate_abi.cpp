@@ -124,7 +124,8 @@ soap_status ensure_y(soap_surrogate* s, int B) {
   return SOAP_OK;
 }
 
-// training buffers of the row kernels
+// training buffers of the row kernels, and the outputs of a prediction of as
+// many rows, which may then be captured
 soap_status ensure_rows(soap_surrogate* s, int B) {
   if (B <= s->cap_rows) return SOAP_OK;
   SG_HIP(hipStreamSynchronize(s->stream));
@@ -137,6 +138,10 @@ soap_status ensure_rows(soap_surrogate* s, int B) {
   SG_HIP(alloc(s->dZf, E * B * H));
   SG_HIP(alloc(s->dZf2, E * B * H));
   SG_HIP(alloc(s->row_se, E * B));
+  {
+    const soap_status st = ensure_y(s, B);
+    if (st != SOAP_OK) return st;
+  }
   s->cap_rows = B;
   return SOAP_OK;
 }

@@ -82,3 +82,26 @@ def test_few_rows_of_a_wide_network_without_memory(monkeypatch, members):
             assert torch.equal(coef, want[:32])
         got, m = call(few)  # (the general kernels)
         assert torch.equal(got, want[:32]) and (not members or torch.equal(m, mem[:, :32]))
+
+
+@pytest.mark.parametrize("H", [64, 800])  # trained by the row kernels, by the general ones
+def test_prediction_captured_after_training(H):
+    """A training step leaves the buffers that a prediction of its batch needs:
+    one can be captured without an eager call before it."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        s = L.soap_surrogate_create(12, H, 32, 2, seed=5)
+        x, t = torch.randn(64, 12, device="cuda"), torch.randn(64, 32, device="cuda")
+        L.soap_surrogate_train_step(s, x, t, 1e-3)
+        coef, want = (torch.zeros((64, 32), dtype=torch.float32, device="cuda") for _ in range(2))
+        stream.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=stream):
+            L.soap_surrogate_predict(s, x, coef)
+        L.soap_surrogate_predict(s, x, want)
+        for _ in range(3):
+            coef.zero_()
+            g.replay()
+            assert torch.equal(coef, want)
